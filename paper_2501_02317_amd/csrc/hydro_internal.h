@@ -152,6 +152,23 @@ struct StageLaunch {
     dim3 grid, block;
     StageArgs args;
 };
+// Launch context of the stage dispatch: a single mesh (args) or a batch group
+// (descriptor table); with rec, a single-mesh launch is described there
+// instead of enqueued.
+struct LaunchCtx {
+    const StageArgs* a;
+    const MeshDesc* d;
+    const int2* blk;
+    int nblk;
+    StageLaunch* rec;
+};
+hipError_t launch_stage_1d_fp64(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
+hipError_t launch_stage_1d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
+hipError_t launch_stage_2d_fp64(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
+hipError_t launch_stage_2d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
+hipError_t launch_stage_3d_fp64(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
+hipError_t launch_stage_3d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
+
 hipError_t plan_stage_launch(int precision, int mode, const Tile& tile, StageArgs a, StageLaunch* out);
 // Fill the tiling fields of a descriptor for a tile.
 void plan_tiles(const Geo& g, const Tile& t, int& tiles_x, int& tiles_y, int& chunks_z, int& kz);

@@ -31,6 +31,13 @@
 
 #include "hydro_internal.h"
 
+// The part of this file that a translation unit compiles: 0 everything but
+// the stage kernels, 1 .. 6 the stage kernels of one dimensionality and
+// precision (see the dispatch below).
+#ifndef HYDRO_PART
+#define HYDRO_PART 0
+#endif
+
 #pragma clang fp contract(off)
 
 namespace hydro {
@@ -1989,16 +1996,6 @@ int grid_for(long long work, int block, int cap) {
     return (int)(gb < cap ? gb : cap);
 }
 
-// Launch context: a single mesh (args) or a batch group (descriptor table);
-// with rec, a single-mesh launch is described there instead of enqueued.
-struct LaunchCtx {
-    const StageArgs* a;
-    const MeshDesc* d;
-    const int2* blk;
-    int nblk;
-    StageLaunch* rec;
-};
-
 // Work-groups of this stage kernel resident on the whole device at once
 // (0 if the runtime cannot tell).
 template <int NDIM, typename R, int MODE, int TX, int TY>
@@ -2099,22 +2096,49 @@ hipError_t launch_stage_mode(int mode, const Tile& t, const LaunchCtx& L, hipStr
     }
 }
 
-template <int NDIM>
-hipError_t launch_stage_prec(int precision, int mode, const Tile& t, const LaunchCtx& L, hipStream_t s) {
-    if (precision == 0) return launch_stage_mode<NDIM, double>(mode, t, L, s);
-    return launch_stage_mode<NDIM, float>(mode, t, L, s);
-}
+}  // namespace
 
+// The stage kernels of one dimensionality and precision, each compiled as a
+// translation unit of its own (HYDRO_PART 1 .. 6).
+#if HYDRO_PART == 1
+hipError_t launch_stage_1d_fp64(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s) {
+    return launch_stage_mode<1, double>(mode, t, L, s);
+}
+#elif HYDRO_PART == 2
+hipError_t launch_stage_1d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s) {
+    return launch_stage_mode<1, float>(mode, t, L, s);
+}
+#elif HYDRO_PART == 3
+hipError_t launch_stage_2d_fp64(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s) {
+    return launch_stage_mode<2, double>(mode, t, L, s);
+}
+#elif HYDRO_PART == 4
+hipError_t launch_stage_2d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s) {
+    return launch_stage_mode<2, float>(mode, t, L, s);
+}
+#elif HYDRO_PART == 5
+hipError_t launch_stage_3d_fp64(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s) {
+    return launch_stage_mode<3, double>(mode, t, L, s);
+}
+#elif HYDRO_PART == 6
+hipError_t launch_stage_3d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s) {
+    return launch_stage_mode<3, float>(mode, t, L, s);
+}
+#else
+
+namespace {
 hipError_t launch_any(int ndim, int precision, int mode, const Tile& t, const LaunchCtx& L,
                       hipStream_t s) {
-    switch (ndim) {
-        case 1: return launch_stage_prec<1>(precision, mode, t, L, s);
-        case 2: return launch_stage_prec<2>(precision, mode, t, L, s);
-        case 3: return launch_stage_prec<3>(precision, mode, t, L, s);
+    switch (2 * ndim + (precision == 0 ? 0 : 1)) {
+        case 2: return launch_stage_1d_fp64(mode, t, L, s);
+        case 3: return launch_stage_1d_mixed(mode, t, L, s);
+        case 4: return launch_stage_2d_fp64(mode, t, L, s);
+        case 5: return launch_stage_2d_mixed(mode, t, L, s);
+        case 6: return launch_stage_3d_fp64(mode, t, L, s);
+        case 7: return launch_stage_3d_mixed(mode, t, L, s);
         default: return hipErrorInvalidValue;
     }
 }
-
 }  // namespace
 
 Tile default_tile(const Geo& g, int precision, int mode) {
@@ -2427,5 +2451,7 @@ hipError_t launch_riemann(int precision, int ntan, double gamma, long long n, co
 #undef RK
     return hipGetLastError();
 }
+
+#endif  // HYDRO_PART
 
 }  // namespace hydro
