@@ -229,9 +229,9 @@ int hydro_padded_primitive(hydro_t h, double* Wpad_host);
 /* Tile of a stage kernel: a work-group covers tx x ty cells of the (x, y)
  * plane (3-D: 32x8, 64x8, 16x16 or 32x16; 1-D and 2-D: 64, 128 or 256 by 1)
  * and marches along the last active axis over chunks of kz planes.  kz = 0
- * (2-D and 3-D) picks the chunk length at each launch so that one round of
- * the work-groups the device holds at once covers the mesh (at least 16 and
- * at most 128 planes; in a batch, about 2048 work-groups per member).  The
+ * (2-D and 3-D) picks the chunk length, 1 to 128 planes, by a model of the
+ * march from the mesh and the work-groups the device holds at once (in a
+ * batch, one length per launch group from all its members' meshes). The
  * two stages have a tile each (the stage right-hand side uses stage 1's;
  * a batch uses each member's stage-1 tile for both stages).  Every face flux
  * is the same function of the same inputs for any tile, so the results are

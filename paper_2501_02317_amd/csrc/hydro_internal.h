@@ -144,6 +144,24 @@ enum StageMode : int {
     MODE_VL2_CORR_C = 6
 };
 
+// The automatic chunk length (Tile::kz == 0), 1 .. kMaxAutoKz planes, of a
+// launch over the columns m[0 .. n) (each marches over n2 planes) by a kernel
+// of the given residency; and the length that gives a column the same number
+// of chunks in the most equal parts.
+constexpr int kMaxAutoKz = 128;
+struct Slots {
+    int cus, per_cu;  // CUs of the device, work-groups of the kernel resident on each
+    int waves;        // waves of a work-group
+};
+struct MarchCols {
+    long long cols;
+    int n2;
+    bool even;  // every XCD's range of work-groups holds whole blocks
+};
+int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n);
+int balanced_kz(int n2, int kz);
+Slots stage_residency(int ndim, int precision, int mode, const Tile& t);
+
 hipError_t launch_stage(int precision, int mode, const Tile& tile, StageArgs a, hipStream_t s);
 // The same launch described (kernel, grid, block, arguments) instead of
 // enqueued, for a caller that adds it to a graph as a kernel node.
@@ -154,13 +172,15 @@ struct StageLaunch {
 };
 // Launch context of the stage dispatch: a single mesh (args) or a batch group
 // (descriptor table); with rec, a single-mesh launch is described there
-// instead of enqueued.
+// instead of enqueued; with slots, nothing is launched and the kernel's
+// residency is written there.
 struct LaunchCtx {
     const StageArgs* a;
     const MeshDesc* d;
     const int2* blk;
     int nblk;
     StageLaunch* rec;
+    Slots* slots;
 };
 hipError_t launch_stage_1d_fp64(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
 hipError_t launch_stage_1d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
@@ -170,7 +190,8 @@ hipError_t launch_stage_3d_fp64(int mode, const Tile& t, const LaunchCtx& L, hip
 hipError_t launch_stage_3d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
 
 hipError_t plan_stage_launch(int precision, int mode, const Tile& tile, StageArgs a, StageLaunch* out);
-// Fill the tiling fields of a descriptor for a tile.
+// Fill the tiling fields of a descriptor for a tile (kz == 0 counts as 1: the
+// caller resolves the automatic length).
 void plan_tiles(const Geo& g, const Tile& t, int& tiles_x, int& tiles_y, int& chunks_z, int& kz);
 // One stage over every mesh of a group sharing ndim, precision and tile:
 // blk[i] = (member, work-group within the member), nblk entries.
@@ -225,9 +246,6 @@ hipError_t launch_dt_levels(const Geo& g0, const LevelStarts& starts, int nblk, 
 // Default tile for a mesh (kernel axes) and precision.
 Tile default_tile(const Geo& g, int precision, int mode);
 // Whether the stage kernel is compiled for this tile shape.
-// Bounds of the automatic chunk length (Tile::kz == 0).
-constexpr int kMinAutoKz = 16;
-constexpr int kMaxAutoKz = 128;
 
 bool tile_supported(int ndim, const Tile& t);
 // Tiles the autotuner tries for a mesh (at most max written); returns how

@@ -1996,38 +1996,39 @@ int grid_for(long long work, int block, int cap) {
     return (int)(gb < cap ? gb : cap);
 }
 
-// Work-groups of this stage kernel resident on the whole device at once
-// (0 if the runtime cannot tell).
+// What the device holds of this stage kernel at once (zero if the runtime
+// cannot tell).
 template <int NDIM, typename R, int MODE, int TX, int TY>
-int stage_slots() {
-    static const int slots = [] {
-        int dev = 0, cus = 0, nb = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+Slots stage_slots() {
+    static const Slots slots = [] {
+        Slots o{0, 0, (TX * TY + 63) / 64};
+        int dev = 0, nb = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return Slots{0, 0, 0};
+        if (hipDeviceGetAttribute(&o.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            return Slots{0, 0, 0};
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
                 &nb, reinterpret_cast<const void*>(&stage_kernel<NDIM, R, MODE, TX, TY>), TX * TY, 0) !=
             hipSuccess)
-            return 0;
-        return cus * nb;
+            return Slots{0, 0, 0};
+        o.per_cu = nb;
+        return o;
     }();
     return slots;
 }
 
 template <int NDIM, typename R, int MODE, int TX, int TY>
 hipError_t launch_stage_t(const LaunchCtx& L, hipStream_t s) {
-    if (L.a) {
+    if (L.slots) {
+        *L.slots = stage_slots<NDIM, R, MODE, TX, TY>();
+    } else if (L.a) {
         StageArgs a = *L.a;
         if (a.kz == 0) {
-            // automatic chunk length: one round of resident work-groups
-            // covers the blocks whose work runs at once (this launch's, or
-            // those of the launches on the other streams as well), so no
-            // work-group waits for a second round
-            const int slots = stage_slots<NDIM, R, MODE, TX, TY>();
-            const long long cols = (long long)a.tiles_x * a.tiles_y * (a.conc > a.nblk ? a.conc : a.nblk);
+            // automatic chunk length for the blocks whose work runs at once
+            // (this launch's, or those of the launches on the other streams
+            // as well)
             const int n2 = a.geo.n[2];
-            long long kz = slots > 0 ? (n2 * cols + slots - 1) / slots : 32;
-            kz = kz < kMinAutoKz ? kMinAutoKz : (kz > kMaxAutoKz ? kMaxAutoKz : kz);
-            a.kz = kz > n2 ? n2 : (int)kz;
+            const MarchCols m{(long long)a.tiles_x * a.tiles_y * (a.conc > a.nblk ? a.conc : a.nblk), n2, a.nblk % 8 == 0};
+            a.kz = auto_kz(NDIM, stage_slots<NDIM, R, MODE, TX, TY>(), &m, 1);
             a.chunks_z = (n2 + a.kz - 1) / a.kz;
         }
         const long long nb = (long long)a.tiles_x * a.tiles_y * a.chunks_z * a.nblk;
@@ -2054,7 +2055,7 @@ hipError_t launch_stage_t(const LaunchCtx& L, hipStream_t s) {
 // each: a refined handle is not autotuned.
 template <int NDIM, typename R, int MODE>
 hipError_t launch_stage_refined(const Tile& t, const LaunchCtx& L, hipStream_t s) {
-    if (!L.a) return hipErrorInvalidValue;
+    if (!L.a && !L.slots) return hipErrorInvalidValue;
     if constexpr (NDIM == 3) {
         if (t.tx == 32 && t.ty == 8) return launch_stage_t<NDIM, R, MODE, 32, 8>(L, s);
     } else {
@@ -2084,7 +2085,7 @@ template <int NDIM, typename R>
 hipError_t launch_stage_mode(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s) {
     switch (mode) {
         case MODE_RHS:
-            if (!L.a) return hipErrorInvalidValue;
+            if (!L.a && !L.slots) return hipErrorInvalidValue;
             return launch_stage_tile<NDIM, R, MODE_RHS>(t, L, s);
         case MODE_STAGE1: return launch_stage_tile<NDIM, R, MODE_STAGE1>(t, L, s);
         case MODE_STAGE2: return launch_stage_tile<NDIM, R, MODE_STAGE2>(t, L, s);
@@ -2152,18 +2153,30 @@ Tile default_tile(const Geo& g, int precision, int mode) {
         // extra faces where the occupancy allows it; 32 x 8 where a larger
         // work-group would cost occupancy (the mixed Heun stages beside their
         // input rings; the FP64 kernels other than the double-buffered Heun
-        // stage 2).
+        // stage 2).  16 x 16 is 2-4 % behind those on a mesh that each fills
+        // (mixed; even in FP64) and takes over where it pads less: 48^3 mixed
+        // 28 against 31 us a step, 101 x 75 x 50 FP64 57 against 65 us.
         const bool narrow = precision == 1 ? (mode == MODE_STAGE2 || mode == MODE_STAGE1) : mode != MODE_STAGE2;
+        auto padded = [&](int tx, int ty) {
+            return (double)((g.n[0] + tx - 1) / tx * tx) * ((g.n[1] + ty - 1) / ty * ty);
+        };
         t.tx = 32;
         t.ty = narrow ? 8 : 16;
+        if (1.04 * padded(16, 16) < padded(t.tx, t.ty)) t.tx = t.ty = 16;
     } else if (g.ndim == 2) {
-        t.tx = g.n[0] >= 256 ? 256 : (g.n[0] >= 128 ? 128 : 64);
+        // the row width with the least padding, each row segment's halo and
+        // extra face counted as 24 cells (they take a wave of the work-group
+        // about a third of a plane): 256 for wide rows, 128 for rows of 384
+        t.tx = 256;
         t.ty = 1;
+        auto cost = [&](int tx) { return (double)((g.n[0] + tx - 1) / tx) * (tx + 24); };
+        for (int tx = 128; tx >= 64; tx /= 2)
+            if (cost(tx) < cost(t.tx)) t.tx = tx;
     } else {
         t.tx = 64;
         t.ty = 1;
     }
-    // chunk length chosen at launch (one round of resident work-groups)
+    // chunk length chosen at launch (auto_kz)
     t.kz = g.ndim == 1 ? 1 : 0;
     return t;
 }
@@ -2199,28 +2212,75 @@ int tile_candidates(const Geo& g, Tile* out, int max) {
     return n;
 }
 
-// Chunk length for tile t: t.kz, or with t.kz == 0 about 2048 work-groups in
-// chunks of 16..64 planes (shorter chunks re-read more ghost planes).
-int batch_kz(const Geo& g, const Tile& t) {
-    if (t.kz > 0) return t.kz;
-    if (g.ndim == 1) return 1;
-    const long long cols = (long long)((g.n[0] + t.tx - 1) / t.tx) * ((g.n[1] + t.ty - 1) / t.ty);
-    long long kz = (g.n[2] * cols + 2047) / 2048;
-    return (int)(kz < 16 ? 16 : (kz > 64 ? 64 : kz));
+int balanced_kz(int n2, int kz) {
+    kz = kz < 1 ? 1 : (kz > n2 ? n2 : kz);
+    const int chunks = (n2 + kz - 1) / kz;
+    return (n2 + chunks - 1) / chunks;
+}
+
+// The chunk length that a launch over the columns m[0 .. n) takes least time
+// with, by a model of the march: a work-group spends kz planes and a lead of
+// about two planes more (three in 2-D: the start of the z pipeline), and a
+// plane takes 1 + (w - 1)/3 with 4 w waves resident on the CU.  Fitted to
+// sweeps of both precisions and integrators from 32^3 to 160^3 and 64^2 to
+// 4096 x 1024: a plane's time is 2.6 us with four waves on a CU and 4.1 us
+// with twelve (mixed 3-D), so small meshes want a work-group per plane or two
+// (48^3 mixed: a step 102 us in chunks of 16, 28 us in chunks of 1-2; 256^2
+// FP64 89 and 21 us), and a last round of a few work-groups costs as much as a
+// full one (160^3 mixed: 316 us with 800 work-groups on 768 places, 225 us
+// with 700) -- unless the columns' last chunks are shorter by up to half and
+// every XCD has its share of them (blocks): then two of those take the time of
+// one of the others (192^3 van Leer in eight blocks: 361 us with 432 equal
+// work-groups on 512 places, 352 us with 576).
+int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n) {
+    if (ndim == 1) return 1;
+    int most = 1;
+    for (int i = 0; i < n; ++i) most = m[i].n2 > most ? m[i].n2 : most;
+    most = most > kMaxAutoKz ? kMaxAutoKz : most;
+    if (sl.cus < 1 || sl.per_cu < 1) return most < 32 ? most : 32;
+    const double lead = ndim == 3 ? 2.0 : 3.0;
+    const long long slots = (long long)sl.cus * sl.per_cu;
+    auto plane = [&](long long wgs) {
+        const double w = (double)((wgs + sl.cus - 1) / sl.cus) * sl.waves / 4.0;
+        return w > 1.0 ? 1.0 + (w - 1.0) / 3.0 : 1.0;
+    };
+    int best = most;
+    double least = 0.0;
+    for (int kz = most; kz >= 1; --kz) {
+        long long wgs = 0;
+        for (int i = 0; i < n; ++i) wgs += m[i].cols * ((m[i].n2 + kz - 1) / kz);
+        const long long full = wgs / slots, rest = wgs % slots;
+        double t = (kz + lead) * (full * plane(slots) + (rest ? plane(rest) : 0.0));
+        if (n == 1 && m[0].even && full == 1 && rest > 0 && rest <= m[0].cols) {
+            const int last = m[0].n2 - (m[0].n2 - 1) / kz * kz;
+            if (2.0 * (last + lead) >= kz + lead) t = std::fmin(t, plane(slots) * 2.0 * (last + lead));
+        }
+        if (kz == most || t <= least) {
+            least = t;
+            best = kz;
+        }
+    }
+    return best;
+}
+
+Slots stage_residency(int ndim, int precision, int mode, const Tile& t) {
+    Slots o{0, 0, 0};
+    LaunchCtx L{nullptr, nullptr, nullptr, 0, nullptr, &o};
+    if (launch_any(ndim, precision, mode, t, L, nullptr) != hipSuccess) return Slots{0, 0, 0};
+    return o;
 }
 
 void plan_tiles(const Geo& g, const Tile& t, int& tiles_x, int& tiles_y, int& chunks_z, int& kz) {
     tiles_x = (g.n[0] + t.tx - 1) / t.tx;
     tiles_y = (g.n[1] + t.ty - 1) / t.ty;
-    kz = batch_kz(g, t);
-    kz = kz > g.n[2] ? g.n[2] : kz;
+    kz = t.kz < 1 ? 1 : (t.kz > g.n[2] ? g.n[2] : t.kz);
     chunks_z = (g.n[2] + kz - 1) / kz;
 }
 
 hipError_t launch_stage(int precision, int mode, const Tile& t, StageArgs a, hipStream_t s) {
     plan_tiles(a.geo, t, a.tiles_x, a.tiles_y, a.chunks_z, a.kz);
     if (t.kz == 0 && a.geo.ndim > 1) a.kz = 0;  // resolved per kernel at launch
-    LaunchCtx L{&a, nullptr, nullptr, 0, nullptr};
+    LaunchCtx L{&a, nullptr, nullptr, 0, nullptr, nullptr};
     return launch_any(a.geo.ndim, precision, mode, t, L, s);
 }
 
@@ -2228,14 +2288,14 @@ hipError_t plan_stage_launch(int precision, int mode, const Tile& t, StageArgs a
     if (!out) return hipErrorInvalidValue;
     plan_tiles(a.geo, t, a.tiles_x, a.tiles_y, a.chunks_z, a.kz);
     if (t.kz == 0 && a.geo.ndim > 1) a.kz = 0;
-    LaunchCtx L{&a, nullptr, nullptr, 0, out};
+    LaunchCtx L{&a, nullptr, nullptr, 0, out, nullptr};
     return launch_any(a.geo.ndim, precision, mode, t, L, nullptr);
 }
 
 hipError_t launch_stage_batch(int ndim, int precision, int mode, const Tile& tile, const MeshDesc* d,
                               const int2* blk, int nblk, hipStream_t s) {
     if (mode == MODE_RHS) return hipErrorInvalidValue;
-    LaunchCtx L{nullptr, d, blk, nblk, nullptr};
+    LaunchCtx L{nullptr, d, blk, nblk, nullptr, nullptr};
     return launch_any(ndim, precision, mode, tile, L, s);
 }
 

@@ -1613,6 +1613,25 @@ bool plan_batch(int n, const hydro_t* members, BatchPlan& P, int rule = 0) {
         return std::make_tuple(h->cfg.ndim, h->cfg.precision, h->cfg.integrator, tiles[i].tx, tiles[i].ty);
     };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key(a) < key(b); });
+    // automatic chunk lengths: one per group, for the columns of all its members
+    std::vector<MarchCols> cols;
+    for (int i0 = 0, i1 = 0; i0 < n; i0 = i1) {
+        cols.clear();
+        for (i1 = i0; i1 < n && key(order[i1]) == key(order[i0]); ++i1) {
+            const MeshDesc& d = desc[order[i1]];
+            if (tiles[order[i1]].kz == 0) cols.push_back({(long long)d.tiles_x * d.tiles_y, d.geo.n[2], false});
+        }
+        if (cols.empty()) continue;
+        const hydro_t h = members[order[i0]];
+        const int kz = auto_kz(h->cfg.ndim, stage_residency(h->cfg.ndim, h->cfg.precision, stage2_mode(&h->cfg),
+                                                            tiles[order[i0]]), cols.data(), (int)cols.size());
+        for (int k = i0; k < i1; ++k) {
+            MeshDesc& d = desc[order[k]];
+            if (tiles[order[k]].kz != 0) continue;
+            d.kz = balanced_kz(d.geo.n[2], kz);
+            d.chunks_z = (d.geo.n[2] + d.kz - 1) / d.kz;
+        }
+    }
     for (int idx = 0; idx < n; ++idx) {
         const int i = order[idx];
         const hydro_t h = members[i];
