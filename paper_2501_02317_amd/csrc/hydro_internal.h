@@ -10,11 +10,21 @@ namespace hydro {
 
 constexpr int kMaxComp = 5;
 
-// Device control block, one per mesh, in the caller's workspace.
+// Device control block, one per mesh, in the caller's workspace: this
+// structure, at kCtrlNext the step control that a step's first stage leaves
+// for its second (StepCtl), and at kCtrlSlots two sets of kRateSlots
+// accumulators of the CFL rate, each in a cache line of its own (an atomic
+// maximum to one address takes 11.5 ns of every work-group on the device: 1024
+// of them were 12 us of a stage).
+//
+// The rate of the current state is still in set `par` of the slots while
+// pend is not kPendNone; then dt_raw (and after a step t, steps and done) are
+// those of before it.  Outside such a state both sets are zero.
 struct Ctrl {
     double dt_raw;                  // cfl / (max CFL rate) of the current state
     double t;                       // simulation time
-    unsigned long long rate_bits;   // max accumulator: non-negative doubles order as integers
+    unsigned int pend;              // what the rate in the slots is still to be used for (kPend...)
+    unsigned int par;               // the set of slots in use
     unsigned int flags;             // sticky error flags
     unsigned int dt_valid;          // dt_raw belongs to the current state
     unsigned long long steps;       // completed steps
@@ -22,20 +32,43 @@ struct Ctrl {
     double t_end;                   // run limit in time (0: none)
     unsigned long long max_steps;   // run limit in steps (0: none)
     unsigned int done;              // a limit is reached: device-dt stages skip this mesh
-    unsigned int pad0;
+    unsigned int pend_flags;        // error flags of the state that a pending rate belongs to
     double pad[6];
 };
 static_assert(sizeof(Ctrl) == 192, "control block layout");
 
+constexpr unsigned int kPendNone = 0;  // nothing pending
+constexpr unsigned int kPendStep = 1;  // a device-dt step: advance t and steps, then the next dt
+constexpr unsigned int kPendRate = 2;  // the rate of a state: its dt only
+
+struct StepCtl {
+    double dt, dt_raw, t;
+    unsigned long long steps;
+    unsigned int done, par;
+};
+
+constexpr int kRateSlots = 32;
+constexpr size_t kRateStride = 16;  // in doubles: one cache line
+constexpr size_t kCtrlNext = 256, kCtrlSlots = 512;
+constexpr size_t kCtrlBytes = kCtrlSlots + 2 * kRateSlots * kRateStride * sizeof(double);
+
+__host__ __device__ inline StepCtl* ctrl_next(Ctrl* c) {
+    return reinterpret_cast<StepCtl*>(reinterpret_cast<char*>(c) + kCtrlNext);
+}
+// Slot i of set par: the bits of a non-negative double, which order as integers.
+__host__ __device__ inline unsigned long long* rate_slot(Ctrl* c, unsigned int par, unsigned int i) {
+    return reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(c) + kCtrlSlots) +
+           (par * kRateSlots + i) * kRateStride;
+}
+
 enum : unsigned int { FLAG_NONPHYSICAL = 1u };
 
 enum CtrlOp : int {
-    CTRL_INIT = 0,           // t = a0, steps = 0, flags = 0, dt invalid, no limits
-    CTRL_RESET_MIN = 1,      // rate accumulator = 0
-    CTRL_FINALIZE_DT = 2,    // dt_raw = cfl / rate, dt valid
-    CTRL_FINALIZE_STEP = 3,  // t += clamped dt, steps += 1, dt_raw = cfl / rate, reset, done
-    CTRL_ADVANCE_T = 4,      // t += a0 (host dt), dt invalid
-    CTRL_SET_LIMITS = 5,     // t_end = a0, max_steps = a1 (relative to the steps done), done
+    CTRL_INIT = 0,           // t = a0, steps = 0, flags = 0, dt invalid, nothing pending, no limits
+    CTRL_FINALIZE = 1,       // use the pending rate, if any: dt_raw = cfl / rate, dt valid (after a step: t, steps, done)
+    CTRL_FINALIZE_STEP = 2,  // the same for a step whose rate is in the slots unannounced
+    CTRL_ADVANCE_T = 3,      // t += a0 (host dt), dt invalid
+    CTRL_SET_LIMITS = 4,     // t_end = a0, max_steps = a1 (relative to the steps done), done
 };
 
 // Geometry in kernel axes.  Kernel axis 0 is x.  For 3-D, kernel axes
@@ -76,6 +109,10 @@ struct StageArgs {
     double dt_host;      // dt when use_device_dt == 0
     int use_device_dt;   // dt from ctrl (clamped to its t_end); skip the mesh when done
     int want_dt;         // stage 2: accumulate the next CFL candidate
+    // the step keeps its own books: the first stage takes the pending rate
+    // and leaves the step's control, the second leaves the next rate pending
+    // (0: the caller's control launches do)
+    int chain;
     int tiles_x, tiles_y, chunks_z, kz;  // per block
     int blk0, nblk;      // the launch covers blocks blk0 .. blk0 + nblk - 1
     int conc;            // blocks whose stage work runs at once (automatic chunk length)
@@ -199,9 +236,8 @@ hipError_t launch_stage_batch(int ndim, int precision, int mode, const Tile& til
                               const int2* blk, int nblk, hipStream_t s);
 // (done, flags, steps) of members [0, n) of a descriptor table into out[3 i ..].
 hipError_t launch_status_gather(const MeshDesc* d, int n, unsigned long long* out, hipStream_t s);
-// CTRL_FINALIZE_STEP for members [0, n) of a descriptor table.
+// CTRL_FINALIZE for members [0, n) of a descriptor table.
 hipError_t launch_ctrl_batch(const MeshDesc* d, int n, hipStream_t s);
-hipError_t launch_dt(const Geo& g, const double* U, Ctrl* ctrl, hipStream_t s);
 hipError_t launch_ctrl(Ctrl* c, int op, double a0, double a1, double cfl, hipStream_t s);
 hipError_t launch_totals(const Geo& g, const double* U, double* partials, int nparts, Ctrl* ctrl,
                          hipStream_t s);
@@ -209,8 +245,12 @@ hipError_t launch_totals(const Geo& g, const double* U, double* partials, int np
 // device (partials: 2 ncomp nparts doubles of scratch).
 hipError_t launch_totals_out(const Geo& g, const double* U, double* partials, int nparts, double* out, double dV,
                              hipStream_t s);
-// W and U in the block layout; in place when W == U.
-hipError_t launch_prim_to_cons(const Geo& g, const double* W, double* U, hipStream_t s);
+// Conserved variables U (block layout) of the primitive state W, in the mesh
+// layout (mesh_layout != 0) or the block layout (in place when W == U), with
+// the CFL rate of U left pending.  Blocks of level L take g0's cell widths
+// times 2^-L.
+hipError_t launch_prim_to_cons(const Geo& g0, const LevelStarts& starts, int nblk, const double* W, double* U,
+                               int mesh_layout, Ctrl* ctrl, hipStream_t s);
 // Copy a field between the mesh layout [comp][k][j][i] (mesh) and the block
 // layout (blk): to_blocks != 0 reads mesh and writes blk, else the reverse.
 hipError_t launch_relayout(const Geo& g, double* mesh, double* blk, int to_blocks, hipStream_t s);
@@ -237,11 +277,11 @@ hipError_t launch_smr_reflux(int precision, int first, const Geo& g0, const Geo&
                              hipStream_t s);
 hipError_t launch_smr_apply(const Geo& g0, double* out, const double* dbuf, long long gcs, const GhostTask* tasks,
                             int idx0, int n, int use_device_dt, Ctrl* ctrl, hipStream_t s);
-// dt reduction over the nblk blocks of U, a block of level L (from the level
-// starts) with g0's cell widths times 2^-L; with skip_done, nothing once the
-// run limit is reached.
+// CFL rate of the nblk blocks of U into the slots, a block of level L (from
+// the level starts) with g0's cell widths times 2^-L; with in_step, nothing
+// once the run limit is reached, else the rate is left pending.
 hipError_t launch_dt_levels(const Geo& g0, const LevelStarts& starts, int nblk, const double* U, Ctrl* ctrl,
-                            int skip_done, hipStream_t s);
+                            int in_step, hipStream_t s);
 
 // Default tile for a mesh (kernel axes) and precision.
 Tile default_tile(const Geo& g, int precision, int mode);

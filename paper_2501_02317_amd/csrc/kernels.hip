@@ -584,7 +584,7 @@ __device__ __forceinline__ void update_done(Ctrl* c) {
 }
 
 // Advance time by the step just taken and take the next dt from the rate.
-__device__ __forceinline__ void finalize_step(Ctrl* c, double cfl) {
+__device__ __forceinline__ void finalize_step(Ctrl* c, double cfl, double rate) {
     if (c->done) return;
     const double dt = device_dt(c);
     const bool last = c->t_end > 0.0 && c->dt_raw >= c->t_end - c->t;
@@ -592,9 +592,8 @@ __device__ __forceinline__ void finalize_step(Ctrl* c, double cfl) {
         c->t = last ? c->t_end : c->t + dt;
         c->steps += 1;
     }
-    c->dt_raw = cfl / __longlong_as_double((long long)c->rate_bits);
+    c->dt_raw = cfl / rate;
     c->dt_valid = 1;
-    c->rate_bits = 0ull;
     update_done(c);
 }
 
@@ -614,6 +613,55 @@ __device__ __forceinline__ double wave_max(double v) {
         v = o > v ? o : v;
     }
     return v;
+}
+
+// Largest value of the set's slots (each lane has loaded one of them).
+__device__ __forceinline__ double slots_max(double v) {
+#pragma unroll
+    for (int off = kRateSlots / 2; off >= 1; off >>= 1) {
+        const double o = __shfl_xor(v, off, 64);
+        v = o > v ? o : v;
+    }
+    return v;
+}
+
+__device__ __forceinline__ double load_slot(Ctrl* c, unsigned int par) {
+    return __longlong_as_double((long long)*rate_slot(c, par, threadIdx.x % kRateSlots));
+}
+
+__device__ __forceinline__ void add_rate(Ctrl* c, unsigned int par, double rate) {
+    atomicMax(rate_slot(c, par, blockIdx.x % kRateSlots), (unsigned long long)__double_as_longlong(rate));
+}
+
+// The control of the step that begins, from the pending rate (of set par,
+// loaded by the caller): what CTRL_FINALIZE would make of the block, without
+// writing it.  The step's own rate goes to the other set when one is pending.
+__device__ __forceinline__ StepCtl begin_step(const Ctrl* c, double cfl, double rate) {
+    Ctrl k;
+    k.dt_raw = c->dt_raw;
+    k.t = c->t;
+    k.steps = c->steps;
+    k.t_end = c->t_end;
+    k.max_steps = c->max_steps;
+    k.done = c->done;
+    const unsigned int pend = c->pend;
+    if (pend == kPendStep) finalize_step(&k, cfl, rate);
+    if (pend == kPendRate) k.dt_raw = cfl / rate;
+    StepCtl n;
+    n.dt_raw = k.dt_raw;
+    n.t = k.t;
+    n.steps = k.steps;
+    n.done = k.done;
+    n.par = pend != kPendNone ? c->par ^ 1u : c->par;
+    n.dt = device_dt(&k);
+    return n;
+}
+
+// A value that every lane holds, in scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | lo);
 }
 
 // ------------------------------------------------------------- stage kernel
@@ -783,7 +831,7 @@ struct StageOccupancy {
 };
 
 template <int NDIM, typename R, int MODE, int TX, int TY>
-__device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk) {
+__device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, bool leader) {
     constexpr int NC = NDIM + 2;
     constexpr bool HY = (NDIM == 3);
     constexpr bool HZ = (NDIM >= 2);
@@ -876,11 +924,12 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk) {
     // (outflow, reflecting); uniform over the grid
     const bool halo_vm = g.bc[0][0] >= BC_OUTFLOW || g.bc[0][1] >= BC_OUTFLOW ||
                          (HY && (g.bc[1][0] >= BC_OUTFLOW || g.bc[1][1] >= BC_OUTFLOW));
-    const double dt_step = a.use_device_dt ? device_dt(a.ctrl) : a.dt_host;
-    const double dt = PRED ? 0.5 * dt_step : dt_step;  // the predictor advances half a step
-    const double lam0 = dt / g.dx[0];
-    const double lam1 = dt / g.dx[1];
-    const double lam2 = dt / g.dx[2];
+    // both sets of rate slots, loaded ahead of the state (a chained first stage)
+    double slot0 = 0.0, slot1 = 0.0;
+    if (!EPILOGUE && a.chain) {
+        slot0 = load_slot(a.ctrl, 0);
+        slot1 = load_slot(a.ctrl, 1);
+    }
     const Gas<R> gr = make_gas<R>(g.gamma);
 
     constexpr bool RING = StageOccupancy<NDIM, R, MODE>::kRing && HZ;
@@ -898,7 +947,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk) {
     __shared__ FT sFx[NB][NC][TY][TX + 1];
     __shared__ FT sFy[NB][HY ? NC : 1][HY ? TY + 1 : 1][TX];
 
-    bool bad = false;
+    bool bad = false, bad_new = false;  // of the stage's input, and of the new state
     double rate = 0.0;
     // z pipeline entering iteration k: W_k, W_{k+1}, d = W_{k+1} - W_k, the
     // left state of face k+1/2 (W_k + delta_k / 2); fza, fzb: the fluxes of
@@ -998,6 +1047,50 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk) {
         }
         load_interior(z0 + 2, uiA, vmA);
     }
+    // the step's length, and whether the mesh still runs (uniform over the
+    // launch; the leader is one thread of the mesh's launch)
+    double dt_step = a.dt_host;
+    unsigned int par = 0;
+    if (a.chain && !EPILOGUE) {
+        const StepCtl n = begin_step(a.ctrl, g.cfl, slots_max(a.ctrl->par ? slot1 : slot0));
+        if (leader) {
+            if (tid == 0) {
+                *ctrl_next(a.ctrl) = n;
+                if (a.use_device_dt && a.ctrl->pend == kPendRate && a.ctrl->pend_flags)
+                    atomicOr(&a.ctrl->flags, a.ctrl->pend_flags);
+                a.ctrl->pend_flags = 0;
+            }
+            if (tid < kRateSlots) *rate_slot(a.ctrl, n.par, tid) = 0ull;
+        }
+        if (a.use_device_dt) {
+            if (n.done) return;
+            dt_step = n.dt;
+        }
+    } else if (a.chain) {
+        const StepCtl n = *ctrl_next(a.ctrl);
+        par = __builtin_amdgcn_readfirstlane(n.par);
+        if (leader && tid == 0) {
+            a.ctrl->par = n.par;
+            a.ctrl->pend = a.use_device_dt ? (n.done ? kPendNone : kPendStep) : kPendRate;
+            a.ctrl->dt_raw = n.dt_raw;
+            a.ctrl->t = a.use_device_dt ? n.t : n.t + a.dt_host;
+            a.ctrl->steps = a.use_device_dt ? n.steps : n.steps + 1;
+            a.ctrl->done = n.done;
+            a.ctrl->dt_valid = a.use_device_dt ? 1 : 0;
+        }
+        if (a.use_device_dt) {
+            if (n.done) return;
+            dt_step = n.dt;
+        }
+    } else {
+        if (a.use_device_dt) dt_step = device_dt(a.ctrl);
+        if (EPILOGUE) par = a.ctrl->par;
+    }
+    dt_step = uniform(dt_step);
+    const double dt = PRED ? 0.5 * dt_step : dt_step;  // the predictor advances half a step
+    const double lam0 = uniform(dt / g.dx[0]);
+    const double lam1 = uniform(dt / g.dx[1]);
+    const double lam2 = uniform(dt / g.dx[2]);
     if (HALO_PF && hact && z0 < z1) load_halo(z0, uhalo);
     // (BASE_PF) U^n of the first updated plane, loaded ahead
     constexpr bool BASE_PF = StageOccupancy<NDIM, R, MODE>::kBasePrefetch && NEED_BASE;
@@ -1224,7 +1317,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk) {
             }
             if (EPILOGUE && a.want_dt) {
                 double w[NC];
-                bad |= !cons_to_prim<NDIM>(gm1, unew, w);
+                bad_new |= !cons_to_prim<NDIM>(gm1, unew, w);
                 const double cr = cfl_rate<NDIM>(g, w);
                 rate = cr > rate ? cr : rate;
             }
@@ -1248,8 +1341,10 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk) {
         for (int k = z0; k < kend; ++k) plane(k, uiA, vmA, uiA, vmA, ubA, ubA);
     }
 
-    if (bad) atomicOr(&a.ctrl->flags, FLAG_NONPHYSICAL);
+    if (bad || (bad_new && a.use_device_dt)) atomicOr(&a.ctrl->flags, FLAG_NONPHYSICAL);
     if (EPILOGUE && a.want_dt) {
+        // a host-dt step's new state is not looked at until its dt is asked for
+        if (bad_new && !a.use_device_dt) atomicOr(&a.ctrl->pend_flags, FLAG_NONPHYSICAL);
         __shared__ double red[NT / 64 > 0 ? NT / 64 : 1];
         rate = wave_max(rate);
         if ((tid & 63) == 0) red[tid >> 6] = rate;
@@ -1257,7 +1352,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk) {
         if (tid == 0) {
             double m = red[0];
             for (int i = 1; i < NT / 64; ++i) m = red[i] > m ? red[i] : m;
-            atomicMax(&a.ctrl->rate_bits, (unsigned long long)__double_as_longlong(m));
+            add_rate(a.ctrl, par, m);
         }
     }
 }
@@ -1266,7 +1361,7 @@ template <int NDIM, typename R, int MODE, int TX, int TY>
 __global__ __launch_bounds__(TX * TY)
 __attribute__((amdgpu_waves_per_eu(StageOccupancy<NDIM, R, MODE>::kWaves, StageOccupancy<NDIM, R, MODE>::kWavesMax)))
 void stage_kernel(StageArgs a) {
-    if (a.use_device_dt && a.ctrl->done) return;  // uniform over the grid
+    if (!a.chain && a.use_device_dt && a.ctrl->done) return;  // uniform over the grid
     // work-group -> (block, work-group within the block), block after block:
     // each XCD's contiguous range of work-groups covers whole blocks (measured
     // faster than taking them in the order of the whole mesh's tile grid)
@@ -1278,7 +1373,7 @@ void stage_kernel(StageArgs a) {
         blk += q;
         wg -= q * per;
     }
-    stage_body<NDIM, R, MODE, TX, TY>(a, wg, blk);
+    stage_body<NDIM, R, MODE, TX, TY>(a, wg, blk, blockIdx.x == 0);
 }
 
 // Batched stage: work-group -> (member, work-group of the member) from a
@@ -1290,12 +1385,12 @@ void stage_kernel_batch(
     const MeshDesc* __restrict__ descs, const int2* __restrict__ blk) {
     const int2 e = blk[xcd_remap(blockIdx.x, gridDim.x)];
     const MeshDesc& d = descs[e.x];
-    if (d.ctrl->done) return;  // uniform over the work-group
     StageArgs a{};  // every field set: a batch member is one unrefined block
     a.ctrl = d.ctrl;
     a.geo = d.geo;
     a.dt_host = 0.0;
     a.use_device_dt = 1;
+    a.chain = 1;
     a.tiles_x = d.tiles_x;
     a.tiles_y = d.tiles_y;
     a.chunks_z = d.chunks_z;
@@ -1317,26 +1412,60 @@ void stage_kernel_batch(
         a.out = d.U;
         a.want_dt = 1;
     }
-    stage_body<NDIM, R, MODE, TX, TY>(a, e.y, 0);
+    stage_body<NDIM, R, MODE, TX, TY>(a, e.y, 0, e.y == 0);
 }
 
 // ------------------------------------------------------------- small kernels
+
+// m_d = rho v_d, E = p/(gamma - 1) + (1/2) sum_d m_d v_d
+template <int NDIM>
+__device__ __forceinline__ void prim_to_cons_cell(double gamma, const double (&w)[NDIM + 2], double (&u)[NDIM + 2]) {
+    double ke2 = 0.0;
+    u[0] = w[0];
+#pragma unroll
+    for (int d = 0; d < NDIM; ++d) {
+        const double mom = w[0] * w[1 + d];
+        u[1 + d] = mom;
+        ke2 = ke2 + mom * w[1 + d];
+    }
+    u[NDIM + 1] = w[NDIM + 1] / (gamma - 1.0) + 0.5 * ke2;
+}
+
+// Geometry of block blk: a refined mesh's blocks of level L (from the level
+// starts) have inverse cell widths of level 0's times 2^L (exact: 1 / (dx
+// 2^-L) rounds to (1 / dx) 2^L).
+__device__ __forceinline__ Geo block_geo(const Geo& g0, const LevelStarts& starts, int blk) {
+    Geo g = g0;
+    int lev = 0;
+#pragma unroll
+    for (int L = 1; L < kMaxLevels; ++L) lev += blk >= starts.s[L - 1] ? 1 : 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) g.inv_dx[k] = __builtin_ldexp(g0.inv_dx[k], lev);
+    return g;
+}
+
+// Largest rate of a work-group of four waves into the slots.
+__device__ __forceinline__ void block_rate(Ctrl* ctrl, double best) {
+    __shared__ double red[4];
+    best = wave_max(best);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double m = red[0];
+        for (int i = 1; i < 4; ++i) m = red[i] > m ? red[i] : m;
+        add_rate(ctrl, ctrl->par, m);
+    }
+}
 
 // blockIdx.y: the block of the mesh (block layout); a refined mesh's blocks
 // of level L (from the level starts) take level 0's cell widths times 2^-L
 template <int NDIM>
 __global__ __launch_bounds__(256) void dt_kernel(Geo g0, LevelStarts starts, const double* __restrict__ U,
-                                                 Ctrl* ctrl, int skip_done) {
+                                                 Ctrl* ctrl, int in_step) {
     constexpr int NC = NDIM + 2;
-    if (skip_done && ctrl->done) return;  // uniform over the grid
-    Geo g = g0;
-    // the block's level: its inverse cell widths are level 0's times 2^L
-    // (exact: 1 / (dx 2^-L) rounds to (1 / dx) 2^L)
-    int lev = 0;
-#pragma unroll
-    for (int L = 1; L < kMaxLevels; ++L) lev += (int)blockIdx.y >= starts.s[L - 1] ? 1 : 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) g.inv_dx[k] = __builtin_ldexp(g0.inv_dx[k], lev);
+    if (in_step && ctrl->done) return;  // uniform over the grid
+    if (!in_step && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctrl->pend = kPendRate;
+    const Geo g = block_geo(g0, starts, blockIdx.y);
     U += (long long)blockIdx.y * NC * g.ncells;
     double best = 0.0;
     bool bad = false;
@@ -1350,19 +1479,34 @@ __global__ __launch_bounds__(256) void dt_kernel(Geo g0, LevelStarts starts, con
         best = cr > best ? cr : best;
     }
     if (bad) atomicOr(&ctrl->flags, FLAG_NONPHYSICAL);
-    __shared__ double red[4];
-    best = wave_max(best);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double m = red[0];
-        for (int i = 1; i < 4; ++i) m = red[i] > m ? red[i] : m;
-        atomicMax(&ctrl->rate_bits, (unsigned long long)__double_as_longlong(m));
-    }
+    block_rate(ctrl, best);
 }
 
-__global__ void ctrl_kernel(Ctrl* c, int op, double a0, double a1, double cfl) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// Use the rate in the slots (pend: what for) and clear both sets; one wave.
+__device__ __forceinline__ void finalize_ctrl(Ctrl* c, unsigned int pend, double cfl) {
+    const double rate = slots_max(load_slot(c, c->par));
+    *rate_slot(c, threadIdx.x / kRateSlots, threadIdx.x % kRateSlots) = 0ull;
+    if (threadIdx.x != 0) return;
+    if (pend == kPendStep) finalize_step(c, cfl, rate);
+    if (pend == kPendRate) {
+        c->dt_raw = cfl / rate;
+        c->dt_valid = 1;
+        c->flags |= c->pend_flags;
+    }
+    c->pend = kPendNone;
+    c->pend_flags = 0;
+}
+
+__global__ __launch_bounds__(64) void ctrl_kernel(Ctrl* c, int op, double a0, double a1, double cfl) {
+    static_assert(2 * kRateSlots == 64, "one wave clears both sets of slots");
+    if (op == CTRL_FINALIZE || op == CTRL_FINALIZE_STEP) {
+        finalize_ctrl(c, op == CTRL_FINALIZE_STEP ? kPendStep : c->pend, cfl);
+        return;
+    }
+    // both leave nothing pending (a replayed host-dt step may meet a state
+    // whose rate is)
+    if (op == CTRL_INIT || op == CTRL_ADVANCE_T) *rate_slot(c, threadIdx.x / kRateSlots, threadIdx.x % kRateSlots) = 0ull;
+    if (threadIdx.x != 0) return;
     switch (op) {
         case CTRL_INIT:
             c->t = a0;
@@ -1370,26 +1514,19 @@ __global__ void ctrl_kernel(Ctrl* c, int op, double a0, double a1, double cfl) {
             c->flags = 0;
             c->dt_valid = 0;
             c->dt_raw = 0.0;
-            c->rate_bits = 0ull;
+            c->pend = kPendNone;
+            c->par = 0;
+            c->pend_flags = 0;
             c->t_end = 0.0;
             c->max_steps = 0ull;
             c->done = 0;
-            break;
-        case CTRL_RESET_MIN:
-            c->rate_bits = 0ull;
-            break;
-        case CTRL_FINALIZE_DT:
-            c->dt_raw = cfl / __longlong_as_double((long long)c->rate_bits);
-            c->dt_valid = 1;
-            c->rate_bits = 0ull;
-            break;
-        case CTRL_FINALIZE_STEP:
-            finalize_step(c, cfl);
             break;
         case CTRL_ADVANCE_T:
             c->t = c->t + a0;
             c->steps += 1;
             c->dt_valid = 0;
+            c->pend = kPendNone;
+            c->pend_flags = 0;
             break;
         case CTRL_SET_LIMITS:
             c->t_end = a0;
@@ -1412,9 +1549,10 @@ __global__ void status_gather_kernel(const MeshDesc* __restrict__ d, int n, unsi
     }
 }
 
-__global__ void ctrl_batch_kernel(const MeshDesc* __restrict__ d, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) finalize_step(d[i].ctrl, d[i].geo.cfl);
+// One wave per member.
+__global__ __launch_bounds__(64) void ctrl_batch_kernel(const MeshDesc* __restrict__ d) {
+    Ctrl* c = d[blockIdx.x].ctrl;
+    finalize_ctrl(c, c->pend, d[blockIdx.x].geo.cfl);
 }
 
 // Neumaier-compensated accumulator combined pairwise in a fixed tree.
@@ -1522,28 +1660,56 @@ __global__ __launch_bounds__(256) void totals_pass2(int nparts, const double* __
         }
 }
 
-// m_d = rho v_d, E = p/(gamma - 1) + (1/2) sum_d m_d v_d
+// m_d = rho v_d, E = p/(gamma - 1) + (1/2) sum_d m_d v_d, and the CFL rate of
+// the conserved state, left pending for the first time step (one pass over
+// the state instead of three: 256^3 372 -> 246 us; 192^3
+// in eight blocks, where it does the relayout too, 237 -> 98 us).
 // W and U may be the same array (each cell is read before it is written);
-// blockIdx.y: the block of the mesh (block layout).
-template <int NDIM>
-__global__ __launch_bounds__(256) void prim_to_cons_kernel(Geo g, const double* W, double* U) {
+// blockIdx.y: the block of the mesh (block layout); MESH: W is in the mesh
+// layout of a uniform block grid.
+template <int NDIM, bool MESH>
+__global__ __launch_bounds__(256) void prim_to_cons_kernel(Geo g0, LevelStarts starts, const double* W, double* U,
+                                                           Ctrl* ctrl) {
     constexpr int NC = NDIM + 2;
-    W += (long long)blockIdx.y * NC * g.ncells;
-    U += (long long)blockIdx.y * NC * g.ncells;
-    for (long long cell = (long long)blockIdx.x * blockDim.x + threadIdx.x; cell < g.ncells;
-         cell += (long long)gridDim.x * blockDim.x) {
-        const double rho = W[cell];
-        double ke2 = 0.0;
-        U[cell] = rho;
-#pragma unroll
-        for (int d = 0; d < NDIM; ++d) {
-            const double v = W[(1 + d) * g.ncells + cell];
-            const double mom = rho * v;
-            U[(1 + d) * g.ncells + cell] = mom;
-            ke2 = ke2 + mom * v;
-        }
-        U[(NC - 1) * g.ncells + cell] = W[(NC - 1) * g.ncells + cell] / (g.gamma - 1.0) + 0.5 * ke2;
+    const Geo g = block_geo(g0, starts, blockIdx.y);
+    const int blk = blockIdx.y;
+    const long long N = g.ncells;
+    // component stride and the block's first cell in W
+    long long ws = N, w0 = (long long)blk * NC * N;
+    long long row = g.n[0], plane = (long long)g.n[0] * g.n[1];
+    if (MESH) {
+        row = (long long)g.n[0] * g.blocks[0];
+        plane = row * g.n[1] * g.blocks[1];
+        ws = plane * g.n[2] * g.blocks[2];
+        w0 = (long long)(blk % g.blocks[0]) * g.n[0] +
+             (long long)((blk / g.blocks[0]) % g.blocks[1]) * g.n[1] * row +
+             (long long)(blk / (g.blocks[0] * g.blocks[1])) * g.n[2] * plane;
     }
+    W += w0;
+    U += (long long)blk * NC * N;
+    double best = 0.0;
+    bool bad = false;
+    for (long long cell = (long long)blockIdx.x * blockDim.x + threadIdx.x; cell < N;
+         cell += (long long)gridDim.x * blockDim.x) {
+        long long q = cell;
+        if (MESH) {
+            const long long r = cell / g.n[0];
+            q = cell % g.n[0] + (r % g.n[1]) * row + (r / g.n[1]) * plane;
+        }
+        double w[NC], u[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) w[c] = W[c * ws + q];
+        prim_to_cons_cell<NDIM>(g.gamma, w, u);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) U[c * N + cell] = u[c];
+        bad |= !cons_to_prim<NDIM>(g.gamma - 1.0, u, w);
+        const double cr = cfl_rate<NDIM>(g, w);
+        best = cr > best ? cr : best;
+    }
+    // looked at once the dt is asked for
+    if (bad) atomicOr(&ctrl->pend_flags, FLAG_NONPHYSICAL);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctrl->pend = kPendRate;
+    block_rate(ctrl, best);
 }
 
 // Padded primitive export: physical padded layout [c][K][J][I] with two ghost
@@ -1648,20 +1814,6 @@ __device__ __forceinline__ void smr_prim(const Geo& g, const Links& L, const dou
     int vax, vm;
     smr_cell<NDIM + 2>(g, L, U, gbuf, gcs, blk, x, y, z, u, vax, vm);
     to_prim<NDIM, double>(g.gamma - 1.0, u, vax, vm, w, bad);
-}
-
-// m_d = rho v_d, E = p/(gamma - 1) + (1/2) sum_d m_d v_d
-template <int NDIM>
-__device__ __forceinline__ void prim_to_cons_cell(double gamma, const double (&w)[NDIM + 2], double (&u)[NDIM + 2]) {
-    double ke2 = 0.0;
-    u[0] = w[0];
-#pragma unroll
-    for (int d = 0; d < NDIM; ++d) {
-        const double mom = w[0] * w[1 + d];
-        u[1 + d] = mom;
-        ke2 = ke2 + mom * w[1 + d];
-    }
-    u[NDIM + 1] = w[NDIM + 1] / (gamma - 1.0) + 0.5 * ke2;
 }
 
 // Kernel axis of the k-th active axis (physical order: x, y, z).
@@ -2307,27 +2459,21 @@ hipError_t launch_status_gather(const MeshDesc* d, int n, unsigned long long* ou
 
 hipError_t launch_ctrl_batch(const MeshDesc* d, int n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(ctrl_batch_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d, n);
+    hipLaunchKernelGGL(ctrl_batch_kernel, dim3(n), dim3(64), 0, s, d);
     return hipGetLastError();
 }
 
 hipError_t launch_dt_levels(const Geo& g0, const LevelStarts& starts, int nblk, const double* U, Ctrl* ctrl,
-                            int skip_done, hipStream_t s) {
+                            int in_step, hipStream_t s) {
     if (nblk < 1) return hipSuccess;
     const dim3 grid(grid_for(g0.ncells, 256, (2048 + nblk - 1) / nblk), nblk);
     switch (g0.ndim) {
-        case 1: hipLaunchKernelGGL(dt_kernel<1>, grid, dim3(256), 0, s, g0, starts, U, ctrl, skip_done); break;
-        case 2: hipLaunchKernelGGL(dt_kernel<2>, grid, dim3(256), 0, s, g0, starts, U, ctrl, skip_done); break;
-        case 3: hipLaunchKernelGGL(dt_kernel<3>, grid, dim3(256), 0, s, g0, starts, U, ctrl, skip_done); break;
+        case 1: hipLaunchKernelGGL(dt_kernel<1>, grid, dim3(256), 0, s, g0, starts, U, ctrl, in_step); break;
+        case 2: hipLaunchKernelGGL(dt_kernel<2>, grid, dim3(256), 0, s, g0, starts, U, ctrl, in_step); break;
+        case 3: hipLaunchKernelGGL(dt_kernel<3>, grid, dim3(256), 0, s, g0, starts, U, ctrl, in_step); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
-}
-
-hipError_t launch_dt(const Geo& g, const double* U, Ctrl* ctrl, hipStream_t s) {
-    LevelStarts none;
-    for (int L = 0; L < kMaxLevels - 1; ++L) none.s[L] = geo_nblk(g);
-    return launch_dt_levels(g, none, geo_nblk(g), U, ctrl, 0, s);
 }
 
 hipError_t launch_ctrl(Ctrl* c, int op, double a0, double a1, double cfl, hipStream_t s) {
@@ -2376,15 +2522,20 @@ hipError_t launch_totals_out(const Geo& g, const double* U, double* parts, int n
     return totals_launch(g, U, parts, nparts, nullptr, out, dV, s);
 }
 
-hipError_t launch_prim_to_cons(const Geo& g, const double* W, double* U, hipStream_t s) {
-    const int nblk = geo_nblk(g);
-    const dim3 grid(grid_for(g.ncells, 256, (4096 + nblk - 1) / nblk), nblk);
-    switch (g.ndim) {
-        case 1: hipLaunchKernelGGL(prim_to_cons_kernel<1>, grid, dim3(256), 0, s, g, W, U); break;
-        case 2: hipLaunchKernelGGL(prim_to_cons_kernel<2>, grid, dim3(256), 0, s, g, W, U); break;
-        case 3: hipLaunchKernelGGL(prim_to_cons_kernel<3>, grid, dim3(256), 0, s, g, W, U); break;
+hipError_t launch_prim_to_cons(const Geo& g0, const LevelStarts& starts, int nblk, const double* W, double* U,
+                               int mesh_layout, Ctrl* ctrl, hipStream_t s) {
+    const dim3 grid(grid_for(g0.ncells, 256, (4096 + nblk - 1) / nblk), nblk);
+#define PC(ND, M) hipLaunchKernelGGL((prim_to_cons_kernel<ND, M>), grid, dim3(256), 0, s, g0, starts, W, U, ctrl)
+    switch (2 * g0.ndim + (mesh_layout ? 1 : 0)) {
+        case 2: PC(1, false); break;
+        case 3: PC(1, true); break;
+        case 4: PC(2, false); break;
+        case 5: PC(2, true); break;
+        case 6: PC(3, false); break;
+        case 7: PC(3, true); break;
         default: return hipErrorInvalidValue;
     }
+#undef PC
     return hipGetLastError();
 }
 

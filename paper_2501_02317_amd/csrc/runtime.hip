@@ -59,7 +59,12 @@ struct hydro_ctx {
     Ctrl* ctrl;
     Ctrl* host_ctrl;  // host mirror for reads (pageable: no pinning or unpinning per handle)
     bool broken;
-    bool dt_valid;    // ctrl->dt_raw belongs to the current state (host-side knowledge)
+    // host-side knowledge of the control block: dt_raw belongs to the current
+    // state; the current state's CFL rate is pending in it; it has no run limit
+    bool dt_valid;
+    bool rate_pending;
+    bool no_limits;
+    bool captured;    // the stream was captured during a call (see capturing())
     // optional event timing of the stage launches
     int prof_cap;
     int prof_n[2];
@@ -461,9 +466,13 @@ hipError_t timed_stage(hydro_t h, int mode, const StageArgs& a) {
 // with the same dependencies instead (enqueue_step_streams_graph), and a
 // refined mesh's second stream runs on the handle's stream.  The results do
 // not depend on the form.
+// A handle that was captured once may be changed by replays that the host
+// does not see: from then on rate_pending and no_limits are not relied on.
 bool capturing(hydro_t h) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(h->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+    const bool on = hipStreamIsCapturing(h->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+    h->captured = h->captured || on;
+    return on;
 }
 
 // The first leaf of each level 1 .. kMaxLevels - 1 of a refined mesh.
@@ -548,28 +557,78 @@ hipError_t enqueue_step(hydro_t h, bool device_dt, double dt) {
     a.in = h->U;
     a.base = h->U;
     a.out = h->U1;
+    // the step keeps its own books: no control launch (the rate of the new
+    // state is left pending, after a host dt as well)
+    a.chain = 1;
     hipError_t e = timed_stage(h, stage1_mode(&h->cfg), a);
     if (e != hipSuccess) return e;
     a.in = h->U1;
     a.base = h->U;
     a.out = h->U;
-    a.want_dt = device_dt ? 1 : 0;
-    e = timed_stage(h, stage2_mode(&h->cfg), a);
-    if (e != hipSuccess) return e;
-    if (device_dt) return launch_ctrl(h->ctrl, CTRL_FINALIZE_STEP, 0.0, 0.0, h->cfg.cfl, h->stream);
-    return launch_ctrl(h->ctrl, CTRL_ADVANCE_T, dt, 0.0, h->cfg.cfl, h->stream);
+    a.want_dt = 1;
+    return timed_stage(h, stage2_mode(&h->cfg), a);
 }
 
-hipError_t enqueue_dt(hydro_t h) {
-    hipError_t e = launch_ctrl(h->ctrl, CTRL_RESET_MIN, 0.0, 0.0, h->cfg.cfl, h->stream);
-    if (h->smr) {
-        if (e == hipSuccess)
-            e = launch_dt_levels(h->lgeo[0], level_starts(h), h->nblk, h->U, h->ctrl, 0, h->stream);
-    } else if (e == hipSuccess) {
-        e = launch_dt(h->geo, h->U, h->ctrl, h->stream);
+// Whether enqueue_step keeps the step's books itself: every step but that of
+// a refined mesh and that of a split mesh on streams of its own.
+bool step_chains(hydro_t h) { return !h->smr && !(h->block_streams && h->nblk > 1 && h->nbs > 0); }
+
+hipError_t enqueue_finalize(hydro_t h) {
+    const hipError_t e = launch_ctrl(h->ctrl, CTRL_FINALIZE, 0.0, 0.0, h->cfg.cfl, h->stream);
+    if (e == hipSuccess) {
+        h->dt_valid = true;
+        h->rate_pending = false;
     }
-    if (e == hipSuccess) e = launch_ctrl(h->ctrl, CTRL_FINALIZE_DT, 0.0, 0.0, h->cfg.cfl, h->stream);
-    if (e == hipSuccess) h->dt_valid = true;
+    return e;
+}
+
+// The CFL rate of the current state pending in the control block.
+hipError_t enqueue_rate(hydro_t h) {
+    if (h->rate_pending && !h->captured) return hipSuccess;
+    const hipError_t e = launch_dt_levels(h->smr ? h->lgeo[0] : h->geo, level_starts(h), h->nblk, h->U, h->ctrl, 0,
+                                          h->stream);
+    if (e == hipSuccess) h->rate_pending = true;
+    return e;
+}
+
+// dt_raw of the current state in the control block, nothing pending.
+hipError_t enqueue_dt(hydro_t h) {
+    const hipError_t e = enqueue_rate(h);
+    return e == hipSuccess ? enqueue_finalize(h) : e;
+}
+
+// Before the device-dt steps of a call: a dt for the first one, pending where
+// the steps keep their own books.
+hipError_t enqueue_first_dt(hydro_t h) {
+    if (h->dt_valid) return hipSuccess;
+    return step_chains(h) ? enqueue_rate(h) : enqueue_dt(h);
+}
+
+hipError_t enqueue_limits(hydro_t h, double max_steps, double t_end) {
+    const bool none = !(max_steps > 0.0) && !(t_end > 0.0);
+    if (none && h->no_limits && !h->captured) return hipSuccess;
+    const hipError_t e = launch_ctrl(h->ctrl, CTRL_SET_LIMITS, t_end, max_steps, h->cfg.cfl, h->stream);
+    h->no_limits = none && e == hipSuccess;
+    return e;
+}
+
+// A new state is in U, its CFL rate unknown; CTRL_INIT cleared the limits.
+void state_replaced(hydro_t h) {
+    h->dt_valid = false;
+    h->rate_pending = false;
+    h->no_limits = true;
+}
+
+// U from the primitive state W (mesh layout of a split mesh: mesh_layout),
+// time and limits reset, its rate pending.
+hipError_t enqueue_primitive(hydro_t h, const double* W, int mesh_layout) {
+    (void)capturing(h);
+    hipError_t e = launch_ctrl(h->ctrl, CTRL_INIT, 0.0, 0.0, h->cfg.cfl, h->stream);
+    state_replaced(h);
+    if (e == hipSuccess)
+        e = launch_prim_to_cons(h->smr ? h->lgeo[0] : h->geo, level_starts(h), h->nblk, W, h->U, mesh_layout,
+                                h->ctrl, h->stream);
+    h->rate_pending = e == hipSuccess;
     return e;
 }
 
@@ -805,7 +864,7 @@ size_t smr_bytes(const hydro_config* c, const SmrPlan& P) {
     const size_t nc = (size_t)c->ndim + 2;
     const size_t cells = (size_t)ncells_of(c) / ((size_t)blocks_of(c, 0) * blocks_of(c, 1) * blocks_of(c, 2));
     const size_t field = align_up(nc * cells * (size_t)P.nleaf * sizeof(double));
-    return 2 * field + align_up(sizeof(Ctrl)) + align_up((size_t)kTotalsParts * kMaxComp * 2 * sizeof(double)) +
+    return 2 * field + align_up(kCtrlBytes) + align_up((size_t)kTotalsParts * kMaxComp * 2 * sizeof(double)) +
            align_up(P.side.size() * sizeof(int)) + align_up(P.tasks.size() * sizeof(GhostTask)) +
            align_up(P.tasks.size() * nc * (size_t)P.gcs * sizeof(double)) +
            align_up((size_t)P.nres * nc * (size_t)(P.gcs / 2) * sizeof(double));
@@ -817,7 +876,7 @@ extern "C" {
 
 size_t hydro_workspace_bytes(const hydro_config* cfg) {
     if (!config_ok(cfg)) return 0;
-    return state_bytes(cfg) + second_bytes(cfg) + align_up(sizeof(Ctrl)) +
+    return state_bytes(cfg) + second_bytes(cfg) + align_up(kCtrlBytes) +
            align_up((size_t)kTotalsParts * kMaxComp * 2 * sizeof(double));
 }
 
@@ -845,7 +904,7 @@ int hydro_create(const hydro_config* cfg, void* d_workspace, size_t nbytes, void
     h->U1 = (double*)p;  // van Leer: holds values of the compute type
     p += sb2;
     h->ctrl = (Ctrl*)p;
-    p += align_up(sizeof(Ctrl));
+    p += align_up(kCtrlBytes);
     h->parts = (double*)p;
     h->host_ctrl = new (std::nothrow) Ctrl;
     if (!h->host_ctrl) {
@@ -925,7 +984,7 @@ int hydro_smr_create(const hydro_config* cfg, int nref, const int32_t* refined, 
     h->U1 = (double*)p;
     p += field;
     h->ctrl = (Ctrl*)p;
-    p += align_up(sizeof(Ctrl));
+    p += align_up(kCtrlBytes);
     h->parts = (double*)p;
     p += align_up((size_t)kTotalsParts * kMaxComp * 2 * sizeof(double));
     h->d_side = (int*)p;
@@ -1001,7 +1060,7 @@ int hydro_set_state(hydro_t h, const double* U_host) {
         e = free_tmp(h, tmp, e);
     }
     if (e == hipSuccess) e = launch_ctrl(h->ctrl, CTRL_INIT, 0.0, 0.0, h->cfg.cfl, h->stream);
-    h->dt_valid = false;
+    state_replaced(h);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     return fail(h, e);
 }
@@ -1020,12 +1079,10 @@ int hydro_set_primitive(hydro_t h, const double* W_host) {
         double* tmp = nullptr;
         e = mesh_tmp(h, &tmp);
         if (e == hipSuccess) e = hipMemcpyAsync(tmp, W_host, bytes, hipMemcpyHostToDevice, h->stream);
-        if (e == hipSuccess) e = launch_relayout(h->geo, tmp, h->U, 1, h->stream);
+        if (e == hipSuccess) e = enqueue_primitive(h, tmp, 1);
         e = free_tmp(h, tmp, e);
     }
-    if (e == hipSuccess) e = launch_prim_to_cons(h->geo, h->U, h->U, h->stream);
-    if (e == hipSuccess) e = launch_ctrl(h->ctrl, CTRL_INIT, 0.0, 0.0, h->cfg.cfl, h->stream);
-    h->dt_valid = false;
+    if (e == hipSuccess && !mesh_relayout(h)) e = enqueue_primitive(h, h->U, 0);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     return fail(h, e);
 }
@@ -1034,17 +1091,7 @@ int hydro_set_primitive_device(hydro_t h, const double* d_W) {
     int rc = usable(h);
     if (rc) return rc;
     if (!d_W) return HYDRO_E_INVAL;
-    hipError_t e = hipSuccess;
-    if (!mesh_relayout(h)) {
-        e = launch_prim_to_cons(h->geo, d_W, h->U, h->stream);
-    } else {
-        // only read: the relayout writes the block layout into U
-        e = launch_relayout(h->geo, const_cast<double*>(d_W), h->U, 1, h->stream);
-        if (e == hipSuccess) e = launch_prim_to_cons(h->geo, h->U, h->U, h->stream);
-    }
-    if (e == hipSuccess) e = launch_ctrl(h->ctrl, CTRL_INIT, 0.0, 0.0, h->cfg.cfl, h->stream);
-    h->dt_valid = false;
-    return fail(h, e);
+    return fail(h, enqueue_primitive(h, d_W, mesh_relayout(h) ? 1 : 0));
 }
 
 int hydro_get_state_device(hydro_t h, double* d_U) {
@@ -1099,8 +1146,14 @@ int hydro_step(hydro_t h, double dt) {
     int rc = usable(h);
     if (rc) return rc;
     if (!(dt > 0.0) || !std::isfinite(dt)) return HYDRO_E_INVAL;
+    (void)capturing(h);
+    // a rate still pending is of no use to the step; the forms that do not
+    // keep their own books start with nothing pending
+    hipError_t e = h->rate_pending && !step_chains(h) ? enqueue_finalize(h) : hipSuccess;
+    if (e == hipSuccess) e = enqueue_step(h, false, dt);
     h->dt_valid = false;
-    return fail(h, enqueue_step(h, false, dt));
+    h->rate_pending = e == hipSuccess && step_chains(h);
+    return fail(h, e);
 }
 
 int hydro_step_auto(hydro_t h, int nsteps, double t_end) {
@@ -1111,9 +1164,11 @@ int hydro_step_auto(hydro_t h, int nsteps, double t_end) {
     // The dt of the first step comes from a standalone reduction when the
     // state changed since the last device-dt step; every later dt from the
     // previous step's epilogue.
-    hipError_t e = launch_ctrl(h->ctrl, CTRL_SET_LIMITS, t_end, 0.0, h->cfg.cfl, h->stream);
-    if (e == hipSuccess && !h->dt_valid) e = enqueue_dt(h);
+    (void)capturing(h);
+    hipError_t e = enqueue_limits(h, 0.0, t_end);
+    if (e == hipSuccess) e = enqueue_first_dt(h);
     for (int s = 0; s < nsteps && e == hipSuccess; ++s) e = enqueue_step(h, true, 0.0);
+    if (e == hipSuccess && step_chains(h)) e = enqueue_finalize(h);
     return fail(h, e);
 }
 
@@ -1121,7 +1176,8 @@ int hydro_set_run_limit(hydro_t h, int64_t max_steps, double t_end) {
     int rc = usable(h);
     if (rc) return rc;
     if (max_steps < 0 || !(t_end >= 0.0) || !std::isfinite(t_end)) return HYDRO_E_INVAL;
-    return fail(h, launch_ctrl(h->ctrl, CTRL_SET_LIMITS, t_end, (double)max_steps, h->cfg.cfl, h->stream));
+    (void)capturing(h);
+    return fail(h, enqueue_limits(h, (double)max_steps, t_end));
 }
 
 int hydro_run_done(hydro_t h, int* done) {
@@ -1331,9 +1387,11 @@ int hydro_autotune(hydro_t h, int steps_per_tile, double t_end, int* tiles, doub
     // on the tile): enqueue_step's launches with events between the stages.
     // One untimed step first, then the candidates in turn, round after round,
     // so clock ramp-up or drift does not favour the candidates timed last.
-    if (e == hipSuccess) e = launch_ctrl(h->ctrl, CTRL_SET_LIMITS, t_end, 0.0, h->cfg.cfl, h->stream);
-    if (e == hipSuccess && !h->dt_valid) e = enqueue_dt(h);
+    if (e == hipSuccess) e = enqueue_limits(h, 0.0, t_end);
+    if (e == hipSuccess) e = enqueue_first_dt(h);
     if (e == hipSuccess) e = enqueue_step(h, true, 0.0);
+    // the timed steps' books are kept by control launches outside the events
+    if (e == hipSuccess && step_chains(h)) e = enqueue_finalize(h);
     for (int s = 0; s < steps_per_tile && e == hipSuccess; ++s) {
         for (int c = 0; c < nc && e == hipSuccess; ++c) {
             hipEvent_t* q = &ev[((size_t)c * steps_per_tile + s) * 3];
@@ -1739,8 +1797,9 @@ bool members_ok(int n, const hydro_t* members) {
     return true;
 }
 
-// One batched Heun step: every group's stage 1, every group's stage 2, then
-// each member's time / dt update.
+// One batched step: every group's stage 1, then every group's stage 2 (they
+// keep the members' books; enqueue_batch_steps ends with every member's
+// pending rate used).
 hipError_t enqueue_batch_step(hydro_batch_t b) {
     hipError_t e = hipSuccess;
     for (const auto& g : b->groups)
@@ -1751,15 +1810,38 @@ hipError_t enqueue_batch_step(hydro_batch_t b) {
         if (e == hipSuccess)
             e = launch_stage_batch(g.ndim, g.precision, g.integrator == HYDRO_VL2 ? MODE_VL2_CORR : MODE_STAGE2,
                                    g.tile, b->d_desc, b->d_blk + g.blk_off, g.nblk, b->stream);
+    return e;
+}
+
+hipError_t enqueue_batch_steps(hydro_batch_t b, int nsteps) {
+    hipError_t e = hipSuccess;
+    for (int s = 0; s < nsteps && e == hipSuccess; ++s) e = enqueue_batch_step(b);
     if (e == hipSuccess) e = launch_ctrl_batch(b->d_desc, (int)b->members.size(), b->stream);
     return e;
 }
 
+// A dt for every member's first step, pending where there is none.
+hipError_t enqueue_batch_first_dt(hydro_batch_t b) {
+    hipError_t e = hipSuccess;
+    for (hydro_t h : b->members) {
+        (void)capturing(h);
+        if (!h->dt_valid && e == hipSuccess) e = enqueue_rate(h);
+    }
+    return e;
+}
+
+void batch_stepped(hydro_batch_t b) {
+    for (hydro_t h : b->members) {
+        h->dt_valid = true;
+        h->rate_pending = false;
+    }
+}
+
 // nsteps batched steps with the groups spread over streams: each group's
-// stage 1, stage 2 and members' time / dt update on its stream, step after
-// step (a member's steps depend on no other group), forked from the batch's
+// stage 1 and stage 2 on its stream, step after step (a member's steps depend
+// on no other group), forked from the batch's
 // stream and joined back to it at the end.  The same results as
-// enqueue_batch_step nsteps times.
+// enqueue_batch_steps.
 hipError_t enqueue_batch_steps_streams(hydro_batch_t b, int nsteps) {
     hipError_t e = hipEventRecord(b->ev_fork, b->stream);
     const int nside = (int)b->side.size();
@@ -1775,7 +1857,12 @@ hipError_t enqueue_batch_steps_streams(hydro_batch_t b, int nsteps) {
             if (e == hipSuccess)
                 e = launch_stage_batch(g.ndim, g.precision, vl2 ? MODE_VL2_CORR : MODE_STAGE2, g.tile, b->d_desc,
                                        b->d_blk + g.blk_off, g.nblk, st);
-            if (e == hipSuccess) e = launch_ctrl_batch(b->d_desc + g.mem_off, g.nmem, st);
+        }
+    if (e == hipSuccess)
+        for (size_t gi = 0; gi < b->groups.size() && e == hipSuccess; ++gi) {
+            const int k = b->group_stream[gi];
+            e = launch_ctrl_batch(b->d_desc + b->groups[gi].mem_off, b->groups[gi].nmem,
+                                  k > 0 && k <= nside ? b->side[k - 1] : b->stream);
         }
     // joined whatever happened above, so no side-stream work outlives a call
     for (int i = 0; i < nside; ++i) {
@@ -1857,16 +1944,14 @@ int hydro_batch_step(hydro_batch_t b, int nsteps) {
     if (b->broken) return HYDRO_E_STATE;
     if (nsteps < 0) return HYDRO_E_INVAL;
     if (nsteps == 0) return HYDRO_OK;
-    hipError_t e = hipSuccess;
-    for (hydro_t h : b->members) {
+    for (hydro_t h : b->members)
         if (h->broken) return HYDRO_E_STATE;
-        if (!h->dt_valid && e == hipSuccess) e = enqueue_dt(h);
-    }
+    hipError_t e = enqueue_batch_first_dt(b);
     if (e == hipSuccess && b->use_graph) {
         if (b->graph_steps != nsteps) {
             drop_graph(b);
             e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
-            for (int s = 0; s < nsteps && e == hipSuccess; ++s) e = enqueue_batch_step(b);
+            if (e == hipSuccess) e = enqueue_batch_steps(b, nsteps);
             hipGraph_t g = nullptr;
             hipError_t e2 = hipStreamEndCapture(b->stream, &g);
             if (e == hipSuccess) e = e2;
@@ -1885,13 +1970,13 @@ int hydro_batch_step(hydro_batch_t b, int nsteps) {
         // refined-mesh step avoids it for the same reason)
         e = enqueue_batch_steps_streams(b, nsteps);
     } else {
-        for (int s = 0; s < nsteps && e == hipSuccess; ++s) e = enqueue_batch_step(b);
+        e = enqueue_batch_steps(b, nsteps);
     }
     if (e != hipSuccess) {
         b->broken = true;
         return HYDRO_E_DEVICE;
     }
-    for (hydro_t h : b->members) h->dt_valid = true;
+    batch_stepped(b);
     return HYDRO_OK;
 }
 
@@ -1922,17 +2007,16 @@ int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule_out, dou
         assign_group_streams(b);
         return x;
     };
-    for (hydro_t h : b->members)
-        if (!h->dt_valid && e == hipSuccess) e = enqueue_dt(h);
+    if (e == hipSuccess) e = enqueue_batch_first_dt(b);
     // one untimed step, then the rules in turn, round after round (real steps
     // of every member; the results do not depend on the tiles)
-    if (e == hipSuccess) e = enqueue_batch_step(b);
+    if (e == hipSuccess) e = enqueue_batch_steps(b, 1);
     for (int s = 0; s < steps_per_rule && e == hipSuccess; ++s)
         for (int r = 0; r < kNumBatchRules && e == hipSuccess; ++r) {
             hipEvent_t* q = &ev[((size_t)s * kNumBatchRules + r) * 2];
             e = upload(plans[r]);
             if (e == hipSuccess) e = hipEventRecord(q[0], b->stream);
-            if (e == hipSuccess) e = enqueue_batch_step(b);
+            if (e == hipSuccess) e = enqueue_batch_steps(b, 1);
             if (e == hipSuccess) e = hipEventRecord(q[1], b->stream);
         }
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
@@ -1961,7 +2045,7 @@ int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule_out, dou
         b->broken = true;
         return HYDRO_E_DEVICE;
     }
-    for (hydro_t h : b->members) h->dt_valid = true;
+    batch_stepped(b);
     *rule_out = best;
     *ms_per_step = ms[best] / steps_per_rule;
     return HYDRO_OK;
