@@ -772,62 +772,46 @@ __device__ __forceinline__ void load_as_double(const T* __restrict__ F, long lon
 // the plane (4 TX + 4 TY <= TX TY).
 // Work-groups per CU the compiler is asked to fit: the FP32 path keeps four
 // 256-thread groups per CU (16 waves); FP64 needs more registers per thread.
-// The input ring and the one-barrier schedule pay in 3-D only: the 2-D
-// kernels (one row of 64..256 cells) already run many small work-groups per
-// CU, and measured slower with either.
+// The input ring pays in 3-D only: the 2-D kernels (one row of 64..256 cells)
+// already run many small work-groups per CU, and measured slower with it.
 constexpr bool kRing2D = false;
-constexpr bool kOne2D = false;
 
 template <int NDIM, typename R, int MODE>
 struct StageOccupancy {
     // Input ring: the raw input values of a cell, read for its conversion
-    // when its plane enters the z stencil, are kept in a three-plane LDS ring
-    // until the update of that plane instead of being read again.  It pays
-    // in the mixed stages (measured at 256^3 at the sustained clock: stage 1
-    // 392 -> 371 us with 32 x 8 tiles in place of 32 x 16 and one barrier
-    // per plane): there the ring's LDS sets the occupancy to three
-    // work-groups per CU, which their register use allows without spills.
-    // The FP64 stage 1 loses a wave per SIMD to it and does without.
+    // when its plane enters the z stencil, are kept in LDS until the update
+    // of that plane instead of being read again.  Two planes suffice: the
+    // value of the plane that is updated is taken out at the top of the
+    // iteration, before that of the plane two ahead goes into its place.
+    // With three planes (and one prefetch more in stage 2) the mixed stages
+    // held twelve waves on a CU; with two they hold sixteen in work-groups of
+    // 32 x 16, whose halo and extra faces are a quarter less than those of
+    // 32 x 8: at 256^3 stage 1 357 -> 333 us, stage 2 463 -> 450 us.  The
+    // FP64 stages lose a wave per SIMD to it and do without.  The van Leer
+    // predictor looks one plane ahead only, so it needs one.
+    static constexpr bool kPred = MODE == MODE_VL2_PRED || MODE == MODE_VL2_PRED_C;
     static constexpr bool kRing =
-        sizeof(R) == 4 && (MODE == MODE_STAGE2 || MODE == MODE_STAGE1) && (NDIM == 3 || kRing2D);
+        (kPred || (sizeof(R) == 4 && (MODE == MODE_STAGE2 || MODE == MODE_STAGE1))) && (NDIM == 3 || kRing2D);
     // occupancy range (waves per SIMD) the compiler aims for: at least
     // kWaves (its register budget), at most kWavesMax (8: no bound)
-    static constexpr int kWaves =
-        sizeof(R) == 4 ? ((kRing || (NDIM == 3 && MODE == MODE_STAGE1)) ? 3 : 4) : 2;
+    // The FP64 stage 2 holds three (twelve waves on a CU) without the double
+    // buffers of W and the fluxes that one barrier per plane takes: 653 us at
+    // 256^3 against 689 us in eight waves with one barrier.
+    static constexpr int kWaves = sizeof(R) == 4 ? 4 : (NDIM == 3 ? 3 : 2);
     static constexpr int kWavesMax = 8;
-    // One barrier per plane (double-buffered W and flux tiles): measured
-    // faster for the FP64 stage 2; the mixed stages would need a fourth ring
-    // plane and lose a work-group per CU.
-    // The marching loop unrolled by two with two prefetch buffers, so that
-    // the prefetched plane is not copied between loop-carried registers
-    // (which makes the compiler wait for the load in the iteration that
-    // issued it).  It pays where registers allow: the mixed 3-D stage 2; the
-    // mixed stage 1 would spill at its four-wave register budget.
-    static constexpr bool kUnroll2 = NDIM == 3 && sizeof(R) == 4 && MODE == MODE_STAGE2;
-    static constexpr bool kOneBarrier =
-        (NDIM == 3 || kOne2D) &&
-        sizeof(R) == 8 && MODE == MODE_STAGE2;
     // The raw halo cell of the next plane loaded one iteration ahead, so the
     // barrier after the plane's W does not wait for it: ten more registers.
-    // Measured at 256^3: the Heun stage 2 holds them without losing
-    // occupancy (mixed 598 -> 556 us; FP64 unchanged); the mixed stage 1
-    // gains about 2 %; the FP64 stage 1 loses 6 % and does without.
+    // Measured at 256^3: the mixed Heun stage 2 holds them (462 -> 452 us at
+    // four waves per SIMD), the mixed stage 1 gains about 2 %; the FP64 stages
+    // lose 5-6 % (a wave per SIMD) and do without.
     static constexpr bool kHaloPrefetch =
-        NDIM == 3 && (MODE == MODE_STAGE2 || (MODE == MODE_STAGE1 && sizeof(R) == 4));
-    // U^n of the next updated plane loaded during this plane's update,
-    // before its stores, instead of at the next update (where the load is
-    // consumed at once): ten more registers.  Measured at 256^3: the mixed
-    // Heun stage 2 holds them at three waves per SIMD (543 -> 530 us); the
-    // FP64 stage 2 loses 2.4 % and does without.
-    static constexpr bool kBasePrefetch = NDIM == 3 && sizeof(R) == 4 && MODE == MODE_STAGE2;
+        NDIM == 3 && sizeof(R) == 4 && (MODE == MODE_STAGE2 || MODE == MODE_STAGE1);
     // The waves that convert the halo cells and compute the faces past the
     // tile's last row and column (the first waves of the work-group) run at
     // raised priority through that work, up to the barrier after the faces:
-    // they are the ones the other waves wait for there.  Measured at 256^3
-    // with two barriers per plane: mixed stage 2 -4.5 %, FP64 stage 1
-    // -6.5 %; with one barrier per plane (the other two 3-D kernels) it cost
-    // 1.5-4 %, so those keep the default priority.
-    static constexpr bool kPrio = NDIM == 3 && !kOneBarrier;
+    // they are the ones the other waves wait for there.  Measured at 256^3:
+    // mixed stage 2 -4.5 %, FP64 stage 1 -6.5 %.
+    static constexpr bool kPrio = NDIM == 3;
 };
 
 template <int NDIM, typename R, int MODE, int TX, int TY>
@@ -845,6 +829,8 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     constexpr bool CORR = MODE == MODE_VL2_CORR || MODE == MODE_VL2_CORR_C;
     constexpr bool PRIM_OUT = MODE == MODE_VL2_PRED;
     constexpr bool FIRST = PRED;
+    // the stencil's reach on every axis: one cell for piecewise-constant states
+    constexpr int HW = FIRST ? 1 : 2;
     constexpr bool PRIM_IN = MODE == MODE_VL2_CORR;
     constexpr bool NEED_UIN = MODE == MODE_STAGE1 || MODE == MODE_STAGE2 || PRED;
     constexpr bool NEED_BASE = MODE == MODE_STAGE2 || CORR;
@@ -883,17 +869,17 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     int hx = 0, hy = 0, hvax = -1, hvm = VM_NONE, hk = 0;
     long long hcol = 0, hc = 0;
     {
-        const int nhx = 4 * ay;
-        const int nhy = HY ? 4 * ax : 0;
+        const int nhx = 2 * HW * ay;
+        const int nhy = HY ? 2 * HW * ax : 0;
         if (tid < nhx) {
-            const int q = tid & 3;
-            hy = tid >> 2;
-            hx = q < 2 ? q - 2 : ax + (q - 2);
+            const int q = tid % (2 * HW);
+            hy = tid / (2 * HW);
+            hx = q < HW ? q - HW : ax + (q - HW);
             hact = true;
         } else if (tid < nhx + nhy) {
-            const int h2 = tid - nhx, q = h2 & 3;
-            hx = h2 >> 2;
-            hy = q < 2 ? q - 2 : ay + (q - 2);
+            const int h2 = tid - nhx, q = h2 % (2 * HW);
+            hx = h2 / (2 * HW);
+            hy = q < HW ? q - HW : ay + (q - HW);
             hact = true;
         }
         if (hact) {
@@ -930,34 +916,81 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
         slot0 = load_slot(a.ctrl, 0);
         slot1 = load_slot(a.ctrl, 1);
     }
+    // the step's length, and whether the mesh still runs (uniform over the
+    // launch; the leader is one work-group of the mesh's launch): taken before
+    // the first planes in 3-D, and while they are on their way in 1-D and 2-D,
+    // whose chunks are short (a batch of 48 meshes 5.78 -> 5.61 ms; the FP64
+    // 3-D stage 1 would lose 3 % to it)
+    constexpr bool CTRL_FIRST = NDIM == 3;
+    double lam0 = 0.0, lam1 = 0.0, lam2 = 0.0;
+    unsigned int par = 0;
+    auto take_step = [&]() __attribute__((always_inline)) -> bool {
+        double dt_step = a.dt_host;
+        if (a.chain && !EPILOGUE) {
+            const StepCtl n = begin_step(a.ctrl, g.cfl, slots_max(a.ctrl->par ? slot1 : slot0));
+            if (leader) {
+                if (tid == 0) {
+                    *ctrl_next(a.ctrl) = n;
+                    if (a.use_device_dt && a.ctrl->pend == kPendRate && a.ctrl->pend_flags)
+                        atomicOr(&a.ctrl->flags, a.ctrl->pend_flags);
+                    a.ctrl->pend_flags = 0;
+                }
+                if (tid < kRateSlots) *rate_slot(a.ctrl, n.par, tid) = 0ull;
+            }
+            if (a.use_device_dt) {
+                if (n.done) return false;
+                dt_step = n.dt;
+            }
+        } else if (a.chain) {
+            const StepCtl n = *ctrl_next(a.ctrl);
+            par = __builtin_amdgcn_readfirstlane(n.par);
+            if (leader && tid == 0) {
+                a.ctrl->par = n.par;
+                a.ctrl->pend = a.use_device_dt ? (n.done ? kPendNone : kPendStep) : kPendRate;
+                a.ctrl->dt_raw = n.dt_raw;
+                a.ctrl->t = a.use_device_dt ? n.t : n.t + a.dt_host;
+                a.ctrl->steps = a.use_device_dt ? n.steps : n.steps + 1;
+                a.ctrl->done = n.done;
+                a.ctrl->dt_valid = a.use_device_dt ? 1 : 0;
+            }
+            if (a.use_device_dt) {
+                if (n.done) return false;
+                dt_step = n.dt;
+            }
+        } else {
+            if (a.use_device_dt) dt_step = device_dt(a.ctrl);
+            if (EPILOGUE) par = a.ctrl->par;
+        }
+        dt_step = uniform(dt_step);
+        const double dt = PRED ? 0.5 * dt_step : dt_step;  // the predictor advances half a step
+        lam0 = uniform(dt / g.dx[0]);
+        lam1 = uniform(dt / g.dx[1]);
+        lam2 = uniform(dt / g.dx[2]);
+        return true;
+    };
+    if (CTRL_FIRST && !take_step()) return;
     const Gas<R> gr = make_gas<R>(g.gamma);
 
     constexpr bool RING = StageOccupancy<NDIM, R, MODE>::kRing && HZ;
-    // One barrier per plane: plane k's W and fluxes go to buffer k & 1 and
-    // the update of plane k-1 follows the face pass of plane k, so the
-    // barrier that publishes plane k's W also publishes plane k-1's fluxes.
-    constexpr bool ONE = StageOccupancy<NDIM, R, MODE>::kOneBarrier;
-    constexpr int NB = ONE ? 2 : 1;
-    constexpr int RS = ONE ? 4 : 3;  // ring slots: planes k-1 .. k+2 live at once
+    constexpr int RS = HW;  // ring slots: planes k .. k + HW - 1 between iterations
     __shared__ double sRaw[RING ? RS : 1][RING ? NC : 1][RING ? NT : 1];
     // rows of the W tile: in 1-D and 2-D a tile is one row (row offset RO)
     constexpr int RO = HY ? 0 : -2;
-    __shared__ R sW[NB][NC][HY ? TY + 4 : 1][TX + 4];
+    __shared__ R sW[NC][HY ? TY + 4 : 1][TX + 4];
     using FT = R;
-    __shared__ FT sFx[NB][NC][TY][TX + 1];
-    __shared__ FT sFy[NB][HY ? NC : 1][HY ? TY + 1 : 1][TX];
+    __shared__ FT sFx[NC][TY][TX + 1];
+    __shared__ FT sFy[HY ? NC : 1][HY ? TY + 1 : 1][TX];
 
     bool bad = false, bad_new = false;  // of the stage's input, and of the new state
     double rate = 0.0;
-    // z pipeline entering iteration k: W_k, W_{k+1}, d = W_{k+1} - W_k, the
-    // left state of face k+1/2 (W_k + delta_k / 2); fza, fzb: the fluxes of
-    // faces k-3/2 and k-1/2 (fzb only, without ONE)
+    // z pipeline entering iteration k: W_k and, with PLM, W_{k+1}, d = W_{k+1} -
+    // W_k, the left state of face k+1/2 (W_k + delta_k / 2); fzb: the flux of
+    // face k-1/2
     R wk[NC], wk1[NC], dk[NC], lz[NC];
-    FT fza[NC], fzb[NC];
-    // raw interior plane k+2 in flight (HZ), in two buffers that alternate
-    // between iterations so a load lands directly where it is consumed
-    double uiA[NC], uiB[NC];
-    int vmA = VM_NONE, vmB = VM_NONE;
+    FT fzb[NC];
+    // raw interior plane k+HW in flight (HZ)
+    double ui[NC];
+    int vmi = VM_NONE;
     // the raw halo cell of this thread (HALO_PF: the next plane's, in flight)
     constexpr bool HALO_PF = StageOccupancy<NDIM, R, MODE>::kHaloPrefetch;
     constexpr bool PRIO = StageOccupancy<NDIM, R, MODE>::kPrio;
@@ -1012,32 +1045,37 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     };
 
     if (HZ && act) {
-        R w[4][NC];
+        // planes z0-HW .. z0+HW-1: face z0-1/2 and, with PLM, the left state of
+        // face z0+1/2, in the operations face_flux uses
+        R w[2 * HW][NC];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int q = 0; q < 2 * HW; ++q) {
             int vm;
             double u[NC];
-            load_interior(z0 - 2 + s, u, vm);
-            in_to_w<NDIM, R, PRIM_IN>(gm1, u, vm == VM_NONE ? -1 : 2, vm, w[s], bad);
-            if (RING && s >= 2) {
+            load_interior(z0 - HW + q, u, vm);
+            in_to_w<NDIM, R, PRIM_IN>(gm1, u, vm == VM_NONE ? -1 : 2, vm, w[q], bad);
+            if (RING && q >= HW) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) sRaw[RING ? (z0 - 2 + s) % RS : 0][RING ? c : 0][RING ? tid : 0] = u[c];
+                for (int c = 0; c < NC; ++c) sRaw[RING ? (z0 - HW + q) % RS : 0][RING ? c : 0][RING ? tid : 0] = u[c];
             }
         }
-        // planes z0-2 .. z0+1: face z0-1/2 and the left state of face z0+1/2,
-        // in the operations face_flux uses
         R wl[NC], wr[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const R d0 = w[1][c] - w[0][c], d1 = w[2][c] - w[1][c], d2 = w[3][c] - w[2][c];
-            R s1, s2;
-            Ops<R>::minmod2(d0, d1, d2, s1, s2);
-            wl[c] = FIRST ? w[1][c] : Ops<R>::fma(R(0.5), s1, w[1][c]);
-            wr[c] = FIRST ? w[2][c] : Ops<R>::fma(R(-0.5), s2, w[2][c]);
-            lz[c] = Ops<R>::fma(R(0.5), s2, w[2][c]);
-            wk[c] = w[2][c];
-            wk1[c] = w[3][c];
-            dk[c] = d2;
+            wk[c] = w[HW][c];
+            if constexpr (FIRST) {
+                wl[c] = w[0][c];
+                wr[c] = w[1][c];
+            } else {
+                const R d0 = w[1][c] - w[0][c], d1 = w[2][c] - w[1][c], d2 = w[3][c] - w[2][c];
+                R s1, s2;
+                Ops<R>::minmod2(d0, d1, d2, s1, s2);
+                wl[c] = Ops<R>::fma(R(0.5), s1, w[1][c]);
+                wr[c] = Ops<R>::fma(R(-0.5), s2, w[2][c]);
+                lz[c] = Ops<R>::fma(R(0.5), s2, w[2][c]);
+                wk1[c] = w[3][c];
+                dk[c] = d2;
+            }
         }
         {
             R f[NC];
@@ -1045,101 +1083,47 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
 #pragma unroll
             for (int c = 0; c < NC; ++c) fzb[c] = (FT)f[c];
         }
-        load_interior(z0 + 2, uiA, vmA);
+        load_interior(z0 + HW, ui, vmi);
     }
-    // the step's length, and whether the mesh still runs (uniform over the
-    // launch; the leader is one thread of the mesh's launch)
-    double dt_step = a.dt_host;
-    unsigned int par = 0;
-    if (a.chain && !EPILOGUE) {
-        const StepCtl n = begin_step(a.ctrl, g.cfl, slots_max(a.ctrl->par ? slot1 : slot0));
-        if (leader) {
-            if (tid == 0) {
-                *ctrl_next(a.ctrl) = n;
-                if (a.use_device_dt && a.ctrl->pend == kPendRate && a.ctrl->pend_flags)
-                    atomicOr(&a.ctrl->flags, a.ctrl->pend_flags);
-                a.ctrl->pend_flags = 0;
-            }
-            if (tid < kRateSlots) *rate_slot(a.ctrl, n.par, tid) = 0ull;
-        }
-        if (a.use_device_dt) {
-            if (n.done) return;
-            dt_step = n.dt;
-        }
-    } else if (a.chain) {
-        const StepCtl n = *ctrl_next(a.ctrl);
-        par = __builtin_amdgcn_readfirstlane(n.par);
-        if (leader && tid == 0) {
-            a.ctrl->par = n.par;
-            a.ctrl->pend = a.use_device_dt ? (n.done ? kPendNone : kPendStep) : kPendRate;
-            a.ctrl->dt_raw = n.dt_raw;
-            a.ctrl->t = a.use_device_dt ? n.t : n.t + a.dt_host;
-            a.ctrl->steps = a.use_device_dt ? n.steps : n.steps + 1;
-            a.ctrl->done = n.done;
-            a.ctrl->dt_valid = a.use_device_dt ? 1 : 0;
-        }
-        if (a.use_device_dt) {
-            if (n.done) return;
-            dt_step = n.dt;
-        }
-    } else {
-        if (a.use_device_dt) dt_step = device_dt(a.ctrl);
-        if (EPILOGUE) par = a.ctrl->par;
-    }
-    dt_step = uniform(dt_step);
-    const double dt = PRED ? 0.5 * dt_step : dt_step;  // the predictor advances half a step
-    const double lam0 = uniform(dt / g.dx[0]);
-    const double lam1 = uniform(dt / g.dx[1]);
-    const double lam2 = uniform(dt / g.dx[2]);
+    if (!CTRL_FIRST && !take_step()) return;
     if (HALO_PF && hact && z0 < z1) load_halo(z0, uhalo);
-    // (BASE_PF) U^n of the first updated plane, loaded ahead
-    constexpr bool BASE_PF = StageOccupancy<NDIM, R, MODE>::kBasePrefetch && NEED_BASE;
-    // the buffers alternate with the iterations: every iteration updates a plane
-    static_assert(!BASE_PF || !ONE, "base prefetch needs an update in every iteration");
-    double ubA[NC], ubB[NC];
-    if (BASE_PF && act && z0 < z1) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            ubA[c] = plane_load<double, kNonTemporal>(a.base, c * N + boff + (long long)z0 * P, ext8, col32 * 8u);
-    }
 
-    // One iteration: plane k enters the stencil (its raw data ui, the ghost
-    // treatment vmi), plane k+3 is loaded into un (vmn), and one plane is
-    // updated (BASE_PF: with U^n from ubc, loading the next plane's into ubn).
-    auto plane = [&](const int k, double(&ui)[NC], int& vmi, double(&un)[NC], int& vmn, double(&ubc)[NC],
-                     double(&ubn)[NC]) __attribute__((always_inline)) {
-        const int bw = ONE ? (k & 1) : 0;        // buffer of plane k
-        const int ku = ONE ? k - 1 : k;          // plane updated in this iteration
-        const int bu = ONE ? (ku & 1) : 0;       // its buffer
-        const bool live = !ONE || k < z1;        // plane k exists (the last ONE iteration only updates)
+    // One iteration: plane k + HW enters the stencil (its raw data ui, the
+    // ghost treatment vmi), the plane after it is loaded into ui in its place,
+    // and one plane is updated.
+    auto plane = [&](const int k) __attribute__((always_inline)) {
         FT fzc[NC];                              // flux of face k+1/2
-        if (live && act) {
+        double uin[NC], ubase[NC];
+        if (RING && act) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) uin[c] = sRaw[RING ? k % RS : 0][RING ? c : 0][RING ? tid : 0];
+        }
+        if (act) {
             R wc[NC];
             if (HZ) {
-                // W_{k+2} arrived: z face k+1/2 from (W_k, W_{k+1}, W_{k+2})
+                // W_{k+HW} arrived: z face k+1/2
                 R w2[NC], wr[NC];
                 // the ghost treatment of a plane is the same for the whole
                 // work-group: held in a scalar register, it costs no divergence
                 const int vz = __builtin_amdgcn_readfirstlane(vmi);
                 in_to_w<NDIM, R, PRIM_IN>(gm1, ui, vz == VM_NONE ? -1 : 2, vz, w2, bad);
-                // plane k+2 is an interior plane whenever its update comes
+                // plane k+HW is an interior plane whenever its update comes
                 if (RING) {
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) sRaw[RING ? (k + 2) % RS : 0][RING ? c : 0][RING ? tid : 0] = ui[c];
+                    for (int c = 0; c < NC; ++c) sRaw[RING ? (k + HW) % RS : 0][RING ? c : 0][RING ? tid : 0] = ui[c];
                 }
-                // plane k+3 is W_{k'+2} of the next iteration k' = k+1; it lies at
-                // most two planes outside the mesh only while that iteration exists
-                if (k + 1 < z1) load_interior(k + 3, un, vmn);
+                // the next iteration's; it lies at most HW planes outside the
+                // mesh only while that iteration exists
+                if (k + 1 < z1) load_interior(k + 1 + HW, ui, vmi);
                 if constexpr (FIRST) {
-                    // face k+1/2 from the cells' values W_k and W_{k+1}
+                    // from the cells' values W_k and W_{k+1}
                     R f[NC];
-                    face_flux_states<NDIM, 2, R>(gr, wk, wk1, f);
+                    face_flux_states<NDIM, 2, R>(gr, wk, w2, f);
 #pragma unroll
                     for (int c = 0; c < NC; ++c) {
                         fzc[c] = (FT)f[c];
                         wc[c] = wk[c];
-                        wk[c] = wk1[c];
-                        wk1[c] = w2[c];
+                        wk[c] = w2[c];
                     }
                 } else {
 #pragma unroll
@@ -1169,9 +1153,9 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
                 in_to_w<NDIM, R, PRIM_IN>(gm1, u, -1, VM_NONE, wc, bad);
             }
 #pragma unroll
-            for (int c = 0; c < NC; ++c) sW[bw][c][ly + 2 + RO][lx + 2] = wc[c];
+            for (int c = 0; c < NC; ++c) sW[c][ly + 2 + RO][lx + 2] = wc[c];
         }
-        if (live && hact) {
+        if (hact) {
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(2);
             R wh[NC];
             // the halo cell of plane k: loaded one iteration ahead (HALO_PF),
@@ -1180,108 +1164,91 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
             // not checked here: every cell is checked by the tile that owns it
             in_to_w<NDIM, R, PRIM_IN, false>(gm1, uhalo, halo_vm ? hvax : -1, hvm, wh, bad);
 #pragma unroll
-            for (int c = 0; c < NC; ++c) sW[bw][c][hy + 2 + RO][hx + 2] = wh[c];
+            for (int c = 0; c < NC; ++c) sW[c][hy + 2 + RO][hx + 2] = wh[c];
             if (HALO_PF && k + 1 < z1) load_halo(k + 1, uhalo);
         }
         __syncthreads();
 
-        if (live) {
-            // x faces: face i separates tile columns i-1 and i; LDS columns i..i+3
-            if (ly < ay && lx <= ax) {
-                R w0[NC], w1[NC], w2[NC], w3[NC], F[NC];
+        // x faces: face i separates tile columns i-1 and i; LDS columns i..i+3
+        if (ly < ay && lx <= ax) {
+            R w0[NC], w1[NC], w2[NC], w3[NC], F[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                w0[c] = sW[c][ly + 2 + RO][lx];
+                w1[c] = sW[c][ly + 2 + RO][lx + 1];
+                w2[c] = sW[c][ly + 2 + RO][lx + 2];
+                w3[c] = sW[c][ly + 2 + RO][lx + 3];
+            }
+            face_flux<NDIM, 0, R, FIRST>(gr, w0, w1, w2, w3, F);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) sFx[c][ly][lx] = (FT)F[c];
+        }
+        if (HY && lx < ax && ly <= ay) {
+            R w0[NC], w1[NC], w2[NC], w3[NC], F[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                w0[c] = sW[c][HY ? ly : 0][lx + 2];
+                w1[c] = sW[c][HY ? ly + 1 : 0][lx + 2];
+                w2[c] = sW[c][ly + 2 + RO][lx + 2];
+                w3[c] = sW[c][HY ? ly + 3 : 0][lx + 2];
+            }
+            face_flux<NDIM, 1, R, FIRST>(gr, w0, w1, w2, w3, F);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) sFy[HY ? c : 0][HY ? ly : 0][lx] = (FT)F[c];
+        }
+        // faces past the last thread column / row of a full tile; in 3-D the
+        // x and y ones share one code path (axis chosen per lane)
+        const int ex = (ax == TX) ? ay : 0;
+        const int ey = (HY && ay == TY) ? ax : 0;
+        for (int e = tid; e < ex + ey; e += NT) {
+            if constexpr (PRIO) __builtin_amdgcn_s_setprio(2);
+            R w0[NC], w1[NC], w2[NC], w3[NC], F[NC];
+            if constexpr (HY) {
+                const bool yaxis = e >= ex;
+                // x face (row e, column TX) or y face (row TY, column e - ex)
+                const int r0 = yaxis ? TY : e + 2, c0 = yaxis ? e - ex + 2 : TX;
+                const int dr = yaxis ? 1 : 0, dc = yaxis ? 0 : 1;
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
-                    w0[c] = sW[bw][c][ly + 2 + RO][lx];
-                    w1[c] = sW[bw][c][ly + 2 + RO][lx + 1];
-                    w2[c] = sW[bw][c][ly + 2 + RO][lx + 2];
-                    w3[c] = sW[bw][c][ly + 2 + RO][lx + 3];
+                    w0[c] = sW[c][HY ? r0 : 0][c0];
+                    w1[c] = sW[c][HY ? r0 + dr : 0][c0 + dc];
+                    w2[c] = sW[c][HY ? r0 + 2 * dr : 0][c0 + 2 * dc];
+                    w3[c] = sW[c][HY ? r0 + 3 * dr : 0][c0 + 3 * dc];
+                }
+                face_flux_xy<R, FIRST>(gr, yaxis, w0, w1, w2, w3, F);
+                if (yaxis) {
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) sFy[c][TY][e - ex] = (FT)F[c];
+                } else {
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) sFx[c][e][TX] = (FT)F[c];
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    w0[c] = sW[c][e + 2 + RO][TX];
+                    w1[c] = sW[c][e + 2 + RO][TX + 1];
+                    w2[c] = sW[c][e + 2 + RO][TX + 2];
+                    w3[c] = sW[c][e + 2 + RO][TX + 3];
                 }
                 face_flux<NDIM, 0, R, FIRST>(gr, w0, w1, w2, w3, F);
 #pragma unroll
-                for (int c = 0; c < NC; ++c) sFx[bw][c][ly][lx] = (FT)F[c];
-            }
-            if (HY && lx < ax && ly <= ay) {
-                R w0[NC], w1[NC], w2[NC], w3[NC], F[NC];
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    w0[c] = sW[bw][c][HY ? ly : 0][lx + 2];
-                    w1[c] = sW[bw][c][HY ? ly + 1 : 0][lx + 2];
-                    w2[c] = sW[bw][c][ly + 2 + RO][lx + 2];
-                    w3[c] = sW[bw][c][HY ? ly + 3 : 0][lx + 2];
-                }
-                face_flux<NDIM, 1, R, FIRST>(gr, w0, w1, w2, w3, F);
-#pragma unroll
-                for (int c = 0; c < NC; ++c) sFy[bw][HY ? c : 0][HY ? ly : 0][lx] = (FT)F[c];
-            }
-            // faces past the last thread column / row of a full tile; in 3-D the
-            // x and y ones share one code path (axis chosen per lane)
-            const int ex = (ax == TX) ? ay : 0;
-            const int ey = (HY && ay == TY) ? ax : 0;
-            for (int e = tid; e < ex + ey; e += NT) {
-                if constexpr (PRIO) __builtin_amdgcn_s_setprio(2);
-                R w0[NC], w1[NC], w2[NC], w3[NC], F[NC];
-                if constexpr (HY) {
-                    const bool yaxis = e >= ex;
-                    // x face (row e, column TX) or y face (row TY, column e - ex)
-                    const int r0 = yaxis ? TY : e + 2, c0 = yaxis ? e - ex + 2 : TX;
-                    const int dr = yaxis ? 1 : 0, dc = yaxis ? 0 : 1;
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        w0[c] = sW[bw][c][HY ? r0 : 0][c0];
-                        w1[c] = sW[bw][c][HY ? r0 + dr : 0][c0 + dc];
-                        w2[c] = sW[bw][c][HY ? r0 + 2 * dr : 0][c0 + 2 * dc];
-                        w3[c] = sW[bw][c][HY ? r0 + 3 * dr : 0][c0 + 3 * dc];
-                    }
-                    face_flux_xy<R, FIRST>(gr, yaxis, w0, w1, w2, w3, F);
-                    if (yaxis) {
-#pragma unroll
-                        for (int c = 0; c < NC; ++c) sFy[bw][c][TY][e - ex] = (FT)F[c];
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < NC; ++c) sFx[bw][c][e][TX] = (FT)F[c];
-                    }
-                } else {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        w0[c] = sW[bw][c][e + 2 + RO][TX];
-                        w1[c] = sW[bw][c][e + 2 + RO][TX + 1];
-                        w2[c] = sW[bw][c][e + 2 + RO][TX + 2];
-                        w3[c] = sW[bw][c][e + 2 + RO][TX + 3];
-                    }
-                    face_flux<NDIM, 0, R, FIRST>(gr, w0, w1, w2, w3, F);
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) sFx[bw][c][e][TX] = (FT)F[c];
-                }
+                for (int c = 0; c < NC; ++c) sFx[c][e][TX] = (FT)F[c];
             }
         }
         if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
-        if (!ONE) __syncthreads();
+        __syncthreads();
 
-        if (act && ku >= z0) {
-            const long long kuP = boff + (long long)ku * P;  // plane offset of the updated cell
+        if (act) {
+            const long long kP = boff + (long long)k * P;  // plane offset of the cell
             const uint32_t colb = col32 * (uint32_t)sizeof(double);
-            // z fluxes of faces ku-1/2 and ku+1/2
-            const FT(&zlo)[NC] = ONE ? fza : fzb;
-            const FT(&zhi)[NC] = ONE ? fzb : fzc;
-            double uin[NC], ubase[NC];
-            if (RING) {
+            if (NEED_UIN && !RING) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) uin[c] = sRaw[RING ? ku % RS : 0][RING ? c : 0][RING ? tid : 0];
-            } else if (NEED_UIN) {
-#pragma unroll
-                for (int c = 0; c < NC; ++c) uin[c] = plane_load(a.in, c * N + kuP, ext8, colb);
+                for (int c = 0; c < NC; ++c) uin[c] = plane_load(a.in, c * N + kP, ext8, colb);
             }
-            if (BASE_PF) {
+            if (NEED_BASE) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) ubase[c] = ubc[c];
-                if (ku + 1 < z1) {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-                        ubn[c] = plane_load<double, kNonTemporal>(a.base, c * N + kuP + P, ext8, colb);
-                }
-            } else if (NEED_BASE) {
-#pragma unroll
-                for (int c = 0; c < NC; ++c) ubase[c] = plane_load<double, kNonTemporal>(a.base, c * N + kuP, ext8, colb);
+                for (int c = 0; c < NC; ++c) ubase[c] = plane_load<double, kNonTemporal>(a.base, c * N + kP, ext8, colb);
             }
             double unew[NC];
 #pragma unroll
@@ -1289,11 +1256,11 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
                 // the axis terms summed in x, y, z order from the first one
                 // (a sum of two rounded products is the same either way round,
                 // so interchanging two axes leaves the update bitwise unchanged)
-                double acc = lam0 * ((double)sFx[bu][c][ly][lx] - (double)sFx[bu][c][ly][lx + 1]);
+                double acc = lam0 * ((double)sFx[c][ly][lx] - (double)sFx[c][ly][lx + 1]);
                 if (HY)
-                    acc = acc + lam1 * ((double)sFy[bu][HY ? c : 0][HY ? ly : 0][lx] -
-                                        (double)sFy[bu][HY ? c : 0][HY ? ly + 1 : 0][lx]);
-                if (HZ) acc = acc + lam2 * ((double)zlo[c] - (double)zhi[c]);
+                    acc = acc + lam1 * ((double)sFy[HY ? c : 0][HY ? ly : 0][lx] -
+                                        (double)sFy[HY ? c : 0][HY ? ly + 1 : 0][lx]);
+                if (HZ) acc = acc + lam2 * ((double)fzb[c] - (double)fzc[c]);
                 double r;
                 if (MODE == MODE_RHS)
                     r = acc;
@@ -1303,7 +1270,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
                     r = ubase[c] + acc;
                 else
                     r = 0.5 * ubase[c] + 0.5 * (uin[c] + acc);
-                if (!PRIM_OUT) plane_store<double, EPILOGUE ? kNonTemporal : 0>(a.out, c * N + kuP, ext8, colb, r);
+                if (!PRIM_OUT) plane_store<double, EPILOGUE ? kNonTemporal : 0>(a.out, c * N + kP, ext8, colb, r);
                 unew[c] = r;
             }
             if (PRIM_OUT) {
@@ -1313,7 +1280,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
                 R* wout = reinterpret_cast<R*>(a.out);
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
-                    plane_store(wout, c * N + kuP, extR, col32 * (uint32_t)sizeof(R), (R)w[c]);
+                    plane_store(wout, c * N + kP, extR, col32 * (uint32_t)sizeof(R), (R)w[c]);
             }
             if (EPILOGUE && a.want_dt) {
                 double w[NC];
@@ -1324,22 +1291,11 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
         }
         if (HZ && act) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                if (ONE) fza[c] = fzb[c];
-                fzb[c] = fzc[c];
-            }
+            for (int c = 0; c < NC; ++c) fzb[c] = fzc[c];
         }
     };
 
-    const int kend = z1 + (ONE ? 1 : 0);
-    if constexpr (StageOccupancy<NDIM, R, MODE>::kUnroll2 && HZ) {
-        for (int k = z0; k < kend; k += 2) {
-            plane(k, uiA, vmA, uiB, vmB, ubA, ubB);
-            if (k + 1 < kend) plane(k + 1, uiB, vmB, uiA, vmA, ubB, ubA);
-        }
-    } else {
-        for (int k = z0; k < kend; ++k) plane(k, uiA, vmA, uiA, vmA, ubA, ubA);
-    }
+    for (int k = z0; k < z1; ++k) plane(k);
 
     if (bad || (bad_new && a.use_device_dt)) atomicOr(&a.ctrl->flags, FLAG_NONPHYSICAL);
     if (EPILOGUE && a.want_dt) {
@@ -2303,12 +2259,11 @@ Tile default_tile(const Geo& g, int precision, int mode) {
     } else if (g.ndim == 3) {
         // From a sweep at 256^3: 32 x 16 halves the share of halo cells and
         // extra faces where the occupancy allows it; 32 x 8 where a larger
-        // work-group would cost occupancy (the mixed Heun stages beside their
-        // input rings; the FP64 kernels other than the double-buffered Heun
-        // stage 2).  16 x 16 is 2-4 % behind those on a mesh that each fills
-        // (mixed; even in FP64) and takes over where it pads less: 48^3 mixed
-        // 28 against 31 us a step, 101 x 75 x 50 FP64 57 against 65 us.
-        const bool narrow = precision == 1 ? (mode == MODE_STAGE2 || mode == MODE_STAGE1) : mode != MODE_STAGE2;
+        // work-group would cost occupancy (the FP64 kernels).  16 x 16 is 2-8 % behind those on a
+        // mesh that each fills (even in FP64) and takes over where it pads
+        // less: 48^3 mixed 28 against 31 us a step, 101 x 75 x 50 FP64 57
+        // against 65 us.
+        const bool narrow = precision == 0;
         auto padded = [&](int tx, int ty) {
             return (double)((g.n[0] + tx - 1) / tx * tx) * ((g.n[1] + ty - 1) / ty * ty);
         };
