@@ -573,6 +573,13 @@ hipError_t enqueue_step(hydro_t h, bool device_dt, double dt) {
 // a refined mesh and that of a split mesh on streams of its own.
 bool step_chains(hydro_t h) { return !h->smr && !(h->block_streams && h->nblk > 1 && h->nbs > 0); }
 
+// Whether hydro_step_auto's steps run in one launch (see launch_run_1d_fp64);
+// under stage timing the stages are launched.
+constexpr int kRunSteps = 4096;  // steps of one such launch at most
+bool runs_whole(hydro_t h) {
+    return h->cfg.ndim == 1 && h->nblk == 1 && !h->smr && h->cfg.n[0] <= kRun1dMost && h->prof_cap == 0;
+}
+
 hipError_t enqueue_finalize(hydro_t h) {
     const hipError_t e = launch_ctrl(h->ctrl, CTRL_FINALIZE, 0.0, 0.0, h->cfg.cfl, h->stream);
     if (e == hipSuccess) {
@@ -1167,6 +1174,17 @@ int hydro_step_auto(hydro_t h, int nsteps, double t_end) {
     (void)capturing(h);
     hipError_t e = enqueue_limits(h, 0.0, t_end);
     if (e == hipSuccess) e = enqueue_first_dt(h);
+    if (runs_whole(h)) {
+        for (int s = 0; s < nsteps && e == hipSuccess; s += kRunSteps) {
+            const int k = std::min(nsteps - s, kRunSteps);
+            const int vl2 = h->cfg.integrator == HYDRO_VL2 ? 1 : 0;
+            e = h->cfg.precision == HYDRO_FP64 ? launch_run_1d_fp64(vl2, h->geo, h->U, h->ctrl, k, h->stream)
+                                               : launch_run_1d_mixed(vl2, h->geo, h->U, h->ctrl, k, h->stream);
+        }
+        h->dt_valid = e == hipSuccess;
+        h->rate_pending = false;
+        return fail(h, e);
+    }
     for (int s = 0; s < nsteps && e == hipSuccess; ++s) e = enqueue_step(h, true, 0.0);
     if (e == hipSuccess && step_chains(h)) e = enqueue_finalize(h);
     return fail(h, e);
