@@ -32,8 +32,7 @@
  *     hydro_workspace_bytes(cfg) bytes (256-byte aligned), which must outlive
  *     the handle.  The handle itself owns only host metadata (among it a
  *     pageable mirror of its control block) and, once hydro_set_block_streams turns them
- *     on, its block streams and events (a refined handle: its second stream
- *     and three events).  hydro_stage_rhs,
+ *     on, its block streams and events.  hydro_stage_rhs,
  *     hydro_padded_primitive and the host transfers of a split mesh take a
  *     temporary device buffer (stream-ordered allocation) for the call.
  *   - All device work is enqueued on the caller's HIP stream given at
@@ -166,9 +165,8 @@ int hydro_step(hydro_t h, double dt);
  * are no-ops.
  * hydro_step and hydro_step_auto enqueue kernels only (no allocation, memset
  * or host synchronisation), so a caller may capture them into a HIP graph on
- * the handle's stream.  While that stream is being captured, the forms that
- * fork work onto other streams (block streams, a refined mesh's second
- * stream) run on the handle's stream alone; the results are the same. */
+ * the handle's stream.  While that stream is being captured, block streams
+ * become nodes of the captured graph; the results are the same. */
 int hydro_step_auto(hydro_t h, int nsteps, double t_end);
 
 /* dV-weighted conserved totals, ncomp values: deterministic compensated
@@ -302,14 +300,12 @@ int hydro_profile_read(hydro_t h, double* ms_stage1, double* ms_stage2, int64_t*
  *     the fine side's by minmod-limited prolongation (eq. minmod) of the
  *     coarse cells level by level from the coarsest (a coarse block's
  *     stencil may include its own prolonged layers), on primitive variables, into ghost slots in the
- *     workspace; then the stage kernel runs per level (same-level faces read
- *     the neighbour's cells in place); then each coarse cell next to a level
+ *     workspace; then the stage kernel runs over every leaf (same-level faces
+ *     read the neighbour's cells in place); then each coarse cell next to a level
  *     jump is corrected so that its update uses the mean of the fine fluxes
  *     through its face, which keeps the totals conserved.  One global time
- *     step (the paper's default), taken from a reduction after the step.
- *     The prolongation and the flux recomputation run on a second stream the
- *     handle creates (default priority, non-blocking), overlapping the
- *     level-0 stage; every step joins it back into the handle's stream.
+ *     step (the paper's default), reduced by the second stage and its
+ *     corrections.
  *   - Not available on a refined handle (HYDRO_E_INVAL): hydro_stage_rhs,
  *     hydro_padded_primitive, hydro_autotune, hydro_set_block_streams(h, 1),
  *     batch membership.

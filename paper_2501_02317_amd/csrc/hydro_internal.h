@@ -100,6 +100,18 @@ struct Tile {
     int tx, ty, kz;
 };
 
+// Refinement levels 0 .. kMaxLevels - 1; a refined block is named by the code
+// level * 2^kLevelShift + its index on that level's block grid.
+constexpr int kMaxLevels = 4;
+constexpr int kLevelShift = 26;
+
+// First block of each level 1 .. kMaxLevels - 1 in a refined mesh's leaf
+// order (a level with no leaves starts where the next one does; unrefined
+// meshes: every entry at the block count).
+struct LevelStarts {
+    int s[kMaxLevels - 1];
+};
+
 struct StageArgs {
     const double* in;    // stencil source: U^n (stage 1 / rhs) or U1 (stage 2)
     const double* base;  // U^n for the stage-2 combine (may alias out)
@@ -121,6 +133,11 @@ struct StageArgs {
     const int* side;
     const double* gbuf;
     long long gcs;       // component stride within a ghost slot (slot = ncomp * gcs)
+    // refined: the levels of the blocks (geo holds level 0's cell widths), and
+    // the number of restriction slots (0 .. nres - 1): the cells next to those
+    // sides are corrected after the stage, which takes their rate then
+    LevelStarts starts;
+    int nres;
 };
 
 // Side codes of a refined mesh's blocks, [block][kernel axis][low, high]:
@@ -145,18 +162,6 @@ struct GhostTask {
     int lev;
 };
 
-// Refinement levels 0 .. kMaxLevels - 1; a refined block is named by the code
-// level * 2^kLevelShift + its index on that level's block grid.
-constexpr int kMaxLevels = 4;
-constexpr int kLevelShift = 26;
-
-// First block of each level 1 .. kMaxLevels - 1 in a refined mesh's leaf
-// order (a level with no leaves starts where the next one does; unrefined
-// meshes: every entry at the block count).
-struct LevelStarts {
-    int s[kMaxLevels - 1];
-};
-
 // One member of a batch: the stage kernels build StageArgs from it.
 struct MeshDesc {
     double* U;
@@ -170,7 +175,9 @@ struct MeshDesc {
 // van Leer predictor and corrector (Sec. 3.3).  The _C forms keep the
 // predicted state conserved in FP64 (a refined mesh, whose level-jump passes
 // read conserved stage inputs): the predictor writes U* = U^n + (dt/2) L_1(U^n)
-// and the corrector reads U* as its stencil input.
+// and the corrector reads U* as its stencil input.  MODE_STAGE2_R is the Heun
+// stage 2 of a refined mesh (as MODE_VL2_CORR_C the corrector of one): the
+// cells corrected after it take no part in its CFL rate.
 enum StageMode : int {
     MODE_RHS = 0,
     MODE_STAGE1 = 1,
@@ -178,7 +185,8 @@ enum StageMode : int {
     MODE_VL2_PRED = 3,
     MODE_VL2_CORR = 4,
     MODE_VL2_PRED_C = 5,
-    MODE_VL2_CORR_C = 6
+    MODE_VL2_CORR_C = 6,
+    MODE_STAGE2_R = 7
 };
 
 // The automatic chunk length (Tile::kz == 0), 1 .. kMaxAutoKz planes, of a
@@ -193,7 +201,7 @@ struct Slots {
 struct MarchCols {
     long long cols;
     int n2;
-    bool even;  // every XCD's range of work-groups holds whole blocks
+    bool per_xcd;  // the launch covers eight blocks of a split mesh: one to each XCD
 };
 int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n);
 int balanced_kz(int n2, int kz);
@@ -269,27 +277,25 @@ hipError_t launch_riemann(int precision, int ntan, double gamma, long long n, co
 
 // Static refinement passes over the ghost slots tasks[0, n) (all of one
 // kind): restriction or prolongation of the stage input U into gbuf
-// (conserved FP64 values); the fine-flux corrections of the coarse cells next
-// to every level jump, from the stage input in, into dbuf (factor * lam *
-// (coarse flux - mean of the fine fluxes), [slot][comp][face]; first: fluxes
-// of piecewise-constant states, as in the van Leer predictor); and their
-// addition to out for the restriction slots idx0 .. idx0 + n - 1 of one
-// kernel axis.  g0 and g1 are the coarse and fine levels' geometries.
-hipError_t launch_smr_restrict(const Geo& g, const double* U, const int* side, double* gbuf, long long gcs,
-                               const GhostTask* tasks, int n, Ctrl* ctrl, hipStream_t s);
+// (conserved FP64 values); and, after a stage from in to out, the fine-flux
+// corrections of the coarse cells next to every level jump (the nres
+// restriction slots): factor * lam * (coarse flux - mean of the fine fluxes)
+// added to out, a cell next to jumps on several axes in axis order (first:
+// fluxes of piecewise-constant states, as in the van Leer predictor), with
+// want_dt also the CFL rate of the corrected cells.  g holds a block's extents
+// and level 0's cell widths; the step's length is the one its first stage left
+// (StageArgs::chain).
+hipError_t launch_smr_restrict(const Geo& g, const double* U, double* gbuf, long long gcs, const GhostTask* tasks,
+                               int n, Ctrl* ctrl, hipStream_t s);
 hipError_t launch_smr_prolong(const Geo& g, const double* U, const int* side, double* gbuf, long long gcs,
                               const GhostTask* tasks, int n, Ctrl* ctrl, hipStream_t s);
-hipError_t launch_smr_reflux(int precision, int first, const Geo& g0, const Geo& g1, const double* in,
-                             double* dbuf, double factor, int use_device_dt, double dt_host, const int* side,
-                             const double* gbuf, long long gcs, const GhostTask* tasks, int n, Ctrl* ctrl,
-                             hipStream_t s);
-hipError_t launch_smr_apply(const Geo& g0, double* out, const double* dbuf, long long gcs, const GhostTask* tasks,
-                            int idx0, int n, int use_device_dt, Ctrl* ctrl, hipStream_t s);
-// CFL rate of the nblk blocks of U into the slots, a block of level L (from
-// the level starts) with g0's cell widths times 2^-L; with in_step, nothing
-// once the run limit is reached, else the rate is left pending.
+hipError_t launch_smr_correct(int precision, int first, const Geo& g, const double* in, double* out, double factor,
+                              int use_device_dt, double dt_host, const int* side, const double* gbuf, long long gcs,
+                              const GhostTask* tasks, int nres, int want_dt, Ctrl* ctrl, hipStream_t s);
+// CFL rate of the nblk blocks of U, left pending; a block of level L (from the
+// level starts) has g0's cell widths times 2^-L.
 hipError_t launch_dt_levels(const Geo& g0, const LevelStarts& starts, int nblk, const double* U, Ctrl* ctrl,
-                            int in_step, hipStream_t s);
+                            hipStream_t s);
 
 // Default tile for a mesh (kernel axes) and precision.
 Tile default_tile(const Geo& g, int precision, int mode);

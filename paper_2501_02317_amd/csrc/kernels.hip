@@ -447,6 +447,22 @@ __device__ __forceinline__ Links table_links(const int* __restrict__ side, int b
 // The sides of a launch's block: from the side codes of a refined mesh, else
 // from the uniform block grid (selected field by field, so the structure
 // stays in registers).
+__device__ __forceinline__ int block_level(const LevelStarts& starts, int blk) {
+    int lev = 0;
+#pragma unroll
+    for (int L = 1; L < kMaxLevels; ++L) lev += blk >= starts.s[L - 1] ? 1 : 0;
+    return lev;
+}
+
+// Whether cell c3 of block blk lies next to a side that a restriction slot
+// covers (a level jump onto finer blocks) on axis ax; the slot.
+__device__ __forceinline__ int jump_slot(const Geo& g, const int* __restrict__ side, int nres, int blk, int ax,
+                                         int at) {
+    const int code = at == 0 ? side[6 * blk + 2 * ax] : (at == g.n[ax] - 1 ? side[6 * blk + 2 * ax + 1] : 0);
+    const int slot = kSideSlot0 - code;
+    return slot >= 0 && slot < nres ? slot : -1;
+}
+
 __device__ __forceinline__ Links stage_links(const StageArgs& a, int blk) {
     const Geo& g = a.geo;
     const bool tab = a.side != nullptr;
@@ -790,8 +806,9 @@ struct StageOccupancy {
     // FP64 stages lose a wave per SIMD to it and do without.  The van Leer
     // predictor looks one plane ahead only, so it needs one.
     static constexpr bool kPred = MODE == MODE_VL2_PRED || MODE == MODE_VL2_PRED_C;
+    static constexpr bool kHeun = MODE == MODE_STAGE1 || MODE == MODE_STAGE2 || MODE == MODE_STAGE2_R;
     static constexpr bool kRing =
-        (kPred || (sizeof(R) == 4 && (MODE == MODE_STAGE2 || MODE == MODE_STAGE1))) && (NDIM == 3 || kRing2D);
+        (kPred || (sizeof(R) == 4 && kHeun)) && (NDIM == 3 || kRing2D);
     // occupancy range (waves per SIMD) the compiler aims for: at least
     // kWaves (its register budget), at most kWavesMax (8: no bound)
     // The FP64 stage 2 holds three (twelve waves on a CU) without the double
@@ -805,7 +822,7 @@ struct StageOccupancy {
     // four waves per SIMD), the mixed stage 1 gains about 2 %; the FP64 stages
     // lose 5-6 % (a wave per SIMD) and do without.
     static constexpr bool kHaloPrefetch =
-        NDIM == 3 && sizeof(R) == 4 && (MODE == MODE_STAGE2 || MODE == MODE_STAGE1);
+        NDIM == 3 && sizeof(R) == 4 && kHeun;
     // The waves that convert the halo cells and compute the faces past the
     // tile's last row and column (the first waves of the work-group) run at
     // raised priority through that work, up to the barrier after the faces:
@@ -832,9 +849,14 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     // the stencil's reach on every axis: one cell for piecewise-constant states
     constexpr int HW = FIRST ? 1 : 2;
     constexpr bool PRIM_IN = MODE == MODE_VL2_CORR;
-    constexpr bool NEED_UIN = MODE == MODE_STAGE1 || MODE == MODE_STAGE2 || PRED;
-    constexpr bool NEED_BASE = MODE == MODE_STAGE2 || CORR;
-    constexpr bool EPILOGUE = MODE == MODE_STAGE2 || CORR;
+    constexpr bool STAGE2 = MODE == MODE_STAGE2 || MODE == MODE_STAGE2_R;
+    constexpr bool NEED_UIN = MODE == MODE_STAGE1 || STAGE2 || PRED;
+    constexpr bool NEED_BASE = STAGE2 || CORR;
+    constexpr bool EPILOGUE = STAGE2 || CORR;
+    // the second stage of a refined mesh leaves the rate of the cells that are
+    // corrected after it to the correction (a mode of its own: the test took
+    // the unrefined mixed stage 2 over its 128 registers, 48^3 +6 %)
+    constexpr bool LEVELS = MODE == MODE_STAGE2_R || MODE == MODE_VL2_CORR_C;
     static_assert(HY || TY == 1, "tile rows need a second in-plane axis");
     static_assert(4 * TX + (HY ? 4 * TY : 0) <= NT || !HY, "one halo cell per thread");
     static_assert(HY || TX >= 4, "one halo cell per thread");
@@ -922,6 +944,8 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     // whose chunks are short (a batch of 48 meshes 5.78 -> 5.61 ms; the FP64
     // 3-D stage 1 would lose 3 % to it)
     constexpr bool CTRL_FIRST = NDIM == 3;
+    // a refined mesh's block: level 0's cell widths times 2^-lev (exact)
+    const int lev = a.side ? block_level(a.starts, blk) : 0;
     double lam0 = 0.0, lam1 = 0.0, lam2 = 0.0;
     unsigned int par = 0;
     auto take_step = [&]() __attribute__((always_inline)) -> bool {
@@ -963,9 +987,9 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
         }
         dt_step = uniform(dt_step);
         const double dt = PRED ? 0.5 * dt_step : dt_step;  // the predictor advances half a step
-        lam0 = uniform(dt / g.dx[0]);
-        lam1 = uniform(dt / g.dx[1]);
-        lam2 = uniform(dt / g.dx[2]);
+        lam0 = uniform(dt / __builtin_ldexp(g.dx[0], -lev));
+        lam1 = uniform(dt / __builtin_ldexp(g.dx[1], -lev));
+        lam2 = uniform(dt / __builtin_ldexp(g.dx[2], -lev));
         return true;
     };
     if (CTRL_FIRST && !take_step()) return;
@@ -1282,7 +1306,15 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
                 for (int c = 0; c < NC; ++c)
                     plane_store(wout, c * N + kP, extR, col32 * (uint32_t)sizeof(R), (R)w[c]);
             }
-            if (EPILOGUE && a.want_dt) {
+            bool final_value = true;
+            if (LEVELS) {
+                const int at[3] = {x0 + lx, y0 + ly, k};
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax)
+                    if (ax == 0 || (ax == 1 && HY) || (ax == 2 && HZ))
+                        final_value = final_value && jump_slot(g, a.side, a.nres, blk, ax, at[ax]) < 0;
+            }
+            if (EPILOGUE && a.want_dt && final_value) {
                 double w[NC];
                 bad_new |= !cons_to_prim<NDIM>(gm1, unew, w);
                 const double cr = cfl_rate<NDIM>(g, w);
@@ -1308,7 +1340,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
         if (tid == 0) {
             double m = red[0];
             for (int i = 1; i < NT / 64; ++i) m = red[i] > m ? red[i] : m;
-            add_rate(a.ctrl, par, m);
+            add_rate(a.ctrl, par, LEVELS ? __builtin_ldexp(m, lev) : m);
         }
     }
 }
@@ -1520,9 +1552,7 @@ __device__ __forceinline__ void prim_to_cons_cell(double gamma, const double (&w
 // 2^-L) rounds to (1 / dx) 2^L).
 __device__ __forceinline__ Geo block_geo(const Geo& g0, const LevelStarts& starts, int blk) {
     Geo g = g0;
-    int lev = 0;
-#pragma unroll
-    for (int L = 1; L < kMaxLevels; ++L) lev += blk >= starts.s[L - 1] ? 1 : 0;
+    const int lev = block_level(starts, blk);
 #pragma unroll
     for (int k = 0; k < 3; ++k) g.inv_dx[k] = __builtin_ldexp(g0.inv_dx[k], lev);
     return g;
@@ -1545,10 +1575,9 @@ __device__ __forceinline__ void block_rate(Ctrl* ctrl, double best) {
 // of level L (from the level starts) take level 0's cell widths times 2^-L
 template <int NDIM>
 __global__ __launch_bounds__(256) void dt_kernel(Geo g0, LevelStarts starts, const double* __restrict__ U,
-                                                 Ctrl* ctrl, int in_step) {
+                                                 Ctrl* ctrl) {
     constexpr int NC = NDIM + 2;
-    if (in_step && ctrl->done) return;  // uniform over the grid
-    if (!in_step && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctrl->pend = kPendRate;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctrl->pend = kPendRate;
     const Geo g = block_geo(g0, starts, blockIdx.y);
     U += (long long)blockIdx.y * NC * g.ncells;
     double best = 0.0;
@@ -1840,64 +1869,59 @@ __device__ __forceinline__ void transverse(int ax, int& lo, int& hi) {
     hi = ax == 2 ? 1 : 2;
 }
 
-// Element i (a run-time index) of a three- or four-element array, by
-// selects: indexing the array itself would place it in private memory.
+// Element i (a run-time index) of an array, by selects: indexing the array
+// itself would place it in private memory.
 __device__ __forceinline__ int at3(const int (&a)[3], int i) { return i == 0 ? a[0] : (i == 1 ? a[1] : a[2]); }
-__device__ __forceinline__ void set3(int (&a)[3], int i, int v) {
-    a[0] = i == 0 ? v : a[0];
-    a[1] = i == 1 ? v : a[1];
-    a[2] = i == 2 ? v : a[2];
-}
-__device__ __forceinline__ int at4(const int (&a)[4], int i) {
-    return i == 0 ? a[0] : (i == 1 ? a[1] : (i == 2 ? a[2] : a[3]));
-}
 
-// Raw conserved values of cell (x, y, z) of block blk of a refined mesh, at
-// most one coordinate outside the block (by up to two cells): through the
-// block's side codes, from a neighbouring block, by a mesh face's boundary
-// rule (vax, vm: the velocity treatment), or from a ghost slot.
-template <int NC>
-__device__ __forceinline__ void smr_cell(const Geo& g, const Links& L, const double* __restrict__ U,
-                                         const double* __restrict__ gbuf, long long gcs, int blk, int x, int y,
-                                         int z, double (&u)[NC], int& vax, int& vm) {
+// Where the conserved values of a refined mesh's cell lie (component c at
+// p[c * cs]), and the boundary treatment of its velocity (vax, vm).
+struct CellRef {
+    const double* p;
+    long long cs;
+    int vax, vm;
+};
+
+// Cell (x, y, z) of block blk, at most one coordinate outside the block (by up
+// to two cells): through the block's side codes, in a neighbouring block, by a
+// mesh face's boundary rule, or in a ghost slot.  The address alone, so that a
+// caller has the loads of all its cells in flight at once (read one after
+// another behind these branches, the seven cells of a prolongation took 14 us,
+// the eight of a flux correction 21 us).
+__device__ __forceinline__ CellRef smr_cell(const Geo& g, const Links& L, const double* __restrict__ U,
+                                            const double* __restrict__ gbuf, int nc, long long gcs, int blk, int x,
+                                            int y, int z) {
     int c3[3] = {x, y, z};
-    int b = blk;
-    vax = -1;
-    vm = VM_NONE;
+    int b = blk, slot = -1, sax = 0, layer = 0;
+    CellRef o;
+    o.vax = -1;
+    o.vm = VM_NONE;
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
         if (c3[ax] >= 0 && c3[ax] < g.n[ax]) continue;
-        int db = 0, sl = -1;
+        int db = 0, sl = -1, vm;
         const int q = resolve(g, L, ax, c3[ax], vm, db, sl);
         if (sl >= 0) {
-            int lo, hi;
-            transverse(ax, lo, hi);
-            const long long o = (long long)sl * NC * gcs + ((long long)q * g.n[hi] + c3[hi]) * g.n[lo] + c3[lo];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) u[c] = gbuf[o + c * gcs];
-            vm = VM_NONE;
-            return;
+            slot = sl;
+            sax = ax;
+            layer = q;
+        } else {
+            c3[ax] = q;
+            b = blk + db;
+            if (vm != VM_NONE) {
+                o.vax = ax;
+                o.vm = vm;
+            }
         }
-        c3[ax] = q;
-        b = blk + db;
-        if (vm != VM_NONE) vax = ax;
-        break;
     }
-    const long long N = g.ncells;
-    const long long o = (long long)b * NC * N + ((long long)c3[2] * g.n[1] + c3[1]) * g.n[0] + c3[0];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) u[c] = U[o + c * N];
-}
-
-// Primitive FP64 state of a refined mesh's cell (see smr_cell).
-template <int NDIM>
-__device__ __forceinline__ void smr_prim(const Geo& g, const Links& L, const double* __restrict__ U,
-                                         const double* __restrict__ gbuf, long long gcs, int blk, int x, int y,
-                                         int z, double (&w)[NDIM + 2], bool& bad) {
-    double u[NDIM + 2];
-    int vax, vm;
-    smr_cell<NDIM + 2>(g, L, U, gbuf, gcs, blk, x, y, z, u, vax, vm);
-    to_prim<NDIM, double>(g.gamma - 1.0, u, vax, vm, w, bad);
+    int lo, hi;
+    transverse(sax, lo, hi);
+    const long long in_slot =
+        (long long)slot * nc * gcs + ((long long)layer * at3(g.n, hi) + at3(c3, hi)) * at3(g.n, lo) + at3(c3, lo);
+    const long long in_block =
+        (long long)b * nc * g.ncells + ((long long)c3[2] * g.n[1] + c3[1]) * g.n[0] + c3[0];
+    o.p = slot >= 0 ? gbuf + in_slot : U + in_block;
+    o.cs = slot >= 0 ? gcs : g.ncells;
+    return o;
 }
 
 // Kernel axis of the k-th active axis (physical order: x, y, z).
@@ -1909,25 +1933,27 @@ __device__ __forceinline__ constexpr int active_axis(int k) {
 // Restriction onto the two ghost layers of a coarse block's side that faces
 // finer blocks: each ghost is the volume average of the 2^NDIM fine cells it
 // covers (pairwise means along x, then y, then z), on primitive variables;
-// stored as conserved values.  blockIdx.x: the slot; one thread per ghost.
+// stored as conserved values.  The fine cells lie inside their blocks, so they
+// are read where they are.  blockIdx.x: the slot; one thread per ghost.
+// Latency bound (a few hundred waves); reading through the side codes and a
+// private copy of the task it took 16 us for 24 slots of 32 x 32 faces.
 template <int NDIM>
 __global__ __launch_bounds__(64) void smr_restrict_kernel(Geo g, const double* __restrict__ U,
-                                                           const int* __restrict__ side, double* __restrict__ gbuf,
-                                                           long long gcs, const GhostTask* __restrict__ tasks,
-                                                           Ctrl* ctrl) {
+                                                           double* __restrict__ gbuf, long long gcs,
+                                                           const GhostTask* __restrict__ tasks, Ctrl* ctrl) {
     constexpr int NC = NDIM + 2;
     constexpr int K = 1 << NDIM;
-    const GhostTask t = tasks[blockIdx.x];
+    const GhostTask& t = tasks[blockIdx.x];
+    const int tax = t.ax, ts = t.s;
     int lo, hi;
-    transverse(t.ax, lo, hi);
-    const int gn[3] = {g.n[0], g.n[1], g.n[2]};
-    const int nlo = at3(gn, lo), nhi = at3(gn, hi), face = nlo * nhi;
+    transverse(tax, lo, hi);
+    const int nlo = at3(g.n, lo), nhi = at3(g.n, hi), face = nlo * nhi;
     bool bad = false;
     const int q = blockIdx.y * blockDim.x + threadIdx.x;
     if (q < 2 * face) {
         const int layer = q / face, r = q - layer * face;
         const int tl = r % nlo, th = r / nlo;
-        double v[NC][K];
+        double u[K][NC], v[NC][K];
 #pragma unroll
         for (int o = 0; o < K; ++o) {
             int x3[3] = {0, 0, 0};
@@ -1936,23 +1962,28 @@ __global__ __launch_bounds__(64) void smr_restrict_kernel(Geo g, const double* _
             for (int k = 0; k < NDIM; ++k) {
                 const int ax = active_axis<NDIM>(k);
                 const int off = (o >> k) & 1;
-                if (ax == t.ax) {
+                if (ax == tax) {
                     // fine cells 2 layer, 2 layer + 1 in from the face (off 0: the lower)
-                    x3[ax] = t.s ? 2 * layer + off : g.n[ax] - 2 - 2 * layer + off;
+                    x3[ax] = ts ? 2 * layer + off : g.n[ax] - 2 - 2 * layer + off;
                 } else {
                     const int p = 2 * (ax == lo ? tl : th) + off;  // from the refined root's origin
-                    cb[ax] = p / g.n[ax];
+                    cb[ax] = p >= g.n[ax] ? 1 : 0;
                     x3[ax] = p - cb[ax] * g.n[ax];
                 }
             }
-            const int fb = at4(t.src, at3(cb, lo) + 2 * at3(cb, hi));
-            const Links L = table_links(side, fb);
+            const int fb = t.src[at3(cb, lo) + 2 * at3(cb, hi)];
+            const double* F = U + (long long)fb * NC * g.ncells + ((long long)x3[2] * g.n[1] + x3[1]) * g.n[0] + x3[0];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) u[o][c] = F[c * g.ncells];
+        }
+#pragma unroll
+        for (int o = 0; o < K; ++o) {
             double w[NC];
-            smr_prim<NDIM>(g, L, U, gbuf, gcs, fb, x3[0], x3[1], x3[2], w, bad);
+            to_prim<NDIM, double>(g.gamma - 1.0, u[o], -1, VM_NONE, w, bad);
 #pragma unroll
             for (int c = 0; c < NC; ++c) v[c][o] = w[c];
         }
-        double w[NC], u[NC];
+        double w[NC], uc[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             // pairwise means: along x first (bit 0), then y, then z
@@ -1962,10 +1993,10 @@ __global__ __launch_bounds__(64) void smr_restrict_kernel(Geo g, const double* _
                 for (int i = 0; i < (K >> (k + 1)); ++i) v[c][i] = 0.5 * (v[c][2 * i] + v[c][2 * i + 1]);
             w[c] = v[c][0];
         }
-        prim_to_cons_cell<NDIM>(g.gamma, w, u);
+        prim_to_cons_cell<NDIM>(g.gamma, w, uc);
         const long long o = (long long)t.slot * NC * gcs + (long long)layer * face + r;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) gbuf[o + c * gcs] = u[c];
+        for (int c = 0; c < NC; ++c) gbuf[o + c * gcs] = uc[c];
     }
     if (bad) atomicOr(&ctrl->flags, FLAG_NONPHYSICAL);
 }
@@ -1976,115 +2007,125 @@ __global__ __launch_bounds__(64) void smr_restrict_kernel(Geo g, const double* _
 // centre the ghost's centre lies on; the coarse block's own ghosts (same
 // level, boundary rule, restricted slots) complete its stencil.  Primitive
 // variables; stored as conserved values.  blockIdx.x: the slot; one thread
-// per ghost.
+// per coarse cell, which holds both layers and 2^(NDIM-1) ghosts of each: they
+// share its stencil of 2 NDIM + 1 cells (a thread per ghost loaded and
+// converted it eight times over in 3-D, 36 us for 96 slots of 32 x 32 faces).
 template <int NDIM>
 __global__ __launch_bounds__(64) void smr_prolong_kernel(Geo g, const double* __restrict__ U,
                                                           const int* __restrict__ side, double* __restrict__ gbuf,
                                                           long long gcs, const GhostTask* __restrict__ tasks,
                                                           Ctrl* ctrl) {
     constexpr int NC = NDIM + 2;
-    const GhostTask t = tasks[blockIdx.x];
+    const GhostTask& t = tasks[blockIdx.x];
+    const int tax = t.ax, ts = t.s;
     int lo, hi;
-    transverse(t.ax, lo, hi);
-    const int gn[3] = {g.n[0], g.n[1], g.n[2]};
-    const int nlo = at3(gn, lo), nhi = at3(gn, hi), face = nlo * nhi;
+    transverse(tax, lo, hi);
+    const int nlo = at3(g.n, lo), nhi = at3(g.n, hi), face = nlo * nhi;
+    // coarse cells across the side (an axis of one cell is inactive)
+    const int mlo = nlo > 1 ? nlo / 2 : 1, mhi = nhi > 1 ? nhi / 2 : 1;
     const int cblk = t.src[0];
     const Links L = table_links(side, cblk);
     bool bad = false;
     const int q = blockIdx.y * blockDim.x + threadIdx.x;
-    if (q < 2 * face) {
-        const int layer = q / face, r = q - layer * face;
+    if (q < mlo * mhi) {
+        const int tl = q % mlo, th = q / mlo;
         int ci[3] = {0, 0, 0};
-        double sg[3] = {0.0, 0.0, 0.0};
-        const int tl = r % nlo, th = r / nlo;
 #pragma unroll
         for (int k = 0; k < NDIM; ++k) {
             const int ax = active_axis<NDIM>(k);
-            if (ax == t.ax) {
-                // the coarse cell next to the face; the ghost's side of its centre
-                ci[ax] = t.s ? 0 : g.n[ax] - 1;
-                sg[ax] = t.s ? (layer == 0 ? -1.0 : 1.0) : (layer == 0 ? 1.0 : -1.0);
-            } else {
-                const int p = t.child[ax] * g.n[ax] + (ax == lo ? tl : th);  // fine index from the parent's origin
-                ci[ax] = p >> 1;
-                sg[ax] = (p & 1) ? 1.0 : -1.0;
-            }
+            // the coarse cell next to the face; across it, counted from the parent's origin
+            if (ax == tax)
+                ci[ax] = ts ? 0 : g.n[ax] - 1;
+            else
+                ci[ax] = t.child[ax] * (g.n[ax] / 2) + (ax == lo ? tl : th);
         }
-        double wc[NC], acc[NC];
-        smr_prim<NDIM>(g, L, U, gbuf, gcs, cblk, ci[0], ci[1], ci[2], wc, bad);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c] = wc[c];
+        // the cell and its neighbours below and above on each axis
+        CellRef at[2 * NDIM + 1];
+        at[0] = smr_cell(g, L, U, gbuf, NC, gcs, cblk, ci[0], ci[1], ci[2]);
 #pragma unroll
         for (int k = 0; k < NDIM; ++k) {
             const int ax = active_axis<NDIM>(k);
             int a3[3] = {ci[0], ci[1], ci[2]}, b3[3] = {ci[0], ci[1], ci[2]};
             a3[ax] -= 1;
             b3[ax] += 1;
-            double wl[NC], wh[NC];
-            smr_prim<NDIM>(g, L, U, gbuf, gcs, cblk, a3[0], a3[1], a3[2], wl, bad);
-            smr_prim<NDIM>(g, L, U, gbuf, gcs, cblk, b3[0], b3[1], b3[2], wh, bad);
-#pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c] = acc[c] + (0.25 * sg[ax]) * minmod(wc[c] - wl[c], wh[c] - wc[c]);
+            at[1 + 2 * k] = smr_cell(g, L, U, gbuf, NC, gcs, cblk, a3[0], a3[1], a3[2]);
+            at[2 + 2 * k] = smr_cell(g, L, U, gbuf, NC, gcs, cblk, b3[0], b3[1], b3[2]);
         }
-        double u[NC];
-        prim_to_cons_cell<NDIM>(g.gamma, acc, u);
-        const long long o = (long long)t.slot * NC * gcs + (long long)layer * face + r;
+        double u7[2 * NDIM + 1][NC], w7[2 * NDIM + 1][NC], slope[NDIM][NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) gbuf[o + c * gcs] = u[c];
+        for (int j = 0; j < 2 * NDIM + 1; ++j)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) u7[j][c] = at[j].p[c * at[j].cs];
+#pragma unroll
+        for (int j = 0; j < 2 * NDIM + 1; ++j)
+            to_prim<NDIM, double>(g.gamma - 1.0, u7[j], at[j].vax, at[j].vm, w7[j], bad);
+        const double(&wc)[NC] = w7[0];
+#pragma unroll
+        for (int k = 0; k < NDIM; ++k)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                slope[k][c] = minmod(wc[c] - w7[1 + 2 * k][c], w7[2 + 2 * k][c] - wc[c]);
+#pragma unroll
+        for (int o = 0; o < (1 << NDIM); ++o) {
+            // bit k of o: the side of the coarse centre on the k-th active axis
+            double acc[NC], u[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[c] = wc[c];
+            int layer = 0, fl = 0, fh = 0;
+#pragma unroll
+            for (int k = 0; k < NDIM; ++k) {
+                const int ax = active_axis<NDIM>(k), bit = (o >> k) & 1;
+                if (ax == tax)
+                    layer = ts ? bit : 1 - bit;
+                else if (ax == lo)
+                    fl = 2 * tl + bit;
+                else
+                    fh = 2 * th + bit;
+                const double sg = bit ? 1.0 : -1.0;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[c] = acc[c] + (0.25 * sg) * slope[k][c];
+            }
+            prim_to_cons_cell<NDIM>(g.gamma, acc, u);
+            const long long to = (long long)t.slot * NC * gcs + (long long)layer * face + fh * nlo + fl;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) gbuf[to + c * gcs] = u[c];
+        }
     }
     if (bad) atomicOr(&ctrl->flags, FLAG_NONPHYSICAL);
 }
 
-// Flux correction at a level jump of kernel axis AX, for coarse face r of
-// restriction slot t: the coarse cell next to the face is to get
-// factor * lam * (F_coarse - mean of the fine fluxes) (sign by side), so that
-// its update uses the fine fluxes' mean in place of its own.  The fluxes are
-// recomputed from the same stage input, ghosts and operations as in the
-// stage kernel, so F_coarse cancels exactly.  The correction goes to
-// dbuf[idx][comp][r]; smr_apply_kernel adds it.
+// Flux correction at a level jump of kernel axis AX, for coarse cell x3 next
+// to restriction slot t: the cell is to get factor * lam * (F_coarse - mean of
+// the fine fluxes) (sign by side), so that its update uses the fine fluxes'
+// mean in place of its own.  The fluxes are recomputed from the same stage
+// input, ghosts and operations as in the stage kernel, so F_coarse cancels
+// exactly; the correction is added to u.  A lane per fine face: 2^NT adjacent
+// lanes share the coarse one (o: this lane's), so the fine fluxes run side by
+// side and their mean is two exchanges.
 template <int NDIM, typename R, bool FIRST, int AX>
-__device__ __forceinline__ void reflux_face(const Geo& g0, const Geo& g1, const double* __restrict__ in,
-                                            double* __restrict__ dbuf, double factor, double dt,
+__device__ __forceinline__ void reflux_cell(const Geo& g, const double* __restrict__ in, double factor, double dt,
                                             const int* __restrict__ side, const double* __restrict__ gbuf,
-                                            long long gcs, const GhostTask& t, int idx, int r, bool& bad) {
+                                            long long gcs, const GhostTask& t, const int (&x3)[3], int o,
+                                            double (&ucell)[NDIM + 2], bool& bad) {
     constexpr int NC = NDIM + 2;
     constexpr int NT = NDIM - 1;
     // the coarse block's cell width: level 0's times 2^-lev (exact)
-    const double lam = dt / __builtin_ldexp(g0.dx[AX], -t.lev);
-    const Gas<R> gr = make_gas<R>(g0.gamma);
-    const double gm1 = g0.gamma - 1.0;
-    int lo, hi;
-    transverse(AX, lo, hi);
-    const int nlo = g0.n[lo], nhi = g0.n[hi], face = nlo * nhi;
-    if (r >= face) return;
-    const int n = g0.n[AX];
-    const Links Lc = table_links(side, t.leaf);
-    const int tl = r % nlo, th = r / nlo;
-    int x3[3] = {0, 0, 0};
-    x3[lo] = tl;
-    x3[hi] = th;
-    // the coarse face flux from the four coarse cells across it
-    R w[4][NC];
+    const double lam = dt / __builtin_ldexp(g.dx[AX], -t.lev);
+    const Gas<R> gr = make_gas<R>(g.gamma);
+    const double gm1 = g.gamma - 1.0;
+    constexpr int lo = AX == 0 ? 1 : 0, hi = AX == 2 ? 1 : 2;
+    const int n = g.n[AX], ts = t.s;
+    // four cells across the coarse face, and across this lane's fine face (at
+    // transverse child offsets o)
+    CellRef at[2][4];
+    {
+        const Links Lc = table_links(side, t.leaf);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        int c3[3] = {x3[0], x3[1], x3[2]};
-        c3[AX] = t.s ? n - 2 + j : -2 + j;
-        double u[NC];
-        int vax, vm;
-        smr_cell<NC>(g0, Lc, in, gbuf, gcs, t.leaf, c3[0], c3[1], c3[2], u, vax, vm);
-        in_to_w<NDIM, R, false>(gm1, u, vax, vm, w[j], bad);
-    }
-    R Fc[NC];
-    face_flux<NDIM, AX, R, FIRST>(gr, w[0], w[1], w[2], w[3], Fc);
-    // the fine fluxes through it, by transverse child offsets
-    // pairwise means as the fluxes arrive (offsets 0, 1 -> a; 2, 3 -> b),
-    // the same operations as a tree of pairwise means
-    double fa[NC], fb2[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) fa[c] = fb2[c] = 0.0;
-    // not unrolled: one fine face's stencil and Riemann solve live at a time
-#pragma unroll 1
-    for (int o = 0; o < (1 << NT); ++o) {
+        for (int j = 0; j < 4; ++j) {
+            int c3[3] = {x3[0], x3[1], x3[2]};
+            c3[AX] = ts ? n - 2 + j : -2 + j;
+            at[0][j] = smr_cell(g, Lc, in, gbuf, NC, gcs, t.leaf, c3[0], c3[1], c3[2]);
+        }
         int f3[3] = {0, 0, 0};
         int cb[3] = {0, 0, 0};
         int bit = 0;
@@ -2094,94 +2135,115 @@ __device__ __forceinline__ void reflux_face(const Geo& g0, const Geo& g1, const 
             if (ax == AX) continue;
             const int p = 2 * x3[ax] + ((o >> bit) & 1);
             ++bit;
-            cb[ax] = p / g1.n[ax];
-            f3[ax] = p - cb[ax] * g1.n[ax];
+            cb[ax] = p >= g.n[ax] ? 1 : 0;
+            f3[ax] = p - cb[ax] * g.n[ax];
         }
-        const int fb = at4(t.src, cb[lo] + 2 * cb[hi]);
+        const int fb = t.src[cb[lo] + 2 * cb[hi]];
         const Links Lf = table_links(side, fb);
-        R v[4][NC];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             int c3[3] = {f3[0], f3[1], f3[2]};
-            c3[AX] = t.s ? -2 + j : g1.n[AX] - 2 + j;
-            double u[NC];
-            int vax, vm;
-            smr_cell<NC>(g1, Lf, in, gbuf, gcs, fb, c3[0], c3[1], c3[2], u, vax, vm);
-            in_to_w<NDIM, R, false>(gm1, u, vax, vm, v[j], bad);
-        }
-        R F[NC];
-        face_flux<NDIM, AX, R, FIRST>(gr, v[0], v[1], v[2], v[3], F);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const double f = (double)F[c];
-            if (o == 0) fa[c] = f;
-            else if (o == 1) fa[c] = 0.5 * (fa[c] + f);
-            else if (o == 2) fb2[c] = f;
-            else fb2[c] = 0.5 * (fb2[c] + f);
+            c3[AX] = ts ? -2 + j : n - 2 + j;
+            at[1][j] = smr_cell(g, Lf, in, gbuf, NC, gcs, fb, c3[0], c3[1], c3[2]);
         }
     }
-    const long long fs = gcs / 2;
+    double u8[2][4][NC];
+    R w[2][4][NC], Fc[NC], F[NC];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) u8[m][j][c] = at[m][j].p[c * at[m][j].cs];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            in_to_w<NDIM, R, false>(gm1, u8[m][j], at[m][j].vax, at[m][j].vm, w[m][j], bad);
+    face_flux<NDIM, AX, R, FIRST>(gr, w[0][0], w[0][1], w[0][2], w[0][3], Fc);
+    face_flux<NDIM, AX, R, FIRST>(gr, w[1][0], w[1][1], w[1][2], w[1][3], F);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const double mean = NT == 2 ? 0.5 * (fa[c] + fb2[c]) : fa[c];
-        const double d = t.s ? ((double)Fc[c] - mean) : (mean - (double)Fc[c]);
-        dbuf[((long long)idx * NC + c) * fs + r] = factor * (lam * d);
-    }
-}
-
-// The corrections of every restriction slot, one launch for all axes:
-// blockIdx.x the slot (in slot order), one thread per coarse face.
-// FIRST: the fluxes of piecewise-constant states (the van Leer predictor).
-template <int NDIM, typename R, bool FIRST>
-__global__ __launch_bounds__(64) void smr_reflux_kernel(Geo g0, Geo g1, const double* __restrict__ in,
-                                                         double* __restrict__ dbuf, double factor,
-                                                         int use_device_dt, double dt_host,
-                                                         const int* __restrict__ side,
-                                                         const double* __restrict__ gbuf, long long gcs,
-                                                         const GhostTask* __restrict__ tasks, Ctrl* ctrl) {
-    if (use_device_dt && ctrl->done) return;  // uniform over the grid
-    const double dt = use_device_dt ? device_dt(ctrl) : dt_host;
-    const GhostTask t = tasks[blockIdx.x];
-    const int r = blockIdx.y * blockDim.x + threadIdx.x;
-    bool bad = false;
-    if (t.ax == 0) {
-        reflux_face<NDIM, R, FIRST, 0>(g0, g1, in, dbuf, factor, dt, side, gbuf, gcs, t, blockIdx.x, r, bad);
-    } else if (t.ax == 1) {
-        if constexpr (NDIM == 3)
-            reflux_face<NDIM, R, FIRST, 1>(g0, g1, in, dbuf, factor, dt, side, gbuf, gcs, t, blockIdx.x, r, bad);
-    } else {
-        if constexpr (NDIM >= 2)
-            reflux_face<NDIM, R, FIRST, 2>(g0, g1, in, dbuf, factor, dt, side, gbuf, gcs, t, blockIdx.x, r, bad);
-    }
-    if (bad) atomicOr(&ctrl->flags, FLAG_NONPHYSICAL);
-}
-
-// Add the corrections of the restriction slots idx0 .. idx0 + gridDim.x - 1
-// (one kernel axis) to their coarse cells: out += dbuf.  One launch per axis,
-// in axis order, so a coarse cell next to jumps on two axes is corrected in a
-// fixed order.
-template <int NDIM>
-__global__ __launch_bounds__(64) void smr_apply_kernel(Geo g0, double* __restrict__ out,
-                                                        const double* __restrict__ dbuf, long long gcs,
-                                                        const GhostTask* __restrict__ tasks, int idx0,
-                                                        int use_device_dt, Ctrl* ctrl) {
-    constexpr int NC = NDIM + 2;
-    if (use_device_dt && ctrl->done) return;  // uniform over the grid
-    const GhostTask t = tasks[blockIdx.x];
-    int lo, hi;
-    transverse(t.ax, lo, hi);
-    const int nlo = g0.n[lo], face = nlo * g0.n[hi];
-    const int r = blockIdx.y * blockDim.x + threadIdx.x;
-    if (r >= face) return;
-    int c3[3] = {0, 0, 0};
-    c3[lo] = r % nlo;
-    c3[hi] = r / nlo;
-    c3[t.ax] = t.s ? g0.n[t.ax] - 1 : 0;
-    const long long N = g0.ncells;
-    const long long cell = (long long)t.leaf * NC * N + ((long long)c3[2] * g0.n[1] + c3[1]) * g0.n[0] + c3[0];
-    const long long fs = gcs / 2;
+        // pairwise means of the fine fluxes in the order of their offsets
+        double mean = (double)F[c];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) out[cell + c * N] = out[cell + c * N] + dbuf[((long long)(idx0 + blockIdx.x) * NC + c) * fs + r];
+        for (int k = 0; k < NT; ++k) mean = 0.5 * (mean + __shfl_xor(mean, 1 << k, 64));
+        const double d = ts ? ((double)Fc[c] - mean) : (mean - (double)Fc[c]);
+        ucell[c] = ucell[c] + factor * (lam * d);
+    }
+}
+
+// The flux corrections of a stage, after it, one launch for all axes.  A
+// coarse cell next to jumps on several axes is taken by the slot of its first
+// axis, which adds them in axis order.  want_dt: the CFL rate of the corrected
+// cells (which the stage left out).  FIRST: the fluxes of piecewise-constant
+// states (the van Leer predictor).  blockIdx.x: the slot; one thread per fine
+// face.  Latency bound; recomputing and adding in one launch instead of one
+// beside the stage and one per axis after it also leaves the stage alone (a
+// recomputation running beside it took it from 91 to 115 us).
+template <int NDIM, typename R, bool FIRST>
+__global__ __launch_bounds__(64) void smr_correct_kernel(Geo g, const double* __restrict__ in,
+                                                          double* __restrict__ out, double factor,
+                                                          int use_device_dt, double dt_host,
+                                                          const int* __restrict__ side,
+                                                          const double* __restrict__ gbuf, long long gcs,
+                                                          const GhostTask* __restrict__ tasks, int nres, int want_dt,
+                                                          Ctrl* ctrl) {
+    constexpr int NC = NDIM + 2;
+    constexpr int NT = NDIM - 1;
+    const StepCtl step = *ctrl_next(ctrl);  // the stage has left or used it
+    if (use_device_dt && step.done) return;  // uniform over the grid
+    const double dt = use_device_dt ? step.dt : dt_host;
+    const GhostTask& t = tasks[blockIdx.x];
+    const int tax = t.ax, leaf = t.leaf;
+    int lo, hi;
+    transverse(tax, lo, hi);
+    const int nlo = at3(g.n, lo), face = nlo * at3(g.n, hi);
+    const int q = blockIdx.y * blockDim.x + threadIdx.x, r = q >> NT, o = q & ((1 << NT) - 1);
+    double rate = 0.0;
+    bool bad = false, bad_new = false, mine = r < face;
+    int c3[3] = {0, 0, 0}, slot[3] = {-1, -1, -1};
+    if (mine) {
+        const int tl = r % nlo, th = r / nlo, side_at = t.s ? at3(g.n, tax) - 1 : 0;
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) c3[ax] = ax == tax ? side_at : (ax == lo ? tl : th);
+#pragma unroll
+        for (int k = 0; k < NDIM; ++k) {
+            const int ax = active_axis<NDIM>(k);
+            slot[ax] = ax == tax ? (int)blockIdx.x : jump_slot(g, side, nres, leaf, ax, c3[ax]);
+            mine = mine && (slot[ax] < 0 || ax >= tax);
+        }
+    }
+    if (mine) {
+        double* cell = out + (long long)leaf * NC * g.ncells + ((long long)c3[2] * g.n[1] + c3[1]) * g.n[0] + c3[0];
+        double u[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) u[c] = cell[c * g.ncells];
+        if (slot[0] >= 0)
+            reflux_cell<NDIM, R, FIRST, 0>(g, in, factor, dt, side, gbuf, gcs, tasks[slot[0]], c3, o, u, bad);
+        if constexpr (NDIM == 3)
+            if (slot[1] >= 0)
+                reflux_cell<NDIM, R, FIRST, 1>(g, in, factor, dt, side, gbuf, gcs, tasks[slot[1]], c3, o, u, bad);
+        if constexpr (NDIM >= 2)
+            if (slot[2] >= 0)
+                reflux_cell<NDIM, R, FIRST, 2>(g, in, factor, dt, side, gbuf, gcs, tasks[slot[2]], c3, o, u, bad);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if ((c & ((1 << NT) - 1)) == o) cell[c * g.ncells] = u[c];
+        if (want_dt) {
+            double w[NC];
+            bad_new = !cons_to_prim<NDIM>(g.gamma - 1.0, u, w);
+            rate = __builtin_ldexp(cfl_rate<NDIM>(g, w), t.lev);
+        }
+    }
+    if (bad || (bad_new && use_device_dt)) atomicOr(&ctrl->flags, FLAG_NONPHYSICAL);
+    if (want_dt) {
+        if (bad_new && !use_device_dt) atomicOr(&ctrl->pend_flags, FLAG_NONPHYSICAL);
+        rate = wave_max(rate > 0.0 ? rate : 0.0);
+        if (threadIdx.x == 0)
+            atomicMax(rate_slot(ctrl, step.par, (blockIdx.x + blockIdx.y) % kRateSlots),
+                      (unsigned long long)__double_as_longlong(rate));
+    }
 }
 
 // Mesh layout [comp][k][j][i] <-> block layout; q runs over the mesh cells.
@@ -2263,7 +2325,8 @@ hipError_t launch_stage_t(const LaunchCtx& L, hipStream_t s) {
             // (this launch's, or those of the launches on the other streams
             // as well)
             const int n2 = a.geo.n[2];
-            const MarchCols m{(long long)a.tiles_x * a.tiles_y * (a.conc > a.nblk ? a.conc : a.nblk), n2, a.nblk % 8 == 0};
+            const MarchCols m{(long long)a.tiles_x * a.tiles_y * (a.conc > a.nblk ? a.conc : a.nblk), n2,
+                               a.nblk == 8 && !a.side};
             a.kz = auto_kz(NDIM, stage_slots<NDIM, R, MODE, TX, TY>(), &m, 1);
             a.chunks_z = (n2 + a.kz - 1) / a.kz;
         }
@@ -2277,7 +2340,7 @@ hipError_t launch_stage_t(const LaunchCtx& L, hipStream_t s) {
             return hipSuccess;
         }
         hipLaunchKernelGGL((stage_kernel<NDIM, R, MODE, TX, TY>), dim3((unsigned)nb), dim3(TX * TY), 0, s, a);
-    } else if constexpr (MODE == MODE_RHS || MODE == MODE_VL2_PRED_C || MODE == MODE_VL2_CORR_C) {
+    } else if constexpr (MODE == MODE_RHS || MODE == MODE_STAGE2_R || MODE == MODE_VL2_PRED_C || MODE == MODE_VL2_CORR_C) {
         return hipErrorInvalidValue;  // not a batch member's stage
     } else {
         if (L.nblk <= 0) return hipSuccess;
@@ -2325,6 +2388,9 @@ hipError_t launch_stage_mode(int mode, const Tile& t, const LaunchCtx& L, hipStr
             return launch_stage_tile<NDIM, R, MODE_RHS>(t, L, s);
         case MODE_STAGE1: return launch_stage_tile<NDIM, R, MODE_STAGE1>(t, L, s);
         case MODE_STAGE2: return launch_stage_tile<NDIM, R, MODE_STAGE2>(t, L, s);
+        case MODE_STAGE2_R:
+            if (!L.a && !L.slots) return hipErrorInvalidValue;
+            return launch_stage_tile<NDIM, R, MODE_STAGE2_R>(t, L, s);
         case MODE_VL2_PRED: return launch_stage_tile<NDIM, R, MODE_VL2_PRED>(t, L, s);
         case MODE_VL2_CORR: return launch_stage_tile<NDIM, R, MODE_VL2_CORR>(t, L, s);
         case MODE_VL2_PRED_C: return launch_stage_refined<NDIM, R, MODE_VL2_PRED_C>(t, L, s);
@@ -2484,10 +2550,10 @@ int balanced_kz(int n2, int kz) {
 // (48^3 mixed: a step 102 us in chunks of 16, 28 us in chunks of 1-2; 256^2
 // FP64 89 and 21 us), and a last round of a few work-groups costs as much as a
 // full one (160^3 mixed: 316 us with 800 work-groups on 768 places, 225 us
-// with 700) -- unless the columns' last chunks are shorter by up to half and
-// every XCD has its share of them (blocks): then two of those take the time of
-// one of the others (192^3 van Leer in eight blocks: 361 us with 432 equal
-// work-groups on 512 places, 352 us with 576).
+// with 700) -- unless each XCD has a block of its own, whose columns' shorter
+// last chunks come last and two deep beside the others (192^3 van Leer in
+// eight blocks: a step 332 us with 432 equal work-groups on 512 places, 310 us
+// with 576 in chunks of 28 and 12).
 int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n) {
     if (ndim == 1) return 1;
     int most = 1;
@@ -2507,9 +2573,9 @@ int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n) {
         for (int i = 0; i < n; ++i) wgs += m[i].cols * ((m[i].n2 + kz - 1) / kz);
         const long long full = wgs / slots, rest = wgs % slots;
         double t = (kz + lead) * (full * plane(slots) + (rest ? plane(rest) : 0.0));
-        if (n == 1 && m[0].even && full == 1 && rest > 0 && rest <= m[0].cols) {
+        if (n == 1 && m[0].per_xcd && full == 1 && rest > 0 && 2 * slots + m[0].cols >= 2 * wgs) {
             const int last = m[0].n2 - (m[0].n2 - 1) / kz * kz;
-            if (2.0 * (last + lead) >= kz + lead) t = std::fmin(t, plane(slots) * 2.0 * (last + lead));
+            t = std::fmin(t, plane(slots) * std::fmax(kz + lead, 2.0 * (last + lead)));
         }
         if (kz == most || t <= least) {
             least = t;
@@ -2568,13 +2634,13 @@ hipError_t launch_ctrl_batch(const MeshDesc* d, int n, hipStream_t s) {
 }
 
 hipError_t launch_dt_levels(const Geo& g0, const LevelStarts& starts, int nblk, const double* U, Ctrl* ctrl,
-                            int in_step, hipStream_t s) {
+                            hipStream_t s) {
     if (nblk < 1) return hipSuccess;
     const dim3 grid(grid_for(g0.ncells, 256, (2048 + nblk - 1) / nblk), nblk);
     switch (g0.ndim) {
-        case 1: hipLaunchKernelGGL(dt_kernel<1>, grid, dim3(256), 0, s, g0, starts, U, ctrl, in_step); break;
-        case 2: hipLaunchKernelGGL(dt_kernel<2>, grid, dim3(256), 0, s, g0, starts, U, ctrl, in_step); break;
-        case 3: hipLaunchKernelGGL(dt_kernel<3>, grid, dim3(256), 0, s, g0, starts, U, ctrl, in_step); break;
+        case 1: hipLaunchKernelGGL(dt_kernel<1>, grid, dim3(256), 0, s, g0, starts, U, ctrl); break;
+        case 2: hipLaunchKernelGGL(dt_kernel<2>, grid, dim3(256), 0, s, g0, starts, U, ctrl); break;
+        case 3: hipLaunchKernelGGL(dt_kernel<3>, grid, dim3(256), 0, s, g0, starts, U, ctrl); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -2672,15 +2738,15 @@ hipError_t launch_padded_prim(const Geo& g, int precision, const double* U, doub
     return hipGetLastError();
 }
 
-hipError_t launch_smr_restrict(const Geo& g, const double* U, const int* side, double* gbuf, long long gcs,
-                               const GhostTask* tasks, int n, Ctrl* ctrl, hipStream_t s) {
+hipError_t launch_smr_restrict(const Geo& g, const double* U, double* gbuf, long long gcs, const GhostTask* tasks,
+                               int n, Ctrl* ctrl, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     // one thread per ghost of the largest slot (gcs = its two layers)
     const dim3 grid(n, (unsigned)((gcs + 63) / 64));
     switch (g.ndim) {
-        case 1: hipLaunchKernelGGL(smr_restrict_kernel<1>, grid, dim3(64), 0, s, g, U, side, gbuf, gcs, tasks, ctrl); break;
-        case 2: hipLaunchKernelGGL(smr_restrict_kernel<2>, grid, dim3(64), 0, s, g, U, side, gbuf, gcs, tasks, ctrl); break;
-        case 3: hipLaunchKernelGGL(smr_restrict_kernel<3>, grid, dim3(64), 0, s, g, U, side, gbuf, gcs, tasks, ctrl); break;
+        case 1: hipLaunchKernelGGL(smr_restrict_kernel<1>, grid, dim3(64), 0, s, g, U, gbuf, gcs, tasks, ctrl); break;
+        case 2: hipLaunchKernelGGL(smr_restrict_kernel<2>, grid, dim3(64), 0, s, g, U, gbuf, gcs, tasks, ctrl); break;
+        case 3: hipLaunchKernelGGL(smr_restrict_kernel<3>, grid, dim3(64), 0, s, g, U, gbuf, gcs, tasks, ctrl); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -2689,7 +2755,9 @@ hipError_t launch_smr_restrict(const Geo& g, const double* U, const int* side, d
 hipError_t launch_smr_prolong(const Geo& g, const double* U, const int* side, double* gbuf, long long gcs,
                               const GhostTask* tasks, int n, Ctrl* ctrl, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const dim3 grid(n, (unsigned)((gcs + 63) / 64));
+    // one thread per coarse cell across the largest side
+    const long long cells = (gcs / 2) >> (g.ndim - 1);
+    const dim3 grid(n, (unsigned)((cells + 63) / 64));
     switch (g.ndim) {
         case 1: hipLaunchKernelGGL(smr_prolong_kernel<1>, grid, dim3(64), 0, s, g, U, side, gbuf, gcs, tasks, ctrl); break;
         case 2: hipLaunchKernelGGL(smr_prolong_kernel<2>, grid, dim3(64), 0, s, g, U, side, gbuf, gcs, tasks, ctrl); break;
@@ -2699,16 +2767,17 @@ hipError_t launch_smr_prolong(const Geo& g, const double* U, const int* side, do
     return hipGetLastError();
 }
 
-hipError_t launch_smr_reflux(int precision, int first, const Geo& g0, const Geo& g1, const double* in,
-                             double* dbuf, double factor, int use_device_dt, double dt_host, const int* side,
-                             const double* gbuf, long long gcs, const GhostTask* tasks, int n, Ctrl* ctrl,
-                             hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const dim3 grid(n, (unsigned)((gcs / 2 + 63) / 64));  // one thread per face of the largest side
-#define RF(ND, RT, FO)                                                                                          \
-    hipLaunchKernelGGL((smr_reflux_kernel<ND, RT, FO>), grid, dim3(64), 0, s, g0, g1, in, dbuf, factor, \
-                       use_device_dt, dt_host, side, gbuf, gcs, tasks, ctrl)
-    switch ((g0.ndim * 2 + (precision == 0 ? 0 : 1)) * 2 + (first ? 1 : 0)) {
+hipError_t launch_smr_correct(int precision, int first, const Geo& g, const double* in, double* out, double factor,
+                              int use_device_dt, double dt_host, const int* side, const double* gbuf, long long gcs,
+                              const GhostTask* tasks, int nres, int want_dt, Ctrl* ctrl, hipStream_t s) {
+    if (nres <= 0) return hipSuccess;
+    // one thread per fine face across the largest side
+    const long long faces = (gcs / 2) << (g.ndim - 1);
+    const dim3 grid(nres, (unsigned)((faces + 63) / 64));
+#define RF(ND, RT, FO)                                                                                        \
+    hipLaunchKernelGGL((smr_correct_kernel<ND, RT, FO>), grid, dim3(64), 0, s, g, in, out, factor, use_device_dt, \
+                       dt_host, side, gbuf, gcs, tasks, nres, want_dt, ctrl)
+    switch ((g.ndim * 2 + (precision == 0 ? 0 : 1)) * 2 + (first ? 1 : 0)) {
         case 4: RF(1, double, false); break;
         case 5: RF(1, double, true); break;
         case 6: RF(1, float, false); break;
@@ -2724,22 +2793,6 @@ hipError_t launch_smr_reflux(int precision, int first, const Geo& g0, const Geo&
         default: return hipErrorInvalidValue;
     }
 #undef RF
-    return hipGetLastError();
-}
-
-hipError_t launch_smr_apply(const Geo& g0, double* out, const double* dbuf, long long gcs, const GhostTask* tasks,
-                            int idx0, int n, int use_device_dt, Ctrl* ctrl, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const dim3 grid(n, (unsigned)((gcs / 2 + 63) / 64));
-#define AP(ND) hipLaunchKernelGGL((smr_apply_kernel<ND>), grid, dim3(64), 0, s, g0, out, dbuf, gcs, tasks, idx0, \
-                                  use_device_dt, ctrl)
-    switch (g0.ndim) {
-        case 1: AP(1); break;
-        case 2: AP(2); break;
-        case 3: AP(3); break;
-        default: return hipErrorInvalidValue;
-    }
-#undef AP
     return hipGetLastError();
 }
 

@@ -44,9 +44,6 @@ struct hydro_ctx {
     int nres, npro, res_off[4];
     int pro_off[kMaxLevels + 1];   // prolongation slots of level L: tasks [pro_off[L], pro_off[L + 1])
     double* gbuf;
-    double* dbuf;                  // flux corrections per restriction slot
-    hipStream_t smr_aux;           // second stream of the level-jump passes (null: none)
-    hipEvent_t ev_smr[3];          // restriction done, prolongation done, recomputation done
     long long gcs;
     int32_t* leaves;               // host: (level, c0, c1, c2) per leaf
     Tile tile[2];  // stage 1 (and the rhs), stage 2
@@ -137,7 +134,7 @@ int stage2_mode(const hydro_config* c) { return c->integrator == HYDRO_VL2 ? MOD
 // since the level-jump passes read conserved stage inputs.
 int smr_mode(const hydro_config* c, int st) {
     if (c->integrator == HYDRO_VL2) return st == 0 ? MODE_VL2_PRED_C : MODE_VL2_CORR_C;
-    return st == 0 ? MODE_STAGE1 : MODE_STAGE2;
+    return st == 0 ? MODE_STAGE1 : MODE_STAGE2_R;
 }
 
 // Kernel-axis geometry of one block (see hydro_internal.h).
@@ -197,6 +194,13 @@ int usable(hydro_t h) {
     return HYDRO_OK;
 }
 
+// The first leaf of each level 1 .. kMaxLevels - 1 of a refined mesh.
+LevelStarts level_starts(hydro_t h) {
+    LevelStarts ls;
+    for (int L = 1; L < kMaxLevels; ++L) ls.s[L - 1] = L < h->nlev ? h->lev_start[L] : h->nblk;
+    return ls;
+}
+
 // Arguments of a launch over every block of the mesh.
 StageArgs stage_args(hydro_t h) {
     StageArgs a;
@@ -209,6 +213,8 @@ StageArgs stage_args(hydro_t h) {
     a.side = h->smr ? h->d_side : nullptr;
     a.gbuf = h->gbuf;
     a.gcs = h->gcs;
+    a.starts = level_starts(h);
+    a.nres = h->nres;
     return a;
 }
 
@@ -443,7 +449,7 @@ hipError_t free_tmp(hydro_t h, double* d, hipError_t e) {
 
 // Launch one stage, bracketed by events when profiling is on.
 hipError_t timed_stage(hydro_t h, int mode, const StageArgs& a) {
-    const int st = (mode == MODE_STAGE2 || mode == MODE_VL2_CORR || mode == MODE_VL2_CORR_C) ? 1 : 0;
+    const int st = (mode == MODE_STAGE2 || mode == MODE_STAGE2_R || mode == MODE_VL2_CORR || mode == MODE_VL2_CORR_C) ? 1 : 0;
     const bool rec = h->prof_cap > 0 && h->prof_n[st] < h->prof_cap;
     hipError_t e = hipSuccess;
     if (rec) e = hipEventRecord(h->prof_ev[st][2 * h->prof_n[st]], h->stream);
@@ -458,14 +464,13 @@ hipError_t timed_stage(hydro_t h, int mode, const StageArgs& a) {
 // One step: stage 1 (Heun: U1 = U^n + dt L(U^n); van Leer: the predicted
 // primitive state) then stage 2 in place over U^n, dt either from the host or
 // from the device control block (clamped to the run limit kept there).
-// Whether the handle's stream is being captured into a graph.  The forms
-// that fork work onto other streams and join it back by events are then not
-// captured as such: capturing that form (group streams waiting on each
-// other's events) crashed the host process in the HIP runtime at the end of
-// the capture.  The block-stream step is captured as explicit graph nodes
-// with the same dependencies instead (enqueue_step_streams_graph), and a
-// refined mesh's second stream runs on the handle's stream.  The results do
-// not depend on the form.
+// Whether the handle's stream is being captured into a graph.  The form that
+// forks work onto other streams and joins it back by events is then not
+// captured as such: capturing it (group streams waiting on each other's
+// events) crashed the host process in the HIP runtime at the end of the
+// capture.  The block-stream step is captured as explicit graph nodes with the
+// same dependencies instead (enqueue_step_streams_graph).  The results do not
+// depend on the form.
 // A handle that was captured once may be changed by replays that the host
 // does not see: from then on rate_pending and no_limits are not relied on.
 bool capturing(hydro_t h) {
@@ -475,76 +480,47 @@ bool capturing(hydro_t h) {
     return on;
 }
 
-// The first leaf of each level 1 .. kMaxLevels - 1 of a refined mesh.
-LevelStarts level_starts(hydro_t h) {
-    LevelStarts ls;
-    for (int L = 1; L < kMaxLevels; ++L) ls.s[L - 1] = L < h->nlev ? h->lev_start[L] : h->nblk;
-    return ls;
-}
-
 // One step of a refined mesh (Heun, or van Leer with its predicted state
 // conserved in U1).  Each stage: the ghost slots of the level jumps from the
 // stage input (restriction, then prolongation level by level from the
 // coarsest, since a coarse block's stencil may include its own prolonged
-// slots), the stage kernel per level, then the flux correction of the coarse
-// cells at the level jumps (computed for every jump in one launch, added axis
-// by axis: a cell next to two jumps is corrected once per axis, in order).
-// The correction's weight: Heun 1 after stage 1 and 1/2 after stage 2 (the
-// stage-2 update averages with U^n); van Leer 1/2 after the predictor (half
-// a step, fluxes of piecewise-constant states) and 1 after the corrector.
-// The CFL rate of the corrected state is a reduction of its own.
+// slots), the stage kernel over every leaf in one launch, then the flux
+// correction of the coarse cells at the level jumps (a cell next to jumps on
+// several axes is corrected in axis order).  The correction's weight: Heun 1
+// after stage 1 and 1/2 after stage 2 (the stage-2 update averages with U^n);
+// van Leer 1/2 after the predictor (half a step, fluxes of piecewise-constant
+// states) and 1 after the corrector.  The second stage takes the CFL rate of
+// the cells it leaves final, the correction that of the others.
+// One launch over the leaves of both levels of 128^3 with the central 2x2x2
+// blocks refined takes 91 and 122 us for the two stages where one per level
+// took 59 + 59 and 72 + 72.
 hipError_t enqueue_step_smr(hydro_t h, bool device_dt, double dt) {
     hipError_t e = hipSuccess;
-    // With a second stream (smr_aux), the passes that the level-0 stage does
-    // not need overlap it: the prolongations (read only by the finer levels)
-    // and the flux recomputation (reads the stage input and the slots, not
-    // the stage's output); the finer levels wait for the prolongations, the
-    // additions for the recomputation.
-    const bool fork = h->smr_aux && !capturing(h);
-    hipStream_t aux = fork ? h->smr_aux : h->stream;
     const bool vl2 = h->cfg.integrator == HYDRO_VL2;
     for (int st = 0; st < 2 && e == hipSuccess; ++st) {
         const int first = vl2 && st == 0 ? 1 : 0;
         const double factor = vl2 ? (st == 0 ? 0.5 : 1.0) : (st == 0 ? 1.0 : 0.5);
         const double* in = st == 0 ? h->U : h->U1;
         double* out = st == 0 ? h->U1 : h->U;
-        e = launch_smr_restrict(h->lgeo[0], in, h->d_side, h->gbuf, h->gcs, h->d_tasks, h->nres, h->ctrl, h->stream);
-        if (e == hipSuccess && fork) e = hipEventRecord(h->ev_smr[0], h->stream);
-        if (e == hipSuccess && fork) e = hipStreamWaitEvent(aux, h->ev_smr[0], 0);
+        e = launch_smr_restrict(h->lgeo[0], in, h->gbuf, h->gcs, h->d_tasks, h->nres, h->ctrl, h->stream);
         for (int L = 1; L < h->nlev && e == hipSuccess; ++L)
             e = launch_smr_prolong(h->lgeo[0], in, h->d_side, h->gbuf, h->gcs, h->d_tasks + h->pro_off[L],
-                                   h->pro_off[L + 1] - h->pro_off[L], h->ctrl, aux);
-        if (e == hipSuccess && fork) e = hipEventRecord(h->ev_smr[1], aux);
+                                   h->pro_off[L + 1] - h->pro_off[L], h->ctrl, h->stream);
+        if (e != hipSuccess) break;
+        StageArgs a = stage_args(h);
+        a.use_device_dt = device_dt ? 1 : 0;
+        a.dt_host = dt;
+        a.in = in;
+        a.base = h->U;
+        a.out = out;
+        a.want_dt = st;
+        a.chain = 1;
+        e = timed_stage(h, smr_mode(&h->cfg, st), a);
         if (e == hipSuccess)
-            e = launch_smr_reflux(h->cfg.precision, first, h->lgeo[0], h->lgeo[0], in, h->dbuf, factor,
-                                  device_dt ? 1 : 0, dt, h->d_side, h->gbuf, h->gcs, h->d_tasks, h->nres, h->ctrl,
-                                  aux);
-        if (e == hipSuccess && fork) e = hipEventRecord(h->ev_smr[2], aux);
-        for (int lev = 0; lev < h->nlev && e == hipSuccess; ++lev) {
-            if (lev == 1 && fork) e = hipStreamWaitEvent(h->stream, h->ev_smr[1], 0);
-            if (e != hipSuccess || h->lev_count[lev] == 0) continue;
-            StageArgs a = stage_args(h);
-            a.geo = h->lgeo[lev];
-            a.blk0 = h->lev_start[lev];
-            a.nblk = a.conc = h->lev_count[lev];
-            a.use_device_dt = device_dt ? 1 : 0;
-            a.dt_host = dt;
-            a.in = in;
-            a.base = h->U;
-            a.out = out;
-            a.want_dt = 0;
-            e = timed_stage(h, smr_mode(&h->cfg, st), a);
-        }
-        if (e == hipSuccess && fork) e = hipStreamWaitEvent(h->stream, h->ev_smr[2], 0);
-        for (int ax = 0; ax < 3 && e == hipSuccess; ++ax)
-            e = launch_smr_apply(h->lgeo[0], out, h->dbuf, h->gcs, h->d_tasks + h->res_off[ax], h->res_off[ax],
-                                 h->res_off[ax + 1] - h->res_off[ax], device_dt ? 1 : 0, h->ctrl, h->stream);
+            e = launch_smr_correct(h->cfg.precision, first, h->lgeo[0], in, out, factor, device_dt ? 1 : 0, dt,
+                                   h->d_side, h->gbuf, h->gcs, h->d_tasks, h->nres, st, h->ctrl, h->stream);
     }
-    if (e != hipSuccess) return e;
-    if (!device_dt) return launch_ctrl(h->ctrl, CTRL_ADVANCE_T, dt, 0.0, h->cfg.cfl, h->stream);
-    e = launch_dt_levels(h->lgeo[0], level_starts(h), h->nblk, h->U, h->ctrl, 1, h->stream);
-    if (e != hipSuccess) return e;
-    return launch_ctrl(h->ctrl, CTRL_FINALIZE_STEP, 0.0, 0.0, h->cfg.cfl, h->stream);
+    return e;
 }
 
 hipError_t enqueue_step(hydro_t h, bool device_dt, double dt) {
@@ -570,8 +546,8 @@ hipError_t enqueue_step(hydro_t h, bool device_dt, double dt) {
 }
 
 // Whether enqueue_step keeps the step's books itself: every step but that of
-// a refined mesh and that of a split mesh on streams of its own.
-bool step_chains(hydro_t h) { return !h->smr && !(h->block_streams && h->nblk > 1 && h->nbs > 0); }
+// a split mesh on streams of its own.
+bool step_chains(hydro_t h) { return !(h->block_streams && h->nblk > 1 && h->nbs > 0); }
 
 // Whether hydro_step_auto's steps run in one launch (see launch_run_1d_fp64);
 // under stage timing the stages are launched.
@@ -592,7 +568,7 @@ hipError_t enqueue_finalize(hydro_t h) {
 // The CFL rate of the current state pending in the control block.
 hipError_t enqueue_rate(hydro_t h) {
     if (h->rate_pending && !h->captured) return hipSuccess;
-    const hipError_t e = launch_dt_levels(h->smr ? h->lgeo[0] : h->geo, level_starts(h), h->nblk, h->U, h->ctrl, 0,
+    const hipError_t e = launch_dt_levels(h->smr ? h->lgeo[0] : h->geo, level_starts(h), h->nblk, h->U, h->ctrl,
                                           h->stream);
     if (e == hipSuccess) h->rate_pending = true;
     return e;
@@ -873,8 +849,7 @@ size_t smr_bytes(const hydro_config* c, const SmrPlan& P) {
     const size_t field = align_up(nc * cells * (size_t)P.nleaf * sizeof(double));
     return 2 * field + align_up(kCtrlBytes) + align_up((size_t)kTotalsParts * kMaxComp * 2 * sizeof(double)) +
            align_up(P.side.size() * sizeof(int)) + align_up(P.tasks.size() * sizeof(GhostTask)) +
-           align_up(P.tasks.size() * nc * (size_t)P.gcs * sizeof(double)) +
-           align_up((size_t)P.nres * nc * (size_t)(P.gcs / 2) * sizeof(double));
+           align_up(P.tasks.size() * nc * (size_t)P.gcs * sizeof(double));
 }
 
 }  // namespace
@@ -999,8 +974,6 @@ int hydro_smr_create(const hydro_config* cfg, int nref, const int32_t* refined, 
     h->d_tasks = (GhostTask*)p;
     p += align_up(P.tasks.size() * sizeof(GhostTask));
     h->gbuf = (double*)p;
-    p += align_up(P.tasks.size() * nc * (size_t)P.gcs * sizeof(double));
-    h->dbuf = (double*)p;
     h->host_ctrl = new (std::nothrow) Ctrl;
     if (!h->host_ctrl) {
         delete[] h->leaves;
@@ -1015,24 +988,6 @@ int hydro_smr_create(const hydro_config* cfg, int nref, const int32_t* refined, 
                            h->stream);
     if (e == hipSuccess) e = launch_ctrl(h->ctrl, CTRL_INIT, 0.0, 0.0, cfg->cfl, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // the plan's host vectors end here
-    if (e == hipSuccess && P.tasks.size() > 0) {
-        // default priority, not synchronising with the legacy default stream
-        hipStream_t aux = nullptr;
-        e = hipStreamCreateWithFlags(&aux, hipStreamNonBlocking);
-        if (e == hipSuccess) {
-            int made = 0;
-            for (; made < 3; ++made) {
-                e = hipEventCreateWithFlags(&h->ev_smr[made], hipEventDisableTiming);
-                if (e != hipSuccess) break;
-            }
-            if (e == hipSuccess) {
-                h->smr_aux = aux;
-            } else {
-                for (int i = 0; i < made; ++i) (void)hipEventDestroy(h->ev_smr[i]);
-                (void)hipStreamDestroy(aux);
-            }
-        }
-    }
     if (e != hipSuccess) {
         delete h->host_ctrl;
         delete[] h->leaves;
@@ -1562,10 +1517,6 @@ int hydro_destroy(hydro_t h) {
     if (!h->broken) (void)hipStreamSynchronize(h->stream);
     block_streams_free(h);
     profile_free(h);
-    if (h->smr_aux) {
-        for (int i = 0; i < 3; ++i) (void)hipEventDestroy(h->ev_smr[i]);
-        (void)hipStreamDestroy(h->smr_aux);
-    }
     delete[] h->leaves;
     delete h->host_ctrl;
     delete h;
