@@ -231,7 +231,8 @@ int hydro_padded_primitive(hydro_t h, double* Wpad_host);
  * march from the mesh and the work-groups the device holds at once (in a
  * batch, one length per launch group from all its members' meshes). The
  * two stages have a tile each (the stage right-hand side uses stage 1's;
- * a batch uses each member's stage-1 tile for both stages).  Every face flux
+ * a batch uses each member's stage-1 tile for both stages, or one of them for
+ * several members that have the defaults).  Every face flux
  * is the same function of the same inputs for any tile, so the results are
  * bitwise independent of the tiles; only speed changes.  hydro_create picks
  * defaults.  Unsupported shapes or a stage other than 0 (both), 1 or 2 return

@@ -203,7 +203,9 @@ struct MarchCols {
     int n2;
     bool per_xcd;  // the launch covers eight blocks of a split mesh: one to each XCD
 };
-int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n);
+// *time (if given): the launch's modelled time, in planes of a work-group that
+// has a CU to itself.
+int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n, double* time = nullptr);
 int balanced_kz(int n2, int kz);
 Slots stage_residency(int ndim, int precision, int mode, const Tile& t);
 

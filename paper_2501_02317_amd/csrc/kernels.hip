@@ -814,7 +814,9 @@ struct StageOccupancy {
     // The FP64 stage 2 holds three (twelve waves on a CU) without the double
     // buffers of W and the fluxes that one barrier per plane takes: 653 us at
     // 256^3 against 689 us in eight waves with one barrier.
-    static constexpr int kWaves = sizeof(R) == 4 ? 4 : (NDIM == 3 ? 3 : 2);
+    // In 2-D the FP64 stages hold four with a few spilled registers (4096 x
+    // 1024: a step 200 -> 187 us, 1024^2 72 -> 66 us against three waves).
+    static constexpr int kWaves = sizeof(R) == 4 || NDIM == 2 ? 4 : (NDIM == 3 ? 3 : 2);
     static constexpr int kWavesMax = 8;
     // The raw halo cell of the next plane loaded one iteration ahead, so the
     // barrier after the plane's W does not wait for it: ten more registers.
@@ -2554,7 +2556,8 @@ int balanced_kz(int n2, int kz) {
 // last chunks come last and two deep beside the others (192^3 van Leer in
 // eight blocks: a step 332 us with 432 equal work-groups on 512 places, 310 us
 // with 576 in chunks of 28 and 12).
-int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n) {
+int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n, double* time) {
+    if (time) *time = 0.0;
     if (ndim == 1) return 1;
     int most = 1;
     for (int i = 0; i < n; ++i) most = m[i].n2 > most ? m[i].n2 : most;
@@ -2582,6 +2585,7 @@ int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n) {
             best = kz;
         }
     }
+    if (time) *time = least;
     return best;
 }
 

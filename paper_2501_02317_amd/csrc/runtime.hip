@@ -47,6 +47,7 @@ struct hydro_ctx {
     long long gcs;
     int32_t* leaves;               // host: (level, c0, c1, c2) per leaf
     Tile tile[2];  // stage 1 (and the rhs), stage 2
+    bool tile_set;  // by the caller or an autotuner (else the defaults)
     hipStream_t stream;
     int ncomp;
     double dV;
@@ -1323,6 +1324,7 @@ int hydro_set_stage_tile(hydro_t h, int stage, int tx, int ty, int kz) {
     if (!tile_supported(h->cfg.ndim, t)) return HYDRO_E_INVAL;
     if (stage != 2) h->tile[0] = t;
     if (stage != 1) h->tile[1] = t;
+    h->tile_set = true;
     return HYDRO_OK;
 }
 
@@ -1411,6 +1413,7 @@ int hydro_autotune(hydro_t h, int steps_per_tile, double t_end, int* tiles, doub
             if (best < 0 || ms[2 * c + st] < ms[2 * best + st]) best = c;
         if (keep_c >= 0 && !(ms[2 * best + st] < 0.95 * ms[2 * keep_c + st])) best = keep_c;
         h->tile[st] = cand[best];
+        h->tile_set = true;
         tiles[3 * st] = cand[best].tx;
         tiles[3 * st + 1] = cand[best].ty;
         tiles[3 * st + 2] = cand[best].kz;
@@ -1616,17 +1619,89 @@ Tile rule_tile(const hydro_t h, int rule) {
     return t;
 }
 
+// The columns of members idx[0 .. n) in tile t, and the automatic chunk length
+// and modelled time of a launch over them (a launch of its own counts two
+// planes; a tile's halo and extra faces as in default_tile).
+int batch_kz(const std::vector<int>& idx, const hydro_t* members, const Tile& t, double* time = nullptr) {
+    std::vector<MarchCols> cols;
+    for (int i : idx) {
+        const Geo& g = members[i]->geo;
+        int tx, ty, cz, kz;
+        plan_tiles(g, t, tx, ty, cz, kz);
+        cols.push_back({(long long)tx * ty, g.n[2], false});
+    }
+    const hydro_t h = members[idx[0]];
+    const Slots sl = stage_residency(h->cfg.ndim, h->cfg.precision, stage2_mode(&h->cfg), t);
+    const int kz = auto_kz(h->cfg.ndim, sl, cols.data(), (int)cols.size(), time);
+    if (time) {
+        const double wide = h->cfg.ndim == 3 ? (t.tx * t.ty > 256 ? 1.0 : 1.08) : 1.0 + 24.0 / t.tx;
+        *time = 2.0 + *time * wide;
+    }
+    return kz;
+}
+
+// One tile for the members (of one ndim, precision and integrator) that have
+// the default ones, where their launches' modelled times add up to more than
+// that of one launch with it: a group's last work-groups leave the chip idle,
+// and a stage of 16-30 us is a good part launch (48 ragged 2-D meshes alone:
+// 7.27 ms in three groups, 5.95 ms in one of width 128, 6.08 of 64).
+void share_tile(const std::vector<int>& idx, const hydro_t* members, std::vector<Tile>& tiles) {
+    if (idx.empty()) return;
+    const hydro_t h0 = members[idx[0]];
+    if (h0->cfg.ndim == 1) return;
+    std::vector<Tile> kinds;
+    std::vector<std::vector<int>> of;
+    for (int i : idx) {
+        size_t k = 0;
+        while (k < kinds.size() && (kinds[k].tx != tiles[i].tx || kinds[k].ty != tiles[i].ty)) ++k;
+        if (k == kinds.size()) {
+            kinds.push_back(tiles[i]);
+            of.push_back({});
+        }
+        of[k].push_back(i);
+    }
+    if (kinds.size() < 2) return;
+    double own = 0.0;
+    for (size_t k = 0; k < kinds.size(); ++k) {
+        double t = 0.0;
+        batch_kz(of[k], members, kinds[k], &t);
+        own += t;
+    }
+    int best = -1;
+    for (size_t k = 0; k < kinds.size(); ++k) {
+        double t = 0.0;
+        batch_kz(idx, members, kinds[k], &t);
+        if (t < own) {
+            own = t;
+            best = (int)k;
+        }
+    }
+    if (best >= 0)
+        for (int i : idx) tiles[i] = kinds[best];
+}
+
 // Members grouped by (ndim, precision, tile): each group's descriptors and
 // work-groups are contiguous in their tables, members in the caller's order
 // within a group (P.order maps a descriptor to its member).  Member i runs
-// tile rule_tile(members[i], rule).
+// tile rule_tile(members[i], rule); with rule 0, members of the default tiles
+// may share one (share_tile).
 bool plan_batch(int n, const hydro_t* members, BatchPlan& P, int rule = 0) {
     std::vector<MeshDesc> desc(n);
     std::vector<int> order(n);
     std::vector<Tile> tiles(n);
+    for (int i = 0; i < n; ++i) tiles[i] = rule_tile(members[i], rule);
+    if (rule == 0)
+        for (int c = 0; c < 16; ++c) {
+            std::vector<int> same;
+            for (int i = 0; i < n; ++i) {
+                const hydro_config& f = members[i]->cfg;
+                if (!members[i]->tile_set && c == 4 * f.ndim + 2 * (f.precision == HYDRO_MIXED) + (f.integrator == HYDRO_VL2))
+                    same.push_back(i);
+            }
+            share_tile(same, members, tiles);
+        }
     for (int i = 0; i < n; ++i) {
         const hydro_t h = members[i];
-        tiles[i] = rule_tile(h, rule);
         MeshDesc& d = desc[i];
         d.U = h->U;
         d.U1 = h->U1;
@@ -1641,20 +1716,14 @@ bool plan_batch(int n, const hydro_t* members, BatchPlan& P, int rule = 0) {
     };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key(a) < key(b); });
     // automatic chunk lengths: one per group, for the columns of all its members
-    std::vector<MarchCols> cols;
     for (int i0 = 0, i1 = 0; i0 < n; i0 = i1) {
-        cols.clear();
-        for (i1 = i0; i1 < n && key(order[i1]) == key(order[i0]); ++i1) {
-            const MeshDesc& d = desc[order[i1]];
-            if (tiles[order[i1]].kz == 0) cols.push_back({(long long)d.tiles_x * d.tiles_y, d.geo.n[2], false});
-        }
-        if (cols.empty()) continue;
-        const hydro_t h = members[order[i0]];
-        const int kz = auto_kz(h->cfg.ndim, stage_residency(h->cfg.ndim, h->cfg.precision, stage2_mode(&h->cfg),
-                                                            tiles[order[i0]]), cols.data(), (int)cols.size());
-        for (int k = i0; k < i1; ++k) {
-            MeshDesc& d = desc[order[k]];
-            if (tiles[order[k]].kz != 0) continue;
+        std::vector<int> aut;
+        for (i1 = i0; i1 < n && key(order[i1]) == key(order[i0]); ++i1)
+            if (tiles[order[i1]].kz == 0) aut.push_back(order[i1]);
+        if (aut.empty()) continue;
+        const int kz = batch_kz(aut, members, tiles[aut[0]]);
+        for (int i : aut) {
+            MeshDesc& d = desc[i];
             d.kz = balanced_kz(d.geo.n[2], kz);
             d.chunks_z = (d.geo.n[2] + d.kz - 1) / d.kz;
         }
@@ -2005,7 +2074,10 @@ int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule_out, dou
             if (ms[r] < ms[best]) best = r;
         if (!(ms[best] < 0.95 * ms[0])) best = 0;
         for (hydro_t h : b->members)
-            if (h->cfg.ndim < 3) h->tile[0] = h->tile[1] = rule_tile(h, best);
+            if (h->cfg.ndim < 3 && best > 0) {
+                h->tile[0] = h->tile[1] = rule_tile(h, best);
+                h->tile_set = true;
+            }
         BatchPlan P;
         if (!plan_batch(n, b->members.data(), P, 0)) e = hipErrorInvalidValue;
         if (e == hipSuccess) e = upload(P);
