@@ -788,10 +788,6 @@ __device__ __forceinline__ void load_as_double(const T* __restrict__ F, long lon
 // the plane (4 TX + 4 TY <= TX TY).
 // Work-groups per CU the compiler is asked to fit: the FP32 path keeps four
 // 256-thread groups per CU (16 waves); FP64 needs more registers per thread.
-// The input ring pays in 3-D only: the 2-D kernels (one row of 64..256 cells)
-// already run many small work-groups per CU, and measured slower with it.
-constexpr bool kRing2D = false;
-
 template <int NDIM, typename R, int MODE>
 struct StageOccupancy {
     // Input ring: the raw input values of a cell, read for its conversion
@@ -802,13 +798,15 @@ struct StageOccupancy {
     // With three planes (and one prefetch more in stage 2) the mixed stages
     // held twelve waves on a CU; with two they hold sixteen in work-groups of
     // 32 x 16, whose halo and extra faces are a quarter less than those of
-    // 32 x 8: at 256^3 stage 1 357 -> 333 us, stage 2 463 -> 450 us.  The
-    // FP64 stages lose a wave per SIMD to it and do without.  The van Leer
-    // predictor looks one plane ahead only, so it needs one.
+    // 32 x 8: at 256^3 stage 1 357 -> 333 us, stage 2 463 -> 450 us.  In 2-D
+    // two rows leave the mixed stages their waves (4096 x 1024: a step 164 ->
+    // 141 us with the halo prefetch below).  The FP64 stages lose a wave per
+    // SIMD to it in 3-D and spill in 2-D (191 -> 198 us) and do without.  The
+    // van Leer predictor looks one plane ahead only, so it needs one.
     static constexpr bool kPred = MODE == MODE_VL2_PRED || MODE == MODE_VL2_PRED_C;
     static constexpr bool kHeun = MODE == MODE_STAGE1 || MODE == MODE_STAGE2 || MODE == MODE_STAGE2_R;
     static constexpr bool kRing =
-        (kPred || (sizeof(R) == 4 && kHeun)) && (NDIM == 3 || kRing2D);
+        kPred || (sizeof(R) == 4 && kHeun);
     // occupancy range (waves per SIMD) the compiler aims for: at least
     // kWaves (its register budget), at most kWavesMax (8: no bound)
     // The FP64 stage 2 holds three (twelve waves on a CU) without the double
@@ -821,10 +819,9 @@ struct StageOccupancy {
     // The raw halo cell of the next plane loaded one iteration ahead, so the
     // barrier after the plane's W does not wait for it: ten more registers.
     // Measured at 256^3: the mixed Heun stage 2 holds them (462 -> 452 us at
-    // four waves per SIMD), the mixed stage 1 gains about 2 %; the FP64 stages
-    // lose 5-6 % (a wave per SIMD) and do without.
-    static constexpr bool kHaloPrefetch =
-        NDIM == 3 && sizeof(R) == 4 && kHeun;
+    // four waves per SIMD), the mixed stage 1 and the mixed 2-D stages gain
+    // about 2 %; the FP64 stages lose 5-6 % (a wave per SIMD) and do without.
+    static constexpr bool kHaloPrefetch = NDIM >= 2 && sizeof(R) == 4 && kHeun;
     // The waves that convert the halo cells and compute the faces past the
     // tile's last row and column (the first waves of the work-group) run at
     // raised priority through that work, up to the barrier after the faces:
