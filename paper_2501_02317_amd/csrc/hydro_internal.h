@@ -247,8 +247,8 @@ hipError_t launch_stage_batch(int ndim, int precision, int mode, const Tile& til
 // nsteps device-dt steps of an unsplit 1-D mesh of at most kRun1dMost cells in
 // one work-group: the pending rate, if any, is used, and nothing is left
 // pending.  Two stage launches take 9.7-10.5 us a step at any such size; the
-// one work-group takes 2.9 us at 256 cells, 8.0 us at 1024 (FP64; mixed 2.4
-// and 5.7 us), and with two cells a thread would take 13 us at 2048.
+// one work-group takes 2.7 us at 256 cells, 7.4 us at 1024 (FP64; mixed 2.3
+// and 5.3 us), and with two cells a thread would take 13 us at 2048.
 constexpr int kRun1dMost = 1024;
 hipError_t launch_run_1d_fp64(int vl2, const Geo& g, double* U, Ctrl* ctrl, int nsteps, hipStream_t s);
 hipError_t launch_run_1d_mixed(int vl2, const Geo& g, double* U, Ctrl* ctrl, int nsteps, hipStream_t s);

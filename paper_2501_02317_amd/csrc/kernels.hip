@@ -622,23 +622,37 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
     return x * q + (x < r ? x : r) + i;
 }
 
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double o = __shfl_xor(v, off, 64);
-        v = o > v ? o : v;
-    }
-    return v;
+// A value that every lane holds, in scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | lo);
 }
 
-// Largest value of the set's slots (each lane has loaded one of them).
-__device__ __forceinline__ double slots_max(double v) {
-#pragma unroll
-    for (int off = kRateSlots / 2; off >= 1; off >>= 1) {
-        const double o = __shfl_xor(v, off, 64);
-        v = o > v ? o : v;
-    }
-    return v;
+// max(v, v of the lane that the DPP control names, 0 where there is none)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_max(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    const double o = __longlong_as_double(((long long)hi << 32) | lo);
+    return o > v ? o : v;
+}
+
+// Largest of the wave's non-negative values, in every lane; the whole wave
+// takes part.  Six lane moves in the VALU (rows of 16 by shifts, then their
+// last lanes broadcast on), about a tenth of the latency of six exchanges
+// through LDS, which a short step waits for.
+__device__ __forceinline__ double wave_max(double v) {
+    v = dpp_max<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8
+    v = dpp_max<0x112, 0xf>(v);
+    v = dpp_max<0x114, 0xf>(v);
+    v = dpp_max<0x118, 0xf>(v);
+    v = dpp_max<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_max<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | lo);
 }
 
 __device__ __forceinline__ double load_slot(Ctrl* c, unsigned int par) {
@@ -671,13 +685,6 @@ __device__ __forceinline__ StepCtl begin_step(const Ctrl* c, double cfl, double 
     n.par = pend != kPendNone ? c->par ^ 1u : c->par;
     n.dt = device_dt(&k);
     return n;
-}
-
-// A value that every lane holds, in scalar registers.
-__device__ __forceinline__ double uniform(double v) {
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | lo);
 }
 
 // ------------------------------------------------------------- stage kernel
@@ -950,7 +957,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     auto take_step = [&]() __attribute__((always_inline)) -> bool {
         double dt_step = a.dt_host;
         if (a.chain && !EPILOGUE) {
-            const StepCtl n = begin_step(a.ctrl, g.cfl, slots_max(a.ctrl->par ? slot1 : slot0));
+            const StepCtl n = begin_step(a.ctrl, g.cfl, wave_max(a.ctrl->par ? slot1 : slot0));
             if (leader) {
                 if (tid == 0) {
                     *ctrl_next(a.ctrl) = n;
@@ -1411,7 +1418,7 @@ void stage_kernel_batch(
 // thread computes both faces of its cell (the two Riemann solves overlap, and
 // no flux has to be exchanged), and the rate's reduction shares the barrier of
 // the next step's first stage, so a step has two barriers.  A step takes
-// 2.9 us at 256 cells and 8.0 us at 1024 in FP64 (2.4 and 5.7 us mixed).
+// 2.7 us at 256 cells and 7.4 us at 1024 in FP64 (2.3 and 5.3 us mixed).
 // Every face and update is the arithmetic of the stage kernels: the states are
 // theirs bit for bit.
 template <typename R, bool VL2>
@@ -1447,8 +1454,8 @@ __global__ __launch_bounds__(kRun1dMost) void run_1d_kernel(Geo g, double* __res
                 for (int c = 0; c < NC; ++c) sW[b][c][at] = c == 1 ? (R)apply_vmode((double)w[c], vmode[q]) : w[c];
             }
     };
-    // dt/dx times the cell's flux difference from the states in buffer b
-    auto divergence = [&](auto first, int b, double lam, double (&d)[NC]) {
+    // the cell's flux difference from the states in buffer b
+    auto difference = [&](auto first, int b, double (&d)[NC]) {
         constexpr bool FIRST = decltype(first)::value;
         R w[5][NC], fl[NC], fr[NC];
 #pragma unroll
@@ -1458,10 +1465,10 @@ __global__ __launch_bounds__(kRun1dMost) void run_1d_kernel(Geo g, double* __res
         face_flux<1, 0, R, FIRST>(gr, w[0], w[1], w[2], w[3], fl);
         face_flux<1, 0, R, FIRST>(gr, w[1], w[2], w[3], w[4], fr);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) d[c] = lam * ((double)fl[c] - (double)fr[c]);
+        for (int c = 0; c < NC; ++c) d[c] = (double)fl[c] - (double)fr[c];
     };
     Ctrl k = *ctrl;
-    double rate = slots_max(load_slot(ctrl, k.par));
+    double rate = wave_max(load_slot(ctrl, k.par));
     for (int s = 0;; ++s) {
         if (act) {
             R w[NC];
@@ -1469,6 +1476,10 @@ __global__ __launch_bounds__(kRun1dMost) void run_1d_kernel(Geo g, double* __res
             publish(0, w);
         }
         __syncthreads();
+        // the fluxes need no time step: ahead of the books of the last one, they
+        // overlap its divisions (after the last step they go unused)
+        double d[NC];
+        if (act) difference(std::integral_constant<bool, VL2>{}, 0, d);
         if (s > 0) {
             rate = sRate[0];
             for (int q = 1; q < waves; ++q) rate = sRate[q] > rate ? sRate[q] : rate;
@@ -1483,11 +1494,9 @@ __global__ __launch_bounds__(kRun1dMost) void run_1d_kernel(Geo g, double* __res
         const double dt = device_dt(&k);
         const double lam = (VL2 ? 0.5 * dt : dt) / g.dx[0], lam2 = dt / g.dx[0];
         if (act) {
-            double d[NC];
             R w[NC];
-            divergence(std::integral_constant<bool, VL2>{}, 0, lam, d);
 #pragma unroll
-            for (int c = 0; c < NC; ++c) u1[c] = u[c] + d[c];
+            for (int c = 0; c < NC; ++c) u1[c] = u[c] + lam * d[c];
             if (VL2) {
                 double wd[NC];
                 bad |= !cons_to_prim<1>(gm1, u1, wd);
@@ -1501,10 +1510,10 @@ __global__ __launch_bounds__(kRun1dMost) void run_1d_kernel(Geo g, double* __res
         __syncthreads();
         double best = 0.0;
         if (act) {
-            double d[NC], w[NC];
-            divergence(std::false_type{}, 1, lam2, d);
+            double w[NC];
+            difference(std::false_type{}, 1, d);
 #pragma unroll
-            for (int c = 0; c < NC; ++c) u[c] = VL2 ? u[c] + d[c] : 0.5 * u[c] + 0.5 * (u1[c] + d[c]);
+            for (int c = 0; c < NC; ++c) u[c] = VL2 ? u[c] + lam2 * d[c] : 0.5 * u[c] + 0.5 * (u1[c] + lam2 * d[c]);
             bad |= !cons_to_prim<1>(gm1, u, w);
             const double cr = cfl_rate<1>(g, w);
             best = cr > best ? cr : best;
@@ -1596,7 +1605,7 @@ __global__ __launch_bounds__(256) void dt_kernel(Geo g0, LevelStarts starts, con
 
 // Use the rate in the slots (pend: what for) and clear both sets; one wave.
 __device__ __forceinline__ void finalize_ctrl(Ctrl* c, unsigned int pend, double cfl) {
-    const double rate = slots_max(load_slot(c, c->par));
+    const double rate = wave_max(load_slot(c, c->par));
     *rate_slot(c, threadIdx.x / kRateSlots, threadIdx.x % kRateSlots) = 0ull;
     if (threadIdx.x != 0) return;
     if (pend == kPendStep) finalize_step(c, cfl, rate);
