@@ -641,8 +641,8 @@ __device__ __forceinline__ double dpp_max(double v) {
 
 // Largest of the wave's non-negative values, in every lane; the whole wave
 // takes part.  Six lane moves in the VALU (rows of 16 by shifts, then their
-// last lanes broadcast on), about a tenth of the latency of six exchanges
-// through LDS, which a short step waits for.
+// last lanes broadcast on) instead of six exchanges through LDS: a 1-D step of
+// 256 cells 2.87 -> 2.71 us, with its books beside the fluxes.
 __device__ __forceinline__ double wave_max(double v) {
     v = dpp_max<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8
     v = dpp_max<0x112, 0xf>(v);
@@ -826,9 +826,18 @@ struct StageOccupancy {
     // The raw halo cell of the next plane loaded one iteration ahead, so the
     // barrier after the plane's W does not wait for it: ten more registers.
     // Measured at 256^3: the mixed Heun stage 2 holds them (462 -> 452 us at
-    // four waves per SIMD), the mixed stage 1 and the mixed 2-D stages gain
-    // about 2 %; the FP64 stages lose 5-6 % (a wave per SIMD) and do without.
-    static constexpr bool kHaloPrefetch = NDIM >= 2 && sizeof(R) == 4 && kHeun;
+    // four waves per SIMD), the mixed stage 1, the mixed 2-D stages and the
+    // mixed van Leer predictor gain about 2 % (192^3 in blocks 128 -> 124 us);
+    // the FP64 stages lose 5-6 % (a wave per SIMD), the mixed van Leer
+    // corrector 17 % in 3-D (383 -> 447 us), and do without.
+    static constexpr bool kHaloPrefetch = NDIM >= 2 && sizeof(R) == 4 && (kHeun || kPred);
+    // U^n for the update loaded before the faces instead of after them, so it
+    // arrives beside them.  Measured: the mixed 2-D van Leer corrector 68 -> 63
+    // us at 4096 x 1024; the mixed 2-D Heun stage 2 is even there and loses 2 %
+    // in batches; in 3-D it costs registers (the van Leer step 663 -> 696 us,
+    // the mixed Heun one +2 %, FP64 +5 %, spilled).
+    static constexpr bool kBaseEarly =
+        NDIM == 2 && sizeof(R) == 4 && (MODE == MODE_VL2_CORR || MODE == MODE_VL2_CORR_C);
     // The waves that convert the halo cells and compute the faces past the
     // tile's last row and column (the first waves of the work-group) run at
     // raised priority through that work, up to the barrier after the faces:
@@ -1024,6 +1033,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     // the raw halo cell of this thread (HALO_PF: the next plane's, in flight)
     constexpr bool HALO_PF = StageOccupancy<NDIM, R, MODE>::kHaloPrefetch;
     constexpr bool PRIO = StageOccupancy<NDIM, R, MODE>::kPrio;
+    constexpr bool BASE_EARLY = StageOccupancy<NDIM, R, MODE>::kBaseEarly;
     double uhalo[NC];
 
     // interior plane z (any z: outside the mesh it is a ghost plane)
@@ -1199,6 +1209,12 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
         }
         __syncthreads();
 
+        const long long kP = boff + (long long)k * P;  // plane offset of the cell
+        const uint32_t colb = col32 * (uint32_t)sizeof(double);
+        if (NEED_BASE && BASE_EARLY && act) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) ubase[c] = plane_load<double, kNonTemporal>(a.base, c * N + kP, ext8, colb);
+        }
         // x faces: face i separates tile columns i-1 and i; LDS columns i..i+3
         if (ly < ay && lx <= ax) {
             R w0[NC], w1[NC], w2[NC], w3[NC], F[NC];
@@ -1270,13 +1286,11 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
         __syncthreads();
 
         if (act) {
-            const long long kP = boff + (long long)k * P;  // plane offset of the cell
-            const uint32_t colb = col32 * (uint32_t)sizeof(double);
             if (NEED_UIN && !RING) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c) uin[c] = plane_load(a.in, c * N + kP, ext8, colb);
             }
-            if (NEED_BASE) {
+            if (NEED_BASE && !BASE_EARLY) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c) ubase[c] = plane_load<double, kNonTemporal>(a.base, c * N + kP, ext8, colb);
             }
