@@ -1209,11 +1209,10 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
         }
         __syncthreads();
 
-        const long long kP = boff + (long long)k * P;  // plane offset of the cell
-        const uint32_t colb = col32 * (uint32_t)sizeof(double);
         if (NEED_BASE && BASE_EARLY && act) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) ubase[c] = plane_load<double, kNonTemporal>(a.base, c * N + kP, ext8, colb);
+            for (int c = 0; c < NC; ++c)
+                ubase[c] = plane_load<double, kNonTemporal>(a.base, c * N + boff + (long long)k * P, ext8, col32 * 8u);
         }
         // x faces: face i separates tile columns i-1 and i; LDS columns i..i+3
         if (ly < ay && lx <= ax) {
@@ -1286,6 +1285,8 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
         __syncthreads();
 
         if (act) {
+            const long long kP = boff + (long long)k * P;  // plane offset of the cell
+            const uint32_t colb = col32 * (uint32_t)sizeof(double);
             if (NEED_UIN && !RING) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c) uin[c] = plane_load(a.in, c * N + kP, ext8, colb);
