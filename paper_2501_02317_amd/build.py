@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libhydro.so")
 # (source, part): kernels.hip compiles in parts (its HYDRO_PART), so the parts
 # compile side by side
-UNITS = [("csrc/kernels.hip", p) for p in (6, 5, 4, 3, 2, 1, 0)] + [("csrc/runtime.hip", 0)]
+UNITS = [("csrc/kernels.hip", p) for p in (6, 5, 4, 3, 2, 1, 0)] + [("csrc/runtime.hip", 0), ("csrc/plan.cpp", 0)]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

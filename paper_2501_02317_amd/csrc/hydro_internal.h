@@ -6,6 +6,8 @@
 
 #include <cstdint>
 
+#include "plan.h"
+
 namespace hydro {
 
 constexpr int kMaxComp = 5;
@@ -69,35 +71,6 @@ enum CtrlOp : int {
     CTRL_FINALIZE_STEP = 2,  // the same for a step whose rate is in the slots unannounced
     CTRL_ADVANCE_T = 3,      // t += a0 (host dt), dt invalid
     CTRL_SET_LIMITS = 4,     // t_end = a0, max_steps = a1 (relative to the steps done), done
-};
-
-// Geometry in kernel axes.  Kernel axis 0 is x.  For 3-D, kernel axes
-// (0, 1, 2) are (x, y, z); for 2-D, kernel axis 2 (the marching axis)
-// is the physical y axis and kernel axis 1 has extent 1; for 1-D only
-// kernel axis 0 is active.  The cell index (k * n1 + j) * n0 + i is the
-// physical storage index in every case.
-//
-// A mesh may be split into blocks[0] x blocks[1] x blocks[2] blocks of equal
-// extents (kernel axes); n and ncells are those of one block.  Fields are
-// stored block after block, [block][comp][cell of the block], with block
-// index b0 + blocks[0] (b1 + blocks[1] b2).  The boundary codes are those of
-// the whole mesh: a side of a block inside the mesh, or on a periodic axis,
-// reads its ghosts from the neighbouring block (a c-boundary); one block on a
-// periodic axis is its own neighbour.
-struct Geo {
-    int ndim;
-    int n[3];
-    int blocks[3];
-    double dx[3];
-    double inv_dx[3];
-    int bc[3][2];
-    double gamma;
-    double cfl;
-    long long ncells;
-};
-
-struct Tile {
-    int tx, ty, kz;
 };
 
 // Refinement levels 0 .. kMaxLevels - 1; a refined block is named by the code
@@ -171,42 +144,8 @@ struct MeshDesc {
     int tiles_x, tiles_y, chunks_z, kz;
 };
 
-// Stage kernels: the Heun stages (and the stage right-hand side), and the
-// van Leer predictor and corrector (Sec. 3.3).  The _C forms keep the
-// predicted state conserved in FP64 (a refined mesh, whose level-jump passes
-// read conserved stage inputs): the predictor writes U* = U^n + (dt/2) L_1(U^n)
-// and the corrector reads U* as its stencil input.  MODE_STAGE2_R is the Heun
-// stage 2 of a refined mesh (as MODE_VL2_CORR_C the corrector of one): the
-// cells corrected after it take no part in its CFL rate.
-enum StageMode : int {
-    MODE_RHS = 0,
-    MODE_STAGE1 = 1,
-    MODE_STAGE2 = 2,
-    MODE_VL2_PRED = 3,
-    MODE_VL2_CORR = 4,
-    MODE_VL2_PRED_C = 5,
-    MODE_VL2_CORR_C = 6,
-    MODE_STAGE2_R = 7
-};
-
-// The automatic chunk length (Tile::kz == 0), 1 .. kMaxAutoKz planes, of a
-// launch over the columns m[0 .. n) (each marches over n2 planes) by a kernel
-// of the given residency; and the length that gives a column the same number
-// of chunks in the most equal parts.
-constexpr int kMaxAutoKz = 128;
-struct Slots {
-    int cus, per_cu;  // CUs of the device, work-groups of the kernel resident on each
-    int waves;        // waves of a work-group
-};
-struct MarchCols {
-    long long cols;
-    int n2;
-    bool per_xcd;  // the launch covers eight blocks of a split mesh: one to each XCD
-};
-// *time (if given): the launch's modelled time, in planes of a work-group that
-// has a CU to itself.
-int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n, double* time = nullptr);
-int balanced_kz(int n2, int kz);
+// What the device holds at once of a stage kernel (zero if the runtime cannot
+// tell).
 Slots stage_residency(int ndim, int precision, int mode, const Tile& t);
 
 hipError_t launch_stage(int precision, int mode, const Tile& tile, StageArgs a, hipStream_t s);
@@ -237,9 +176,6 @@ hipError_t launch_stage_3d_fp64(int mode, const Tile& t, const LaunchCtx& L, hip
 hipError_t launch_stage_3d_mixed(int mode, const Tile& t, const LaunchCtx& L, hipStream_t s);
 
 hipError_t plan_stage_launch(int precision, int mode, const Tile& tile, StageArgs a, StageLaunch* out);
-// Fill the tiling fields of a descriptor for a tile (kz == 0 counts as 1: the
-// caller resolves the automatic length).
-void plan_tiles(const Geo& g, const Tile& t, int& tiles_x, int& tiles_y, int& chunks_z, int& kz);
 // One stage over every mesh of a group sharing ndim, precision and tile:
 // blk[i] = (member, work-group within the member), nblk entries.
 hipError_t launch_stage_batch(int ndim, int precision, int mode, const Tile& tile, const MeshDesc* d,
@@ -299,14 +235,6 @@ hipError_t launch_smr_correct(int precision, int first, const Geo& g, const doub
 hipError_t launch_dt_levels(const Geo& g0, const LevelStarts& starts, int nblk, const double* U, Ctrl* ctrl,
                             hipStream_t s);
 
-// Default tile for a mesh (kernel axes) and precision.
-Tile default_tile(const Geo& g, int precision, int mode);
-// Whether the stage kernel is compiled for this tile shape.
-
-bool tile_supported(int ndim, const Tile& t);
-// Tiles the autotuner tries for a mesh (at most max written); returns how
-// many there are.
-int tile_candidates(const Geo& g, Tile* out, int max);
 // Number of totals partials the runtime reserves.
 constexpr int kTotalsParts = 1024;
 // Blocks of one mesh: each needs one totals partial at least.

@@ -2488,140 +2488,11 @@ hipError_t launch_any(int ndim, int precision, int mode, const Tile& t, const La
 }
 }  // namespace
 
-Tile default_tile(const Geo& g, int precision, int mode) {
-    Tile t;
-    if (mode == MODE_VL2_PRED_C || mode == MODE_VL2_CORR_C) {
-        // the one tile of the refined mesh's van Leer stages
-        t.tx = g.ndim == 3 ? 32 : 64;
-        t.ty = g.ndim == 3 ? 8 : 1;
-    } else if (g.ndim == 3) {
-        // From a sweep at 256^3: 32 x 16 halves the share of halo cells and
-        // extra faces where the occupancy allows it; 32 x 8 where a larger
-        // work-group would cost occupancy (the FP64 kernels).  16 x 16 is 2-8 % behind those on a
-        // mesh that each fills (even in FP64) and takes over where it pads
-        // less: 48^3 mixed 28 against 31 us a step, 101 x 75 x 50 FP64 57
-        // against 65 us.
-        const bool narrow = precision == 0;
-        auto padded = [&](int tx, int ty) {
-            return (double)((g.n[0] + tx - 1) / tx * tx) * ((g.n[1] + ty - 1) / ty * ty);
-        };
-        t.tx = 32;
-        t.ty = narrow ? 8 : 16;
-        if (1.04 * padded(16, 16) < padded(t.tx, t.ty)) t.tx = t.ty = 16;
-    } else if (g.ndim == 2) {
-        // the row width with the least padding, each row segment's halo and
-        // extra face counted as 24 cells (they take a wave of the work-group
-        // about a third of a plane): 256 for wide rows, 128 for rows of 384
-        t.tx = 256;
-        t.ty = 1;
-        auto cost = [&](int tx) { return (double)((g.n[0] + tx - 1) / tx) * (tx + 24); };
-        for (int tx = 128; tx >= 64; tx /= 2)
-            if (cost(tx) < cost(t.tx)) t.tx = tx;
-    } else {
-        t.tx = 64;
-        t.ty = 1;
-    }
-    // chunk length chosen at launch (auto_kz)
-    t.kz = g.ndim == 1 ? 1 : 0;
-    return t;
-}
-
-bool tile_supported(int ndim, const Tile& t) {
-    if (t.kz < 0 || (t.kz == 0 && ndim == 1)) return false;
-    if (ndim == 3)
-        return (t.tx == 32 && t.ty == 8) || (t.tx == 64 && t.ty == 8) || (t.tx == 16 && t.ty == 16) ||
-               (t.tx == 32 && t.ty == 16);
-    return t.ty == 1 && (t.tx == 64 || t.tx == 128 || t.tx == 256);
-}
-
-int tile_candidates(const Geo& g, Tile* out, int max) {
-    static const int shapes3[4][2] = {{32, 8}, {64, 8}, {16, 16}, {32, 16}};
-    static const int shapes12[4][2] = {{64, 1}, {128, 1}, {256, 1}, {0, 0}};
-    static const int kzs[5] = {0, 8, 16, 32, 64};  // 0: automatic
-    const int(*shapes)[2] = g.ndim == 3 ? shapes3 : shapes12;
-    int n = 0;
-    for (int s = 0; s < (g.ndim == 3 ? 4 : 3); ++s) {
-        // in 1-D and 2-D a row wider than twice the mesh only idles threads
-        if (g.ndim < 3 && s > 0 && shapes[s][0] >= 2 * g.n[0]) continue;
-        for (int q = 0; q < (g.ndim == 1 ? 1 : 5); ++q) {
-            const int kz = g.ndim == 1 ? 1 : kzs[q];
-            if (q > 1 && kzs[q - 1] >= g.n[2]) break;  // same chunks as the previous kz
-            if (n < max) {
-                out[n].tx = shapes[s][0];
-                out[n].ty = shapes[s][1];
-                out[n].kz = kz;
-            }
-            ++n;
-        }
-    }
-    return n;
-}
-
-int balanced_kz(int n2, int kz) {
-    kz = kz < 1 ? 1 : (kz > n2 ? n2 : kz);
-    const int chunks = (n2 + kz - 1) / kz;
-    return (n2 + chunks - 1) / chunks;
-}
-
-// The chunk length that a launch over the columns m[0 .. n) takes least time
-// with, by a model of the march: a work-group spends kz planes and a lead of
-// about two planes more (three in 2-D: the start of the z pipeline), and a
-// plane takes 1 + (w - 1)/3 with 4 w waves resident on the CU.  Fitted to
-// sweeps of both precisions and integrators from 32^3 to 160^3 and 64^2 to
-// 4096 x 1024: a plane's time is 2.6 us with four waves on a CU and 4.1 us
-// with twelve (mixed 3-D), so small meshes want a work-group per plane or two
-// (48^3 mixed: a step 102 us in chunks of 16, 28 us in chunks of 1-2; 256^2
-// FP64 89 and 21 us), and a last round of a few work-groups costs as much as a
-// full one (160^3 mixed: 316 us with 800 work-groups on 768 places, 225 us
-// with 700) -- unless each XCD has a block of its own, whose columns' shorter
-// last chunks come last and two deep beside the others (192^3 van Leer in
-// eight blocks: a step 332 us with 432 equal work-groups on 512 places, 310 us
-// with 576 in chunks of 28 and 12).
-int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n, double* time) {
-    if (time) *time = 0.0;
-    if (ndim == 1) return 1;
-    int most = 1;
-    for (int i = 0; i < n; ++i) most = m[i].n2 > most ? m[i].n2 : most;
-    most = most > kMaxAutoKz ? kMaxAutoKz : most;
-    if (sl.cus < 1 || sl.per_cu < 1) return most < 32 ? most : 32;
-    const double lead = ndim == 3 ? 2.0 : 3.0;
-    const long long slots = (long long)sl.cus * sl.per_cu;
-    auto plane = [&](long long wgs) {
-        const double w = (double)((wgs + sl.cus - 1) / sl.cus) * sl.waves / 4.0;
-        return w > 1.0 ? 1.0 + (w - 1.0) / 3.0 : 1.0;
-    };
-    int best = most;
-    double least = 0.0;
-    for (int kz = most; kz >= 1; --kz) {
-        long long wgs = 0;
-        for (int i = 0; i < n; ++i) wgs += m[i].cols * ((m[i].n2 + kz - 1) / kz);
-        const long long full = wgs / slots, rest = wgs % slots;
-        double t = (kz + lead) * (full * plane(slots) + (rest ? plane(rest) : 0.0));
-        if (n == 1 && m[0].per_xcd && full == 1 && rest > 0 && 2 * slots + m[0].cols >= 2 * wgs) {
-            const int last = m[0].n2 - (m[0].n2 - 1) / kz * kz;
-            t = std::fmin(t, plane(slots) * std::fmax(kz + lead, 2.0 * (last + lead)));
-        }
-        if (kz == most || t <= least) {
-            least = t;
-            best = kz;
-        }
-    }
-    if (time) *time = least;
-    return best;
-}
-
 Slots stage_residency(int ndim, int precision, int mode, const Tile& t) {
     Slots o{0, 0, 0};
     LaunchCtx L{nullptr, nullptr, nullptr, 0, nullptr, &o};
     if (launch_any(ndim, precision, mode, t, L, nullptr) != hipSuccess) return Slots{0, 0, 0};
     return o;
-}
-
-void plan_tiles(const Geo& g, const Tile& t, int& tiles_x, int& tiles_y, int& chunks_z, int& kz) {
-    tiles_x = (g.n[0] + t.tx - 1) / t.tx;
-    tiles_y = (g.n[1] + t.ty - 1) / t.ty;
-    kz = t.kz < 1 ? 1 : (t.kz > g.n[2] ? g.n[2] : t.kz);
-    chunks_z = (g.n[2] + kz - 1) / kz;
 }
 
 hipError_t launch_stage(int precision, int mode, const Tile& t, StageArgs a, hipStream_t s) {

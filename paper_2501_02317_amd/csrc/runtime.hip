@@ -1558,14 +1558,7 @@ struct hydro_batch_ctx {
     hipStream_t stream;
     MeshDesc* d_desc;  // descriptor table in the caller's workspace, in group order
     int2* d_blk;       // work-group table, grouped
-    struct Group {
-        int ndim, precision, integrator;
-        Tile tile;
-        int blk_off, nblk;
-        int mem_off, nmem;  // the group's descriptors: d_desc[mem_off .. mem_off + nmem)
-        double cells;       // cells of its members
-    };
-    std::vector<Group> groups;
+    std::vector<BatchGroup> groups;
     std::vector<int> order;  // order[k]: the member (caller's index) of descriptor k
     // Direct launches spread the groups over the batch's stream and up to
     // kBatchSideStreams more (group_stream[g]: 0 the batch's stream, i > 0
@@ -1589,7 +1582,7 @@ struct BatchPlan {
     std::vector<MeshDesc> desc;
     std::vector<int> order;
     std::vector<int2> blk;
-    std::vector<hydro_batch_ctx::Group> groups;
+    std::vector<BatchGroup> groups;
 };
 
 // Two more streams: with the batch's own, three of the four hardware queues
@@ -1600,160 +1593,28 @@ struct BatchPlan {
 // held at 1.37-1.42e10.
 constexpr int kBatchSideStreams = 2;
 
-// Tile rules of the batch autotuner for members of one or two dimensions:
-// a row width for every such member (0: the member's own) and a chunk length
-// (-1: the member's own, 0: about 2048 work-groups per member).  Rule 0
-// keeps every member's tile.  3-D members keep their tiles.
-struct BatchRule {
-    int tx, kz;
-};
-constexpr BatchRule kBatchRules[] = {{0, -1}, {64, -1}, {128, -1}, {256, -1}, {0, 16},   {64, 16},
-                                     {128, 16}, {0, 32}, {64, 32},   {128, 32},  {0, 64},  {64, 64}};
-constexpr int kNumBatchRules = (int)(sizeof(kBatchRules) / sizeof(kBatchRules[0]));
-
-Tile rule_tile(const hydro_t h, int rule) {
-    Tile t = h->tile[0];
-    if (h->cfg.ndim == 3 || rule <= 0 || rule >= kNumBatchRules) return t;
-    if (kBatchRules[rule].tx > 0) t.tx = kBatchRules[rule].tx;
-    if (kBatchRules[rule].kz >= 0) t.kz = kBatchRules[rule].kz;
-    return t;
+PlanMember plan_member(const hydro_t h) {
+    return {h->geo, h->cfg.precision, h->cfg.integrator, h->tile[0], h->tile_set};
 }
 
-// The columns of members idx[0 .. n) in tile t, and the automatic chunk length
-// and modelled time of a launch over them (a launch of its own counts two
-// planes; a tile's halo and extra faces as in default_tile).
-int batch_kz(const std::vector<int>& idx, const hydro_t* members, const Tile& t, double* time = nullptr) {
-    std::vector<MarchCols> cols;
-    for (int i : idx) {
-        const Geo& g = members[i]->geo;
-        int tx, ty, cz, kz;
-        plan_tiles(g, t, tx, ty, cz, kz);
-        cols.push_back({(long long)tx * ty, g.n[2], false});
-    }
-    const hydro_t h = members[idx[0]];
-    const Slots sl = stage_residency(h->cfg.ndim, h->cfg.precision, stage2_mode(&h->cfg), t);
-    const int kz = auto_kz(h->cfg.ndim, sl, cols.data(), (int)cols.size(), time);
-    if (time) {
-        const double wide = h->cfg.ndim == 3 ? (t.tx * t.ty > 256 ? 1.0 : 1.08) : 1.0 + 24.0 / t.tx;
-        *time = 2.0 + *time * wide;
-    }
-    return kz;
-}
-
-// One tile for the members (of one ndim, precision and integrator) that have
-// the default ones, where their launches' modelled times add up to more than
-// that of one launch with it: a group's last work-groups leave the chip idle,
-// and a stage of 16-30 us is a good part launch (48 ragged 2-D meshes alone:
-// 7.27 ms in three groups, 5.95 ms in one of width 128, 6.08 of 64).
-void share_tile(const std::vector<int>& idx, const hydro_t* members, std::vector<Tile>& tiles) {
-    if (idx.empty()) return;
-    const hydro_t h0 = members[idx[0]];
-    if (h0->cfg.ndim == 1) return;
-    std::vector<Tile> kinds;
-    std::vector<std::vector<int>> of;
-    for (int i : idx) {
-        size_t k = 0;
-        while (k < kinds.size() && (kinds[k].tx != tiles[i].tx || kinds[k].ty != tiles[i].ty)) ++k;
-        if (k == kinds.size()) {
-            kinds.push_back(tiles[i]);
-            of.push_back({});
-        }
-        of[k].push_back(i);
-    }
-    if (kinds.size() < 2) return;
-    double own = 0.0;
-    for (size_t k = 0; k < kinds.size(); ++k) {
-        double t = 0.0;
-        batch_kz(of[k], members, kinds[k], &t);
-        own += t;
-    }
-    int best = -1;
-    for (size_t k = 0; k < kinds.size(); ++k) {
-        double t = 0.0;
-        batch_kz(idx, members, kinds[k], &t);
-        if (t < own) {
-            own = t;
-            best = (int)k;
-        }
-    }
-    if (best >= 0)
-        for (int i : idx) tiles[i] = kinds[best];
-}
-
-// Members grouped by (ndim, precision, tile): each group's descriptors and
-// work-groups are contiguous in their tables, members in the caller's order
-// within a group (P.order maps a descriptor to its member).  Member i runs
-// tile rule_tile(members[i], rule); with rule 0, members of the default tiles
-// may share one (share_tile).
+// The tables of a batch under a rule of its autotuner: descriptors in the
+// layout's order, and their work-groups.
 bool plan_batch(int n, const hydro_t* members, BatchPlan& P, int rule = 0) {
-    std::vector<MeshDesc> desc(n);
-    std::vector<int> order(n);
-    std::vector<Tile> tiles(n);
-    for (int i = 0; i < n; ++i) tiles[i] = rule_tile(members[i], rule);
-    if (rule == 0)
-        for (int c = 0; c < 16; ++c) {
-            std::vector<int> same;
-            for (int i = 0; i < n; ++i) {
-                const hydro_config& f = members[i]->cfg;
-                if (!members[i]->tile_set && c == 4 * f.ndim + 2 * (f.precision == HYDRO_MIXED) + (f.integrator == HYDRO_VL2))
-                    same.push_back(i);
-            }
-            share_tile(same, members, tiles);
-        }
-    for (int i = 0; i < n; ++i) {
-        const hydro_t h = members[i];
-        MeshDesc& d = desc[i];
-        d.U = h->U;
-        d.U1 = h->U1;
-        d.ctrl = h->ctrl;
-        d.geo = h->geo;
-        plan_tiles(h->geo, tiles[i], d.tiles_x, d.tiles_y, d.chunks_z, d.kz);
-        order[i] = i;
-    }
-    auto key = [&](int i) {
-        const hydro_t h = members[i];
-        return std::make_tuple(h->cfg.ndim, h->cfg.precision, h->cfg.integrator, tiles[i].tx, tiles[i].ty);
-    };
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key(a) < key(b); });
-    // automatic chunk lengths: one per group, for the columns of all its members
-    for (int i0 = 0, i1 = 0; i0 < n; i0 = i1) {
-        std::vector<int> aut;
-        for (i1 = i0; i1 < n && key(order[i1]) == key(order[i0]); ++i1)
-            if (tiles[order[i1]].kz == 0) aut.push_back(order[i1]);
-        if (aut.empty()) continue;
-        const int kz = batch_kz(aut, members, tiles[aut[0]]);
-        for (int i : aut) {
-            MeshDesc& d = desc[i];
-            d.kz = balanced_kz(d.geo.n[2], kz);
-            d.chunks_z = (d.geo.n[2] + d.kz - 1) / d.kz;
-        }
-    }
+    std::vector<PlanMember> m;
+    for (int i = 0; i < n; ++i) m.push_back(plan_member(members[i]));
+    BatchLayout L;
+    if (!plan_layout(m, rule, stage_residency, L)) return false;
+    P.blk.reserve(L.nblk);
     for (int idx = 0; idx < n; ++idx) {
-        const int i = order[idx];
+        const int i = L.order[idx];
         const hydro_t h = members[i];
-        if (P.groups.empty() || key(order[idx - 1]) != key(i)) {
-            hydro_batch_ctx::Group g;
-            g.ndim = h->cfg.ndim;
-            g.precision = h->cfg.precision;
-            g.integrator = h->cfg.integrator;
-            g.tile = tiles[i];
-            g.blk_off = (int)P.blk.size();
-            g.nblk = 0;
-            g.mem_off = idx;
-            g.nmem = 0;
-            g.cells = 0.0;
-            P.groups.push_back(g);
-        }
-        const MeshDesc& d = desc[i];
-        P.desc.push_back(d);
-        P.order.push_back(i);
-        P.groups.back().nmem += 1;
-        P.groups.back().cells += (double)d.geo.ncells;
-        const long long nb = (long long)d.tiles_x * d.tiles_y * d.chunks_z;
-        if (nb > (1ll << 28) || (long long)P.blk.size() + nb > (1ll << 30)) return false;
-        for (int b = 0; b < (int)nb; ++b) P.blk.push_back(make_int2(idx, b));
-        P.groups.back().nblk += (int)nb;
+        const MemberTiling& t = L.tiling[i];
+        P.desc.push_back({h->U, h->U1, h->ctrl, h->geo, t.tiles_x, t.tiles_y, t.chunks_z, t.kz});
+        const int nb = t.tiles_x * t.tiles_y * t.chunks_z;
+        for (int b = 0; b < nb; ++b) P.blk.push_back(make_int2(idx, b));
     }
+    P.order = L.order;
+    P.groups = L.groups;
     return true;
 }
 
@@ -2075,7 +1936,7 @@ int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule_out, dou
         if (!(ms[best] < 0.95 * ms[0])) best = 0;
         for (hydro_t h : b->members)
             if (h->cfg.ndim < 3 && best > 0) {
-                h->tile[0] = h->tile[1] = rule_tile(h, best);
+                h->tile[0] = h->tile[1] = rule_tile(plan_member(h), best);
                 h->tile_set = true;
             }
         BatchPlan P;
