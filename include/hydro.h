@@ -373,7 +373,9 @@ int hydro_batch_step(hydro_batch_t b, int nsteps);
  * their run limits.  *rule receives the rule index (0: members' own tiles)
  * and *ms_per_step its time per batched step.  Blocks.  steps_per_rule in
  * [1, 64].  The batch workspace (hydro_batch_workspace_bytes) is sized for
- * every rule. */
+ * every rule with the tiles that the members have then; if a tile set since
+ * makes a rule need more than the workspace holds, the call returns
+ * HYDRO_E_INVAL and changes nothing. */
 int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule, double* ms_per_step);
 
 /* Per-member run-limit flag (done[i] = 1 once member i reached its limit),

@@ -227,22 +227,23 @@ Tile rule_tile(const PlanMember& m, int rule) {
 
 // Members grouped by (ndim, precision, tile): each group's descriptors and
 // work-groups are contiguous in their tables, members in the caller's order
-// within a group.  Member i runs tile rule_tile(m[i], rule); with rule 0,
-// members of the default tiles may share one (share_tile).
+// within a group.  Member i runs tile rule_tile(m[i], rule); members of the
+// default tiles may share one (share_tile) where the rule keeps their tiles:
+// under every rule in 3-D, so that what a rule leaves is what was timed under
+// it.
 bool plan_layout(const std::vector<PlanMember>& m, int rule, Residency residency, BatchLayout& L) {
     const int n = (int)m.size();
     std::vector<int> order(n);
     std::vector<Tile> tiles(n);
     for (int i = 0; i < n; ++i) tiles[i] = rule_tile(m[i], rule);
-    if (rule == 0)
-        for (int c = 0; c < 16; ++c) {
-            std::vector<int> same;
-            for (int i = 0; i < n; ++i)
-                if (!m[i].tile_set && c == 4 * m[i].geo.ndim + 2 * (m[i].precision == HYDRO_MIXED) +
-                                               (m[i].integrator == HYDRO_VL2))
-                    same.push_back(i);
-            share_tile(same, m, residency, tiles);
-        }
+    for (int c = 0; c < 16; ++c) {
+        std::vector<int> same;
+        for (int i = 0; i < n; ++i)
+            if ((rule == 0 || m[i].geo.ndim == 3) && !m[i].tile_set &&
+                c == 4 * m[i].geo.ndim + 2 * (m[i].precision == HYDRO_MIXED) + (m[i].integrator == HYDRO_VL2))
+                same.push_back(i);
+        share_tile(same, m, residency, tiles);
+    }
     L.tiling.resize(n);
     for (int i = 0; i < n; ++i) {
         MemberTiling& d = L.tiling[i];

@@ -1556,8 +1556,11 @@ int hydro_riemann_fluxes(int precision, int ntan, double gamma, int64_t nfaces, 
 struct hydro_batch_ctx {
     std::vector<hydro_t> members;
     hipStream_t stream;
-    MeshDesc* d_desc;  // descriptor table in the caller's workspace, in group order
-    int2* d_blk;       // work-group table, grouped
+    // tables in the caller's workspace: descriptors in group order, the status
+    // of every member, work-groups (grouped), which may take the rest of it
+    MeshDesc* d_desc;
+    int2* d_blk;
+    size_t bytes;  // of the workspace
     std::vector<BatchGroup> groups;
     std::vector<int> order;  // order[k]: the member (caller's index) of descriptor k
     // Direct launches spread the groups over the batch's stream and up to
@@ -1808,7 +1811,11 @@ int hydro_batch_create(int n, const hydro_t* members, void* d_workspace, size_t 
     b->members.assign(members, members + n);
     b->stream = members[0]->stream;
     b->d_desc = (MeshDesc*)d_workspace;
-    b->d_blk = (int2*)((char*)d_workspace + align_up(P.desc.size() * sizeof(MeshDesc)));
+    char* p = (char*)d_workspace + align_up(P.desc.size() * sizeof(MeshDesc));
+    b->d_status = (unsigned long long*)p;
+    p += align_up((size_t)n * 3 * sizeof(unsigned long long));
+    b->d_blk = (int2*)p;
+    b->bytes = nbytes;
     b->groups = P.groups;
     b->order = P.order;
     b->ev_fork = nullptr;
@@ -1819,10 +1826,6 @@ int hydro_batch_create(int n, const hydro_t* members, void* d_workspace, size_t 
     // stream capture needs a stream other than the legacy default stream
     b->use_graph = use_graph != 0 && b->stream != nullptr;
     b->broken = false;
-    // the status table after the two plan tables, whose sizes differ between
-    // tile rules: at the end of the workspace the largest plan needs
-    b->d_status = (unsigned long long*)((char*)d_workspace + hydro_batch_workspace_bytes(n, members) -
-                                        align_up((size_t)n * 3 * sizeof(unsigned long long)));
     b->h_status.assign((size_t)n * 3, 0ull);
     hipError_t e = hipMemcpyAsync(b->d_desc, P.desc.data(), P.desc.size() * sizeof(MeshDesc),
                                   hipMemcpyHostToDevice, b->stream);
@@ -1886,8 +1889,10 @@ int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule_out, dou
     for (hydro_t h : b->members)
         if (h->broken) return HYDRO_E_STATE;
     std::vector<BatchPlan> plans(kNumBatchRules);
+    // the workspace holds every rule's tables for the tiles that the members
+    // had when it was sized; with tiles set since, they may not fit
     for (int r = 0; r < kNumBatchRules; ++r)
-        if (!plan_batch(n, b->members.data(), plans[r], r)) return HYDRO_E_INVAL;
+        if (!plan_batch(n, b->members.data(), plans[r], r) || batch_bytes(plans[r]) > b->bytes) return HYDRO_E_INVAL;
     drop_graph(b);
     std::vector<hipEvent_t> ev((size_t)kNumBatchRules * steps_per_rule * 2);
     size_t made = 0;
@@ -1935,13 +1940,11 @@ int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule_out, dou
             if (ms[r] < ms[best]) best = r;
         if (!(ms[best] < 0.95 * ms[0])) best = 0;
         for (hydro_t h : b->members)
-            if (h->cfg.ndim < 3 && best > 0) {
+            if (h->cfg.ndim < 3) {
                 h->tile[0] = h->tile[1] = rule_tile(plan_member(h), best);
-                h->tile_set = true;
+                h->tile_set = h->tile_set || best > 0;
             }
-        BatchPlan P;
-        if (!plan_batch(n, b->members.data(), P, 0)) e = hipErrorInvalidValue;
-        if (e == hipSuccess) e = upload(P);
+        e = upload(plans[best]);
     }
     if (e != hipSuccess) {
         b->broken = true;
