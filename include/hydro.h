@@ -146,8 +146,12 @@ int hydro_get_state(hydro_t h, double* U_host);
 /* Copy the current conserved state to a device array (async). */
 int hydro_get_state_device(hydro_t h, double* d_U);
 
-/* Device address of the current conserved state (valid until the next step;
- * the block layout when the mesh is split). */
+/* Device address of the current conserved state (valid until the next step
+ * or until a state is set; the block layout when the mesh is split).  Work
+ * that writes there on the handle's stream (a source term added between
+ * steps) is seen by the next step; its dt is that of the state as written
+ * unless the dt was taken before (by hydro_cfl_dt, or by the device steps
+ * that made the state). */
 int hydro_state_device(hydro_t h, const double** d_U);
 
 /* CFL step of the current state, cfl * min over cells and active axes of

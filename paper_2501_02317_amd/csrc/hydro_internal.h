@@ -71,6 +71,7 @@ enum CtrlOp : int {
     CTRL_FINALIZE_STEP = 2,  // the same for a step whose rate is in the slots unannounced
     CTRL_ADVANCE_T = 3,      // t += a0 (host dt), dt invalid
     CTRL_SET_LIMITS = 4,     // t_end = a0, max_steps = a1 (relative to the steps done), done
+    CTRL_DROP_RATE = 5,      // nothing pending
 };
 
 // Refinement levels 0 .. kMaxLevels - 1; a refined block is named by the code

@@ -1639,9 +1639,10 @@ __global__ __launch_bounds__(64) void ctrl_kernel(Ctrl* c, int op, double a0, do
         finalize_ctrl(c, op == CTRL_FINALIZE_STEP ? kPendStep : c->pend, cfl);
         return;
     }
-    // both leave nothing pending (a replayed host-dt step may meet a state
+    // these leave nothing pending (a replayed host-dt step may meet a state
     // whose rate is)
-    if (op == CTRL_INIT || op == CTRL_ADVANCE_T) *rate_slot(c, threadIdx.x / kRateSlots, threadIdx.x % kRateSlots) = 0ull;
+    if (op == CTRL_INIT || op == CTRL_ADVANCE_T || op == CTRL_DROP_RATE)
+        *rate_slot(c, threadIdx.x / kRateSlots, threadIdx.x % kRateSlots) = 0ull;
     if (threadIdx.x != 0) return;
     switch (op) {
         case CTRL_INIT:
@@ -1661,6 +1662,10 @@ __global__ __launch_bounds__(64) void ctrl_kernel(Ctrl* c, int op, double a0, do
             c->t = c->t + a0;
             c->steps += 1;
             c->dt_valid = 0;
+            c->pend = kPendNone;
+            c->pend_flags = 0;
+            break;
+        case CTRL_DROP_RATE:
             c->pend = kPendNone;
             c->pend_flags = 0;
             break;

@@ -63,6 +63,7 @@ struct hydro_ctx {
     bool rate_pending;
     bool no_limits;
     bool captured;    // the stream was captured during a call (see capturing())
+    bool exposed;     // the caller has the state's address and may write there (until a set or device steps)
     // optional event timing of the stage launches
     int prof_cap;
     int prof_n[2];
@@ -566,12 +567,16 @@ hipError_t enqueue_finalize(hydro_t h) {
     return e;
 }
 
-// The CFL rate of the current state pending in the control block.
+// The CFL rate of the current state pending in the control block.  One that is
+// pending already is taken again where the state may have changed since
+// without the host seeing it: by a replay, or through its address.
 hipError_t enqueue_rate(hydro_t h) {
-    if (h->rate_pending && !h->captured) return hipSuccess;
-    const hipError_t e = launch_dt_levels(h->smr ? h->lgeo[0] : h->geo, level_starts(h), h->nblk, h->U, h->ctrl,
-                                          h->stream);
-    if (e == hipSuccess) h->rate_pending = true;
+    if (h->rate_pending && !h->captured && !h->exposed) return hipSuccess;
+    hipError_t e = hipSuccess;
+    if (h->rate_pending || h->captured) e = launch_ctrl(h->ctrl, CTRL_DROP_RATE, 0.0, 0.0, h->cfg.cfl, h->stream);
+    if (e == hipSuccess)
+        e = launch_dt_levels(h->smr ? h->lgeo[0] : h->geo, level_starts(h), h->nblk, h->U, h->ctrl, h->stream);
+    h->rate_pending = e == hipSuccess;
     return e;
 }
 
@@ -601,6 +606,7 @@ void state_replaced(hydro_t h) {
     h->dt_valid = false;
     h->rate_pending = false;
     h->no_limits = true;
+    h->exposed = false;
 }
 
 // U from the primitive state W (mesh layout of a split mesh: mesh_layout),
@@ -1090,6 +1096,7 @@ int hydro_state_device(hydro_t h, const double** d_U) {
     if (rc) return rc;
     if (!d_U) return HYDRO_E_INVAL;
     *d_U = h->U;
+    h->exposed = true;
     return HYDRO_OK;
 }
 
@@ -1130,6 +1137,7 @@ int hydro_step_auto(hydro_t h, int nsteps, double t_end) {
     (void)capturing(h);
     hipError_t e = enqueue_limits(h, 0.0, t_end);
     if (e == hipSuccess) e = enqueue_first_dt(h);
+    h->exposed = false;
     if (runs_whole(h)) {
         for (int s = 0; s < nsteps && e == hipSuccess; s += kRunSteps) {
             const int k = std::min(nsteps - s, kRunSteps);
@@ -1364,6 +1372,7 @@ int hydro_autotune(hydro_t h, int steps_per_tile, double t_end, int* tiles, doub
     // so clock ramp-up or drift does not favour the candidates timed last.
     if (e == hipSuccess) e = enqueue_limits(h, 0.0, t_end);
     if (e == hipSuccess) e = enqueue_first_dt(h);
+    h->exposed = false;
     if (e == hipSuccess) e = enqueue_step(h, true, 0.0);
     // the timed steps' books are kept by control launches outside the events
     if (e == hipSuccess && step_chains(h)) e = enqueue_finalize(h);
@@ -1736,6 +1745,7 @@ void batch_stepped(hydro_batch_t b) {
     for (hydro_t h : b->members) {
         h->dt_valid = true;
         h->rate_pending = false;
+        h->exposed = false;
     }
 }
 
