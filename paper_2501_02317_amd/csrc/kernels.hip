@@ -1802,9 +1802,13 @@ __global__ __launch_bounds__(256) void totals_pass2(int nparts, const double* __
 }
 
 // m_d = rho v_d, E = p/(gamma - 1) + (1/2) sum_d m_d v_d, and the CFL rate of
-// the conserved state, left pending for the first time step (one pass over
-// the state instead of three: 256^3 372 -> 246 us; 192^3
-// in eight blocks, where it does the relayout too, 237 -> 98 us).
+// the conserved state, left pending for the first time step: one pass over
+// the state instead of three.  1024 work-groups, each with the next cells'
+// values on their way: the passes of a larger grid end in more work-groups'
+// reductions and atomics than they hide.  A state set and its dt read back
+// take 273 us at 256^3 and 38 us at 1024^2 (as passes of their own 398 and
+// 66, with 4096 work-groups without the early loads 287 and 40); a state set
+// alone 252 and 16 us (the conversion alone 244 and 15, with 4096 268 and 19).
 // W and U may be the same array (each cell is read before it is written);
 // blockIdx.y: the block of the mesh (block layout); MESH: W is in the mesh
 // layout of a uniform block grid.
@@ -1830,16 +1834,25 @@ __global__ __launch_bounds__(256) void prim_to_cons_kernel(Geo g0, LevelStarts s
     U += (long long)blk * NC * N;
     double best = 0.0;
     bool bad = false;
-    for (long long cell = (long long)blockIdx.x * blockDim.x + threadIdx.x; cell < N;
-         cell += (long long)gridDim.x * blockDim.x) {
+    // the primitive state of a cell
+    auto load = [&](long long cell, double(&w)[NC]) {
         long long q = cell;
         if (MESH) {
             const long long r = cell / g.n[0];
             q = cell % g.n[0] + (r % g.n[1]) * row + (r / g.n[1]) * plane;
         }
-        double w[NC], u[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) w[c] = W[c * ws + q];
+    };
+    const long long step = (long long)gridDim.x * blockDim.x;
+    long long cell = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    double next[NC];
+    if (cell < N) load(cell, next);
+    for (; cell < N; cell += step) {
+        double w[NC], u[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) w[c] = next[c];
+        if (cell + step < N) load(cell + step, next);
         prim_to_cons_cell<NDIM>(g.gamma, w, u);
 #pragma unroll
         for (int c = 0; c < NC; ++c) U[c * N + cell] = u[c];
@@ -2595,7 +2608,7 @@ hipError_t launch_totals_out(const Geo& g, const double* U, double* parts, int n
 
 hipError_t launch_prim_to_cons(const Geo& g0, const LevelStarts& starts, int nblk, const double* W, double* U,
                                int mesh_layout, Ctrl* ctrl, hipStream_t s) {
-    const dim3 grid(grid_for(g0.ncells, 256, (4096 + nblk - 1) / nblk), nblk);
+    const dim3 grid(grid_for(g0.ncells, 256, (1024 + nblk - 1) / nblk), nblk);
 #define PC(ND, M) hipLaunchKernelGGL((prim_to_cons_kernel<ND, M>), grid, dim3(256), 0, s, g0, starts, W, U, ctrl)
     switch (2 * g0.ndim + (mesh_layout ? 1 : 0)) {
         case 2: PC(1, false); break;
