@@ -97,7 +97,7 @@ struct StageArgs {
     int want_dt;         // stage 2: accumulate the next CFL candidate
     // the step keeps its own books: the first stage takes the pending rate
     // and leaves the step's control, the second leaves the next rate pending
-    // (0: the caller's control launches do)
+    // (with want_dt; else nothing).  0: the caller's control launches do
     int chain;
     int tiles_x, tiles_y, chunks_z, kz;  // per block
     int blk0, nblk;      // the launch covers blocks blk0 .. blk0 + nblk - 1

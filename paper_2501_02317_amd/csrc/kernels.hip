@@ -985,7 +985,8 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
             par = __builtin_amdgcn_readfirstlane(n.par);
             if (leader && tid == 0) {
                 a.ctrl->par = n.par;
-                a.ctrl->pend = a.use_device_dt ? (n.done ? kPendNone : kPendStep) : kPendRate;
+                a.ctrl->pend = a.use_device_dt ? (n.done ? kPendNone : kPendStep)
+                                              : (a.want_dt ? kPendRate : kPendNone);
                 a.ctrl->dt_raw = n.dt_raw;
                 a.ctrl->t = a.use_device_dt ? n.t : n.t + a.dt_host;
                 a.ctrl->steps = a.use_device_dt ? n.steps : n.steps + 1;
