@@ -1620,16 +1620,40 @@ __global__ __launch_bounds__(256) void dt_kernel(Geo g0, LevelStarts starts, con
 }
 
 // Use the rate in the slots (pend: what for) and clear both sets; one wave.
-__device__ __forceinline__ void finalize_ctrl(Ctrl* c, unsigned int pend, double cfl) {
-    const double rate = wave_max(load_slot(c, c->par));
-    *rate_slot(c, threadIdx.x / kRateSlots, threadIdx.x % kRateSlots) = 0ull;
-    if (threadIdx.x != 0) return;
-    if (pend == kPendStep) finalize_step(c, cfl, rate);
-    if (pend == kPendRate) {
-        c->dt_raw = cfl / rate;
-        c->dt_valid = 1;
-        c->flags |= c->pend_flags;
+// Latency bound (a chain of two loads at most): each lane takes one slot of
+// both sets, and the block is read whole beside them.
+__device__ __forceinline__ void finalize_ctrl(Ctrl* c, int op, double cfl) {
+    const unsigned int set = threadIdx.x / kRateSlots;
+    unsigned long long* slot = rate_slot(c, set, threadIdx.x % kRateSlots);
+    const double mine = __longlong_as_double((long long)*slot);
+    Ctrl k;
+    k.dt_raw = c->dt_raw;
+    k.t = c->t;
+    k.pend = c->pend;
+    k.par = c->par;
+    k.flags = c->flags;
+    k.dt_valid = c->dt_valid;
+    k.steps = c->steps;
+    k.t_end = c->t_end;
+    k.max_steps = c->max_steps;
+    k.done = c->done;
+    k.pend_flags = c->pend_flags;
+    const double rate = wave_max(set == k.par ? mine : 0.0);
+    *slot = 0ull;
+    if (op == CTRL_FINALIZE_STEP) k.pend = kPendStep;
+    if (k.pend == kPendStep) finalize_step(&k, cfl, rate);
+    if (k.pend == kPendRate) {
+        k.dt_raw = cfl / rate;
+        k.dt_valid = 1;
+        k.flags |= k.pend_flags;
     }
+    if (threadIdx.x != 0) return;
+    c->dt_raw = k.dt_raw;
+    c->t = k.t;
+    c->flags = k.flags;
+    c->dt_valid = k.dt_valid;
+    c->steps = k.steps;
+    c->done = k.done;
     c->pend = kPendNone;
     c->pend_flags = 0;
 }
@@ -1637,7 +1661,7 @@ __device__ __forceinline__ void finalize_ctrl(Ctrl* c, unsigned int pend, double
 __global__ __launch_bounds__(64) void ctrl_kernel(Ctrl* c, int op, double a0, double a1, double cfl) {
     static_assert(2 * kRateSlots == 64, "one wave clears both sets of slots");
     if (op == CTRL_FINALIZE || op == CTRL_FINALIZE_STEP) {
-        finalize_ctrl(c, op == CTRL_FINALIZE_STEP ? kPendStep : c->pend, cfl);
+        finalize_ctrl(c, op, cfl);
         return;
     }
     // these leave nothing pending (a replayed host-dt step may meet a state
@@ -1693,8 +1717,7 @@ __global__ void status_gather_kernel(const MeshDesc* __restrict__ d, int n, unsi
 
 // One wave per member.
 __global__ __launch_bounds__(64) void ctrl_batch_kernel(const MeshDesc* __restrict__ d) {
-    Ctrl* c = d[blockIdx.x].ctrl;
-    finalize_ctrl(c, c->pend, d[blockIdx.x].geo.cfl);
+    finalize_ctrl(d[blockIdx.x].ctrl, CTRL_FINALIZE, d[blockIdx.x].geo.cfl);
 }
 
 // Neumaier-compensated accumulator combined pairwise in a fixed tree.
