@@ -149,6 +149,11 @@ struct MeshDesc {
 // tell).
 Slots stage_residency(int ndim, int precision, int mode, const Tile& t);
 
+// The chunk length of a launch: the tile's, or the automatic one for the blocks
+// whose work runs at once (this launch's, or those of the launches on the
+// other streams as well).  The model takes 0.3-5 us of the host, so a handle
+// keeps the answer.
+int stage_kz(int precision, int mode, const Tile& tile, const StageArgs& a);
 hipError_t launch_stage(int precision, int mode, const Tile& tile, StageArgs a, hipStream_t s);
 // The same launch described (kernel, grid, block, arguments) instead of
 // enqueued, for a caller that adds it to a graph as a kernel node.

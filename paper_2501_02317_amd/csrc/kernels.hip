@@ -2385,16 +2385,6 @@ hipError_t launch_stage_t(const LaunchCtx& L, hipStream_t s) {
         *L.slots = stage_slots<NDIM, R, MODE, TX, TY>();
     } else if (L.a) {
         StageArgs a = *L.a;
-        if (a.kz == 0) {
-            // automatic chunk length for the blocks whose work runs at once
-            // (this launch's, or those of the launches on the other streams
-            // as well)
-            const int n2 = a.geo.n[2];
-            const MarchCols m{(long long)a.tiles_x * a.tiles_y * (a.conc > a.nblk ? a.conc : a.nblk), n2,
-                               a.nblk == 8 && !a.side};
-            a.kz = auto_kz(NDIM, stage_slots<NDIM, R, MODE, TX, TY>(), &m, 1);
-            a.chunks_z = (n2 + a.kz - 1) / a.kz;
-        }
         const long long nb = (long long)a.tiles_x * a.tiles_y * a.chunks_z * a.nblk;
         if (a.nblk < 1 || nb > 0x7fffffffll) return hipErrorInvalidValue;
         if (L.rec) {
@@ -2537,19 +2527,27 @@ Slots stage_residency(int ndim, int precision, int mode, const Tile& t) {
     return o;
 }
 
+int stage_kz(int precision, int mode, const Tile& t, const StageArgs& a) {
+    if (t.kz > 0) return t.kz;
+    int tx, ty, cz, kz;
+    plan_tiles(a.geo, t, tx, ty, cz, kz);
+    const MarchCols m{(long long)tx * ty * (a.conc > a.nblk ? a.conc : a.nblk), a.geo.n[2], a.nblk == 8 && !a.side};
+    return auto_kz(a.geo.ndim, stage_residency(a.geo.ndim, precision, mode, t), &m, 1);
+}
+
 hipError_t launch_stage(int precision, int mode, const Tile& t, StageArgs a, hipStream_t s) {
-    plan_tiles(a.geo, t, a.tiles_x, a.tiles_y, a.chunks_z, a.kz);
-    if (t.kz == 0 && a.geo.ndim > 1) a.kz = 0;  // resolved per kernel at launch
+    const Tile r{t.tx, t.ty, stage_kz(precision, mode, t, a)};
+    plan_tiles(a.geo, r, a.tiles_x, a.tiles_y, a.chunks_z, a.kz);
     LaunchCtx L{&a, nullptr, nullptr, 0, nullptr, nullptr};
-    return launch_any(a.geo.ndim, precision, mode, t, L, s);
+    return launch_any(a.geo.ndim, precision, mode, r, L, s);
 }
 
 hipError_t plan_stage_launch(int precision, int mode, const Tile& t, StageArgs a, StageLaunch* out) {
     if (!out) return hipErrorInvalidValue;
-    plan_tiles(a.geo, t, a.tiles_x, a.tiles_y, a.chunks_z, a.kz);
-    if (t.kz == 0 && a.geo.ndim > 1) a.kz = 0;
+    const Tile r{t.tx, t.ty, stage_kz(precision, mode, t, a)};
+    plan_tiles(a.geo, r, a.tiles_x, a.tiles_y, a.chunks_z, a.kz);
     LaunchCtx L{&a, nullptr, nullptr, 0, out, nullptr};
-    return launch_any(a.geo.ndim, precision, mode, t, L, nullptr);
+    return launch_any(a.geo.ndim, precision, mode, r, L, nullptr);
 }
 
 hipError_t launch_stage_batch(int ndim, int precision, int mode, const Tile& tile, const MeshDesc* d,

@@ -110,18 +110,28 @@ int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n, double* time) 
         const double w = (double)((wgs + sl.cus - 1) / sl.cus) * sl.waves / 4.0;
         return w > 1.0 ? 1.0 + (w - 1.0) / 3.0 : 1.0;
     };
+    const bool xcd = n == 1 && m[0].per_xcd;
     int best = most;
-    double least = 0.0;
-    for (int kz = most; kz >= 1; --kz) {
+    double least = -1.0;
+    for (int kz = most, next; kz >= 1; kz = next) {
+        // with the same chunks per column the shortest length is the best (the
+        // last chunk alone may still matter to per_xcd)
+        int same = xcd ? kz : 1;
         long long wgs = 0;
-        for (int i = 0; i < n; ++i) wgs += m[i].cols * ((m[i].n2 + kz - 1) / kz);
+        for (int i = 0; i < n; ++i) {
+            const int chunks = (m[i].n2 + kz - 1) / kz, shortest = (m[i].n2 + chunks - 1) / chunks;
+            wgs += m[i].cols * chunks;
+            same = shortest > same ? shortest : same;
+        }
+        kz = same;
+        next = kz - 1;
         const long long full = wgs / slots, rest = wgs % slots;
         double t = (kz + lead) * (full * plane(slots) + (rest ? plane(rest) : 0.0));
-        if (n == 1 && m[0].per_xcd && full == 1 && rest > 0 && 2 * slots + m[0].cols >= 2 * wgs) {
+        if (xcd && full == 1 && rest > 0 && 2 * slots + m[0].cols >= 2 * wgs) {
             const int last = m[0].n2 - (m[0].n2 - 1) / kz * kz;
             t = std::fmin(t, plane(slots) * std::fmax(kz + lead, 2.0 * (last + lead)));
         }
-        if (kz == most || t <= least) {
+        if (least < 0.0 || t <= least) {
             least = t;
             best = kz;
         }
@@ -157,12 +167,15 @@ static_assert(sizeof(kBatchRules) / sizeof(kBatchRules[0]) == kNumBatchRules, "r
 // planes; a tile's halo and extra faces as in default_tile).
 int batch_kz(const std::vector<int>& idx, const std::vector<PlanMember>& m, const Tile& t, Residency residency,
              double* time = nullptr) {
-    std::vector<MarchCols> cols;
+    std::vector<MarchCols> cols;  // of one length each
     for (int i : idx) {
         const Geo& g = m[i].geo;
         int tx, ty, cz, kz;
         plan_tiles(g, t, tx, ty, cz, kz);
-        cols.push_back({(long long)tx * ty, g.n[2], false});
+        size_t k = 0;
+        while (k < cols.size() && cols[k].n2 != g.n[2]) ++k;
+        if (k == cols.size()) cols.push_back({0, g.n[2], false});
+        cols[k].cols += (long long)tx * ty;
     }
     const PlanMember& h = m[idx[0]];
     const int mode = h.integrator == HYDRO_VL2 ? MODE_VL2_CORR : MODE_STAGE2;

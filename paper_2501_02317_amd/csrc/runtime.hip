@@ -48,6 +48,7 @@ struct hydro_ctx {
     int32_t* leaves;               // host: (level, c0, c1, c2) per leaf
     Tile tile[2];  // stage 1 (and the rhs), stage 2
     bool tile_set;  // by the caller or an autotuner (else the defaults)
+    int kz[2][2];   // their automatic chunk lengths, once known (stage_tile)
     hipStream_t stream;
     int ncomp;
     double dV;
@@ -322,6 +323,21 @@ hipError_t block_streams_make(hydro_t h) {
     return hipSuccess;
 }
 
+// The tile of a stage's launch over a.nblk of the blocks, its chunk length
+// resolved.
+Tile stage_tile(hydro_t h, int st, int mode, const StageArgs& a) {
+    Tile t = h->tile[st];
+    int& kz = h->kz[st][a.nblk == 8 ? 1 : 0];  // all that the length depends on besides the handle
+    if (kz == 0) kz = stage_kz(h->cfg.precision, mode, t, a);
+    t.kz = kz;
+    return t;
+}
+
+void set_tile(hydro_t h, int st, const Tile& t) {
+    h->tile[st] = t;
+    h->kz[st][0] = h->kz[st][1] = 0;
+}
+
 // One step with the blocks' stages launched by group, each group of
 // contiguous blocks on a stream of its own: stage 1 of every group, then
 // stage 2 of a group once the groups holding its blocks' face neighbours have
@@ -344,7 +360,8 @@ hipError_t enqueue_step_streams(hydro_t h, bool device_dt, double dt) {
         a.base = h->U;
         a.out = h->U1;
         a.want_dt = 0;
-        e = launch_stage(h->cfg.precision, stage1_mode(&h->cfg), h->tile[0], a, h->bs[g]);
+        e = launch_stage(h->cfg.precision, stage1_mode(&h->cfg), stage_tile(h, 0, stage1_mode(&h->cfg), a), a,
+                         h->bs[g]);
         if (e == hipSuccess) e = hipEventRecord(h->ev_s1[g], h->bs[g]);
     }
     for (int g = 0; g < h->nbs && e == hipSuccess; ++g) {
@@ -356,7 +373,8 @@ hipError_t enqueue_step_streams(hydro_t h, bool device_dt, double dt) {
         a.base = h->U;
         a.out = h->U;
         a.want_dt = device_dt ? 1 : 0;
-        if (e == hipSuccess) e = launch_stage(h->cfg.precision, stage2_mode(&h->cfg), h->tile[1], a, h->bs[g]);
+        if (e == hipSuccess) e = launch_stage(h->cfg.precision, stage2_mode(&h->cfg), stage_tile(h, 1, stage2_mode(&h->cfg), a), a,
+                             h->bs[g]);
     }
     for (int i = 0; i < h->nbs && e == hipSuccess; ++i) {
         e = hipEventRecord(h->ev_join[i], h->bs[i]);
@@ -414,7 +432,7 @@ hipError_t enqueue_step_streams_graph(hydro_t h, bool device_dt, double dt) {
         a.base = h->U;
         a.out = h->U1;
         a.want_dt = 0;
-        e = add(stage1_mode(&h->cfg), h->tile[0], d0, &s1[g]);
+        e = add(stage1_mode(&h->cfg), stage_tile(h, 0, stage1_mode(&h->cfg), a), d0, &s1[g]);
     }
     for (int g = 0; g < h->nbs && e == hipSuccess; ++g) {
         // it reads their stage-1 output, and they read the state it overwrites
@@ -426,7 +444,7 @@ hipError_t enqueue_step_streams_graph(hydro_t h, bool device_dt, double dt) {
         a.base = h->U;
         a.out = h->U;
         a.want_dt = device_dt ? 1 : 0;
-        e = add(stage2_mode(&h->cfg), h->tile[1], dep, &s2[g]);
+        e = add(stage2_mode(&h->cfg), stage_tile(h, 1, stage2_mode(&h->cfg), a), dep, &s2[g]);
     }
     if (e == hipSuccess)
         e = hipStreamUpdateCaptureDependencies(h->stream, s2.data(), s2.size(), hipStreamSetCaptureDependencies);
@@ -456,7 +474,7 @@ hipError_t timed_stage(hydro_t h, int mode, const StageArgs& a) {
     const bool rec = h->prof_cap > 0 && h->prof_n[st] < h->prof_cap;
     hipError_t e = hipSuccess;
     if (rec) e = hipEventRecord(h->prof_ev[st][2 * h->prof_n[st]], h->stream);
-    if (e == hipSuccess) e = launch_stage(h->cfg.precision, mode, h->tile[st], a, h->stream);
+    if (e == hipSuccess) e = launch_stage(h->cfg.precision, mode, stage_tile(h, st, mode, a), a, h->stream);
     if (rec && e == hipSuccess) {
         e = hipEventRecord(h->prof_ev[st][2 * h->prof_n[st] + 1], h->stream);
         h->prof_n[st] += 1;
@@ -1339,8 +1357,8 @@ int hydro_set_stage_tile(hydro_t h, int stage, int tx, int ty, int kz) {
     t.ty = ty;
     t.kz = kz;
     if (!tile_supported(h->cfg.ndim, t)) return HYDRO_E_INVAL;
-    if (stage != 2) h->tile[0] = t;
-    if (stage != 1) h->tile[1] = t;
+    if (stage != 2) set_tile(h, 0, t);
+    if (stage != 1) set_tile(h, 1, t);
     h->tile_set = true;
     return HYDRO_OK;
 }
@@ -1430,7 +1448,7 @@ int hydro_autotune(hydro_t h, int steps_per_tile, double t_end, int* tiles, doub
         for (int c = 0; c < nc; ++c)
             if (best < 0 || ms[2 * c + st] < ms[2 * best + st]) best = c;
         if (keep_c >= 0 && !(ms[2 * best + st] < 0.95 * ms[2 * keep_c + st])) best = keep_c;
-        h->tile[st] = cand[best];
+        set_tile(h, st, cand[best]);
         h->tile_set = true;
         tiles[3 * st] = cand[best].tx;
         tiles[3 * st + 1] = cand[best].ty;
@@ -1618,13 +1636,20 @@ PlanMember plan_member(const hydro_t h) {
     return {h->geo, h->cfg.precision, h->cfg.integrator, h->tile[0], h->tile_set};
 }
 
+std::vector<PlanMember> plan_members(int n, const hydro_t* members) {
+    std::vector<PlanMember> m;
+    m.reserve(n);
+    for (int i = 0; i < n; ++i) m.push_back(plan_member(members[i]));
+    return m;
+}
+
 // The tables of a batch under a rule of its autotuner: descriptors in the
 // layout's order, and their work-groups.
-bool plan_batch(int n, const hydro_t* members, BatchPlan& P, int rule = 0) {
-    std::vector<PlanMember> m;
-    for (int i = 0; i < n; ++i) m.push_back(plan_member(members[i]));
+bool plan_batch(const std::vector<PlanMember>& m, const hydro_t* members, BatchPlan& P, int rule = 0) {
     BatchLayout L;
     if (!plan_layout(m, rule, stage_residency, L)) return false;
+    const int n = (int)m.size();
+    P.desc.reserve(n);
     P.blk.reserve(L.nblk);
     for (int idx = 0; idx < n; ++idx) {
         const int i = L.order[idx];
@@ -1639,9 +1664,26 @@ bool plan_batch(int n, const hydro_t* members, BatchPlan& P, int rule = 0) {
     return true;
 }
 
-size_t batch_bytes(const BatchPlan& P) {
-    return align_up(P.desc.size() * sizeof(MeshDesc)) + align_up(P.blk.size() * sizeof(int2)) +
-           align_up(P.desc.size() * 3 * sizeof(unsigned long long));
+size_t batch_bytes(size_t n, size_t nblk) {
+    return align_up(n * sizeof(MeshDesc)) + align_up(nblk * sizeof(int2)) +
+           align_up(n * 3 * sizeof(unsigned long long));
+}
+
+// Enough for the tables of every tile rule the autotuner tries (0: a rule has
+// too many work-groups).  From the layouts alone, and once for the 3-D members,
+// which no rule changes: planning every rule's tables for both the caller's
+// size and hydro_batch_create took 411 us a batch of 60.
+size_t batch_need(const std::vector<PlanMember>& m) {
+    std::vector<PlanMember> part[2];  // ruled, 3-D
+    for (const PlanMember& h : m) part[h.geo.ndim == 3 ? 1 : 0].push_back(h);
+    int most[2] = {0, 0};
+    for (int q = 0; q < 2; ++q)
+        for (int r = 0; r < (part[q].empty() ? 0 : (q == 0 ? kNumBatchRules : 1)); ++r) {
+            BatchLayout L;
+            if (!plan_layout(part[q], r, stage_residency, L)) return 0;
+            most[q] = std::max(most[q], L.nblk);
+        }
+    return batch_bytes(m.size(), (size_t)most[0] + most[1]);
 }
 
 // Groups onto streams, largest first onto the least loaded (by cells), over
@@ -1808,23 +1850,17 @@ extern "C" {
 
 size_t hydro_batch_workspace_bytes(int n, const hydro_t* members) {
     if (!members_ok(n, members)) return 0;
-    // large enough for the work-group table of any tile rule the autotuner tries
-    size_t most = 0;
-    for (int r = 0; r < kNumBatchRules; ++r) {
-        BatchPlan P;
-        if (!plan_batch(n, members, P, r)) return 0;
-        most = std::max(most, batch_bytes(P));
-    }
-    return most;
+    return batch_need(plan_members(n, members));
 }
 
 int hydro_batch_create(int n, const hydro_t* members, void* d_workspace, size_t nbytes, int use_graph,
                        hydro_batch_t* out) {
     if (!out || !members_ok(n, members) || !d_workspace) return HYDRO_E_INVAL;
     if (((uintptr_t)d_workspace) % kAlign != 0) return HYDRO_E_INVAL;
+    const std::vector<PlanMember> m = plan_members(n, members);
+    const size_t need = batch_need(m);
     BatchPlan P;
-    if (!plan_batch(n, members, P)) return HYDRO_E_INVAL;
-    if (nbytes < hydro_batch_workspace_bytes(n, members)) return HYDRO_E_INVAL;
+    if (need == 0 || nbytes < need || !plan_batch(m, members, P)) return HYDRO_E_INVAL;
     hydro_batch_ctx* b = new (std::nothrow) hydro_batch_ctx;
     if (!b) return HYDRO_E_NOMEM;
     b->members.assign(members, members + n);
@@ -1910,8 +1946,10 @@ int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule_out, dou
     std::vector<BatchPlan> plans(kNumBatchRules);
     // the workspace holds every rule's tables for the tiles that the members
     // had when it was sized; with tiles set since, they may not fit
+    const std::vector<PlanMember> m = plan_members(n, b->members.data());
     for (int r = 0; r < kNumBatchRules; ++r)
-        if (!plan_batch(n, b->members.data(), plans[r], r) || batch_bytes(plans[r]) > b->bytes) return HYDRO_E_INVAL;
+        if (!plan_batch(m, b->members.data(), plans[r], r) || batch_bytes(n, plans[r].blk.size()) > b->bytes)
+            return HYDRO_E_INVAL;
     drop_graph(b);
     std::vector<hipEvent_t> ev((size_t)kNumBatchRules * steps_per_rule * 2);
     size_t made = 0;
@@ -1960,7 +1998,9 @@ int hydro_batch_autotune(hydro_batch_t b, int steps_per_rule, int* rule_out, dou
         if (!(ms[best] < 0.95 * ms[0])) best = 0;
         for (hydro_t h : b->members)
             if (h->cfg.ndim < 3) {
-                h->tile[0] = h->tile[1] = rule_tile(plan_member(h), best);
+                const Tile t = rule_tile(plan_member(h), best);
+                set_tile(h, 0, t);
+                set_tile(h, 1, t);
                 h->tile_set = h->tile_set || best > 0;
             }
         e = upload(plans[best]);

@@ -2,7 +2,8 @@
 of the work-groups a device of 256 CUs holds in place of the runtime's query.
 
 Members that the autotuner has left with a rule's tiles plan to the layout that
-it timed under the rule, so that one fits a workspace sized for all rules.
+it timed under the rule, so that one fits a workspace sized for all rules.  The
+chunk length is the one that the model's least time over all lengths gives.
 """
 import ctypes as C
 import os
@@ -16,12 +17,49 @@ CSRC = os.path.join(ROOT, "paper_2501_02317_amd", "csrc")
 RULES = 12
 
 HARNESS = r"""
-#include <cstdlib>
+#include <algorithm>
 #include "plan.h"
 using namespace hydro;
 static Slots residency(int ndim, int precision, int mode, const Tile& t) {
     const int waves = (t.tx * t.ty + 63) / 64;
     return {256, (ndim == 3 && precision == 0 ? 12 : 16) / waves, waves};
+}
+// The model of auto_kz over every length and every column by itself.
+static int every_kz(int ndim, const Slots& sl, const MarchCols* m, int n, double* time) {
+    int most = 1;
+    for (int i = 0; i < n; ++i) most = std::max(most, m[i].n2);
+    most = std::min(most, kMaxAutoKz);
+    const double lead = ndim == 3 ? 2.0 : 3.0;
+    const long long slots = (long long)sl.cus * sl.per_cu;
+    auto plane = [&](long long wgs) {
+        const double w = (double)((wgs + sl.cus - 1) / sl.cus) * sl.waves / 4.0;
+        return w > 1.0 ? 1.0 + (w - 1.0) / 3.0 : 1.0;
+    };
+    int best = most;
+    for (int kz = most; kz >= 1; --kz) {
+        long long wgs = 0;
+        for (int i = 0; i < n; ++i) wgs += m[i].cols * ((m[i].n2 + kz - 1) / kz);
+        const long long full = wgs / slots, rest = wgs % slots;
+        double t = (kz + lead) * (full * plane(slots) + (rest ? plane(rest) : 0.0));
+        if (n == 1 && m[0].per_xcd && full == 1 && rest > 0 && 2 * slots + m[0].cols >= 2 * wgs) {
+            const int last = m[0].n2 - (m[0].n2 - 1) / kz * kz;
+            t = std::min(t, plane(slots) * std::max(kz + lead, 2.0 * (last + lead)));
+        }
+        if (kz == most || t <= *time) {
+            *time = t;
+            best = kz;
+        }
+    }
+    return best;
+}
+// q: (columns, n2) each; whether auto_kz finds the same length and time.
+extern "C" int same_kz(int ndim, int per_cu, int waves, int n, const int* q, int per_xcd) {
+    std::vector<MarchCols> m;
+    for (int i = 0; i < n; ++i) m.push_back({q[2 * i], q[2 * i + 1], per_xcd != 0});
+    double a = 0.0, b = 0.0;
+    const Slots sl{256, per_cu, waves};
+    const int ka = auto_kz(ndim, sl, m.data(), n, &a), kb = every_kz(ndim, sl, m.data(), n, &b);
+    return ka == kb && a == b;
 }
 // members: (ndim, precision, integrator, n0, n1, n2, tx, ty, kz) each, tx 0: the default tile.
 // out: work-groups, groups, then per member (in descriptor order) its index, tiles and chunks.
@@ -117,3 +155,13 @@ def test_tuned_layout_is_the_timed_one_and_fits(lib):
             got = plan(lib, m, r, tuned=True)
             assert got[0] <= most, (m, r, got[0], most)
             assert got == rules[r], (m, r)
+
+
+def test_chunk_length_has_the_least_modelled_time(lib):
+    rng = random.Random(8)
+    for i in range(3000):
+        n = rng.choice([1, 1, 2, 5])
+        q = [v for _ in range(n) for v in (int(2 ** rng.uniform(0, 13)), int(2 ** rng.uniform(0, 11)))]
+        waves = rng.choice([1, 2, 4, 8])
+        args = (rng.choice([2, 3]), rng.choice([1, 2, 3, 4, 16 // waves]), waves, n, (C.c_int * len(q))(*q), i % 3 == 0)
+        assert lib.same_kz(*args), (q, args)
