@@ -164,7 +164,9 @@ int hydro_step(hydro_t h, double dt);
 
 /* nsteps Heun steps with the CFL dt kept on the device (async, no host
  * synchronisation).  The dt of each step comes from the previous step's
- * stage-2 epilogue (the first from a standalone reduction).  When t_end > 0
+ * second stage (the first from the pass that set the state, or from a
+ * reduction).  An unsplit 1-D mesh of at most 1024 cells takes its steps in
+ * one launch of one work-group, with the same results.  When t_end > 0
  * the step that would pass t_end is shortened to land on it and later steps
  * are no-ops.
  * hydro_step and hydro_step_auto enqueue kernels only (no allocation, memset
@@ -261,7 +263,8 @@ int hydro_tile_candidates(const hydro_config* cfg, int* tiles, int max);
  * warm-up steps.  Blocks until done.  If the run reached its limit while
  * tuning (timings of skipped steps mean nothing) the tiles are left as they
  * were and the call returns HYDRO_E_STATE; the handle stays usable.
- * steps_per_tile in [1, 64]. */
+ * steps_per_tile in [1, 64].  On a 1-D mesh whose hydro_step_auto runs in one
+ * launch the tiles are those of hydro_step and of batches. */
 int hydro_autotune(hydro_t h, int steps_per_tile, double t_end, int* tiles, double* ms_per_step);
 
 /* Event timing of the stage kernels, for measurement: after
@@ -269,7 +272,9 @@ int hydro_autotune(hydro_t h, int steps_per_tile, double t_end, int* tiles, doub
  * bracketed by HIP events on the handle's stream (cap = 0 turns timing off
  * and frees the events).  hydro_profile_read blocks, returns the summed
  * durations in milliseconds of the recorded stage-1 and stage-2 launches and
- * their counts (launches[0], launches[1]), and restarts the recording. */
+ * their counts (launches[0], launches[1]), and restarts the recording.  While
+ * timing is on, hydro_step_auto launches the stages on every mesh, also on the
+ * 1-D meshes whose steps it otherwise takes in one launch. */
 int hydro_profile(hydro_t h, int cap);
 int hydro_profile_read(hydro_t h, double* ms_stage1, double* ms_stage2, int64_t* launches);
 
@@ -345,16 +350,16 @@ const char* hydro_strerror(int status);
  * member status table in a caller-owned device workspace of hydro_batch_workspace_bytes(n, members)
  * bytes (0 when the members are invalid: NULL, repeated, broken, or on
  * different streams).  A batched step is one launch per (ndim, precision,
- * tile) group for each stage over all members' tiles, then one launch that
- * advances every member's time and device dt; each member keeps its own dt
+ * tile) group for each stage over all members' tiles, and a call ends with one
+ * launch that takes every member's last rate; each member keeps its own dt
  * and run limit (hydro_set_run_limit), and members that reached it are
  * skipped.  With use_graph != 0 and a non-default stream, the nsteps-step
  * sequence is captured once into a HIP graph and replayed (recaptured when
  * nsteps changes).  Without a graph, and when the stream is not being
  * captured, a batch of several groups spreads them over its stream and up
  * to two more streams of its own (made at the first such step, freed by
- * hydro_batch_destroy): each group's stages and its members' time / dt
- * update follow one another on one stream, step after step, forked from the
+ * hydro_batch_destroy): each group's stages follow one another on one
+ * stream, step after step, forked from the
  * members' stream at the call and joined back to it before the call
  * returns, so work enqueued on that stream afterwards sees every step.
  * hydro_batch_step is async; read results through the

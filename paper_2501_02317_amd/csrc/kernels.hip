@@ -444,9 +444,7 @@ __device__ __forceinline__ Links table_links(const int* __restrict__ side, int b
     return L;
 }
 
-// The sides of a launch's block: from the side codes of a refined mesh, else
-// from the uniform block grid (selected field by field, so the structure
-// stays in registers).
+// The refinement level of a block.
 __device__ __forceinline__ int block_level(const LevelStarts& starts, int blk) {
     int lev = 0;
 #pragma unroll
@@ -454,8 +452,8 @@ __device__ __forceinline__ int block_level(const LevelStarts& starts, int blk) {
     return lev;
 }
 
-// Whether cell c3 of block blk lies next to a side that a restriction slot
-// covers (a level jump onto finer blocks) on axis ax; the slot.
+// The restriction slot (a level jump onto finer blocks) of the side of block
+// blk that the cells at coordinate `at` of axis ax lie next to, or -1.
 __device__ __forceinline__ int jump_slot(const Geo& g, const int* __restrict__ side, int nres, int blk, int ax,
                                          int at) {
     const int code = at == 0 ? side[6 * blk + 2 * ax] : (at == g.n[ax] - 1 ? side[6 * blk + 2 * ax + 1] : 0);
@@ -463,6 +461,9 @@ __device__ __forceinline__ int jump_slot(const Geo& g, const int* __restrict__ s
     return slot >= 0 && slot < nres ? slot : -1;
 }
 
+// The sides of a launch's block: from the side codes of a refined mesh, else
+// from the uniform block grid (selected field by field, so the structure
+// stays in registers).
 __device__ __forceinline__ Links stage_links(const StageArgs& a, int blk) {
     const Geo& g = a.geo;
     const bool tab = a.side != nullptr;

@@ -153,7 +153,7 @@ namespace {
 
 // Tile rules of the batch autotuner for members of one or two dimensions:
 // a row width for every such member (0: the member's own) and a chunk length
-// (-1: the member's own, 0: about 2048 work-groups per member).  Rule 0
+// (-1: the member's own, 0: the automatic one of its group).  Rule 0
 // keeps every member's tile.  3-D members keep their tiles.
 struct BatchRule {
     int tx, kz;

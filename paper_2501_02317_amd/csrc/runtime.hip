@@ -41,7 +41,7 @@ struct hydro_ctx {
     Geo lgeo[kMaxLevels];          // per level: one block's extents and the level's cell widths
     int* d_side;                   // 6 side codes per leaf
     GhostTask* d_tasks;            // restriction slots by kernel axis, then prolongation slots
-    int nres, npro, res_off[4];
+    int nres, npro;
     int pro_off[kMaxLevels + 1];   // prolongation slots of level L: tasks [pro_off[L], pro_off[L + 1])
     double* gbuf;
     long long gcs;
@@ -656,7 +656,7 @@ struct SmrPlan {
     std::vector<int32_t> leaves;  // (level, c0, c1, c2), physical axes
     std::vector<int> side;        // 6 per leaf, kernel axes
     std::vector<GhostTask> tasks;
-    int nres = 0, npro = 0, res_off[4] = {0, 0, 0, 0};
+    int nres = 0, npro = 0;
     int pro_off[kMaxLevels + 1] = {0, 0, 0, 0, 0};
     int lev_start[kMaxLevels] = {0, 0, 0, 0}, lev_count[kMaxLevels] = {0, 0, 0, 0};
     long long gcs = 0;
@@ -838,14 +838,13 @@ bool smr_plan(const hydro_config* c, int nref, const int32_t* refined, SmrPlan& 
         }
     }
     for (int k = 0; k < 3; ++k) {
-        P.res_off[k] = (int)P.tasks.size();
         for (size_t i = 0; i < res[k].size(); ++i) {
             res[k][i].slot = (int)P.tasks.size();
             P.side[6 * res_at[k][i].first + res_at[k][i].second] = kSideSlot0 - res[k][i].slot;
             P.tasks.push_back(res[k][i]);
         }
     }
-    P.res_off[3] = P.nres = (int)P.tasks.size();
+    P.nres = (int)P.tasks.size();
     // prolongation slots by the fine block's level: each level's launch
     // follows the coarser one's, whose slots its coarse stencils may read
     for (int L = 0; L < kMaxLevels; ++L) {
@@ -983,7 +982,6 @@ int hydro_smr_create(const hydro_config* cfg, int nref, const int32_t* refined, 
     for (int d = 0; d < cfg->ndim; ++d) h->dV *= (cfg->hi[d] - cfg->lo[d]) / cfg->n[d];
     h->nres = P.nres;
     h->npro = P.npro;
-    for (int k = 0; k < 4; ++k) h->res_off[k] = P.res_off[k];
     h->gcs = P.gcs;
     const size_t nc = (size_t)h->ncomp;
     const size_t field = align_up(nc * (size_t)h->geo.ncells * P.nleaf * sizeof(double));
@@ -1158,9 +1156,10 @@ int hydro_step_auto(hydro_t h, int nsteps, double t_end) {
     if (rc) return rc;
     if (nsteps < 0 || !(t_end >= 0.0) || !std::isfinite(t_end)) return HYDRO_E_INVAL;
     if (nsteps == 0) return HYDRO_OK;
-    // The dt of the first step comes from a standalone reduction when the
+    // The dt of the first step comes from the rate that the set-up pass or a
+    // host-dt step left pending, else from a reduction of its own, when the
     // state changed since the last device-dt step; every later dt from the
-    // previous step's epilogue.
+    // previous step's second stage.
     (void)capturing(h);
     hipError_t e = enqueue_limits(h, 0.0, t_end);
     if (e == hipSuccess) e = enqueue_first_dt(h);
@@ -1923,8 +1922,8 @@ int hydro_batch_step(hydro_batch_t b, int nsteps) {
         if (e == hipSuccess) e = hipGraphLaunch(b->exec, b->stream);
     } else if (e == hipSuccess && b->groups.size() > 1 && !stream_capturing(b->stream) &&
                side_streams_ready(b)) {
-        // (a caller's capture of the forked form is not attempted: the
-        // refined-mesh step avoids it for the same reason)
+        // (a caller's capture of the forked form is not attempted; see
+        // capturing())
         e = enqueue_batch_steps_streams(b, nsteps);
     } else {
         e = enqueue_batch_steps(b, nsteps);
