@@ -64,6 +64,7 @@ struct hydro_ctx {
     bool rate_pending;
     bool no_limits;
     bool captured;    // the stream was captured during a call (see capturing())
+    bool step_captured;  // during hydro_step
     bool dt_asked;    // hydro_cfl_dt was called since the last host-dt step
     bool exposed;     // the caller has the state's address and may write there (until a set or device steps)
     // optional event timing of the stage launches
@@ -493,7 +494,8 @@ hipError_t timed_stage(hydro_t h, int mode, const StageArgs& a) {
 // same dependencies instead (enqueue_step_streams_graph).  The results do not
 // depend on the form.
 // A handle that was captured once may be changed by replays that the host
-// does not see: from then on rate_pending and no_limits are not relied on.
+// does not see: from then on rate_pending and no_limits are not relied on, and
+// dt_valid not where a replay may be a host-dt step (dt_known).
 bool capturing(hydro_t h) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     const bool on = hipStreamIsCapturing(h->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
@@ -587,6 +589,8 @@ hipError_t enqueue_finalize(hydro_t h) {
     return e;
 }
 
+bool dt_known(hydro_t h) { return h->dt_valid && !h->step_captured; }
+
 // The CFL rate of the current state pending in the control block.  One that is
 // pending already is taken again where the state may have changed since
 // without the host seeing it: by a replay, or through its address.
@@ -609,7 +613,7 @@ hipError_t enqueue_dt(hydro_t h) {
 // Before the device-dt steps of a call: a dt for the first one, pending where
 // the steps keep their own books.
 hipError_t enqueue_first_dt(hydro_t h) {
-    if (h->dt_valid) return hipSuccess;
+    if (dt_known(h)) return hipSuccess;
     return step_chains(h) ? enqueue_rate(h) : enqueue_dt(h);
 }
 
@@ -1123,7 +1127,7 @@ int hydro_cfl_dt(hydro_t h, double* dt) {
     if (rc) return rc;
     if (!dt) return HYDRO_E_INVAL;
     h->dt_asked = true;
-    hipError_t e = h->dt_valid ? hipSuccess : enqueue_dt(h);
+    hipError_t e = dt_known(h) ? hipSuccess : enqueue_dt(h);
     if (e != hipSuccess) return fail(h, e);
     rc = read_ctrl(h);
     if (rc) return rc;
@@ -1135,7 +1139,7 @@ int hydro_step(hydro_t h, double dt) {
     int rc = usable(h);
     if (rc) return rc;
     if (!(dt > 0.0) || !std::isfinite(dt)) return HYDRO_E_INVAL;
-    (void)capturing(h);
+    if (capturing(h)) h->step_captured = true;
     // The new state's rate is taken by the step for a caller that asks for
     // every dt; one that brings its own pays nothing for it (four FP64 steps of
     // 128^3: 808 us with it, 784 without).  Where the caller may write the
@@ -1786,7 +1790,7 @@ hipError_t enqueue_batch_first_dt(hydro_batch_t b) {
     hipError_t e = hipSuccess;
     for (hydro_t h : b->members) {
         (void)capturing(h);
-        if (!h->dt_valid && e == hipSuccess) e = enqueue_rate(h);
+        if (!dt_known(h) && e == hipSuccess) e = enqueue_rate(h);
     }
     return e;
 }

@@ -22,12 +22,10 @@ def H():
     return hydro
 
 
-@pytest.mark.parametrize("n,blocks,refined", MESHES)
+@pytest.mark.parametrize("n,blocks,refined,streams",
+                         [(*m, False) for m in MESHES] + [(*m, True) for m in MESHES if m[1] and not m[2]])
 @pytest.mark.parametrize("order", ORDERS)
-@pytest.mark.parametrize("streams", [False, True])
 def test_dt_after_any_order(H, n, blocks, refined, order, streams):
-    if streams and (refined or not blocks):
-        pytest.skip("no block streams")
     say("host steps", n, blocks, refined, order, streams)
     c = wl.turbulence_3d(n=n, mach=0.6, seed=11)
 
