@@ -796,7 +796,12 @@ __device__ __forceinline__ void load_as_double(const T* __restrict__ F, long lon
 // the plane (4 TX + 4 TY <= TX TY).
 // Work-groups per CU the compiler is asked to fit: the FP32 path keeps four
 // 256-thread groups per CU (16 waves); FP64 needs more registers per thread.
-template <int NDIM, typename R, int MODE>
+// FEW: the form of the FP64 3-D Heun stage 2 for at most two waves on a SIMD,
+// where a march is bound by the latency of its plane's loads and not by the
+// waves that fit: everything is loaded a plane ahead.
+constexpr bool has_few(int ndim, bool fp64, int mode) { return ndim == 3 && fp64 && mode == MODE_STAGE2; }
+
+template <int NDIM, typename R, int MODE, bool FEW = false>
 struct StageOccupancy {
     // Input ring: the raw input values of a cell, read for its conversion
     // when its plane enters the z stencil, are kept in LDS until the update
@@ -814,7 +819,7 @@ struct StageOccupancy {
     static constexpr bool kPred = MODE == MODE_VL2_PRED || MODE == MODE_VL2_PRED_C;
     static constexpr bool kHeun = MODE == MODE_STAGE1 || MODE == MODE_STAGE2 || MODE == MODE_STAGE2_R;
     static constexpr bool kRing =
-        kPred || (sizeof(R) == 4 && kHeun);
+        FEW || kPred || (sizeof(R) == 4 && kHeun);
     // occupancy range (waves per SIMD) the compiler aims for: at least
     // kWaves (its register budget), at most kWavesMax (8: no bound)
     // The FP64 stage 2 holds three (twelve waves on a CU) without the double
@@ -822,7 +827,7 @@ struct StageOccupancy {
     // 256^3 against 689 us in eight waves with one barrier.
     // In 2-D the FP64 stages hold four with a few spilled registers (4096 x
     // 1024: a step 200 -> 187 us, 1024^2 72 -> 66 us against three waves).
-    static constexpr int kWaves = sizeof(R) == 4 || NDIM == 2 ? 4 : (NDIM == 3 ? 3 : 2);
+    static constexpr int kWaves = FEW ? 2 : (sizeof(R) == 4 || NDIM == 2 ? 4 : (NDIM == 3 ? 3 : 2));
     static constexpr int kWavesMax = 8;
     // The raw halo cell of the next plane loaded one iteration ahead, so the
     // barrier after the plane's W does not wait for it: ten more registers.
@@ -831,7 +836,12 @@ struct StageOccupancy {
     // mixed van Leer predictor gain about 2 % (192^3 in blocks 128 -> 124 us);
     // the FP64 stages lose 5-6 % (a wave per SIMD), the mixed van Leer
     // corrector 17 % in 3-D (383 -> 447 us), and do without.
-    static constexpr bool kHaloPrefetch = NDIM >= 2 && sizeof(R) == 4 && (kHeun || kPred);
+    static constexpr bool kHaloPrefetch = FEW || (NDIM >= 2 && sizeof(R) == 4 && (kHeun || kPred));
+    // U^n of the next updated plane loaded during this plane's update, before
+    // its stores.  With the input ring and the halo prefetch it is what FEW is:
+    // 96^3 in chunks of 64 planes (four waves on a CU) a step 512 -> 467 us, of
+    // 16 planes 148 -> 138 us, 192^3 in chunks of 64 (eight waves) 698 -> 661 us.
+    static constexpr bool kBaseAhead = FEW;
     // U^n for the update loaded before the faces instead of after them, so it
     // arrives beside them.  Measured: the mixed 2-D van Leer corrector 68 -> 63
     // us at 4096 x 1024; the mixed 2-D Heun stage 2 is even there and loses 2 %
@@ -847,7 +857,7 @@ struct StageOccupancy {
     static constexpr bool kPrio = NDIM == 3;
 };
 
-template <int NDIM, typename R, int MODE, int TX, int TY>
+template <int NDIM, typename R, int MODE, int TX, int TY, bool FEW>
 __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, bool leader) {
     constexpr int NC = NDIM + 2;
     constexpr bool HY = (NDIM == 3);
@@ -1012,7 +1022,7 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     if (CTRL_FIRST && !take_step()) return;
     const Gas<R> gr = make_gas<R>(g.gamma);
 
-    constexpr bool RING = StageOccupancy<NDIM, R, MODE>::kRing && HZ;
+    constexpr bool RING = StageOccupancy<NDIM, R, MODE, FEW>::kRing && HZ;
     constexpr int RS = HW;  // ring slots: planes k .. k + HW - 1 between iterations
     __shared__ double sRaw[RING ? RS : 1][RING ? NC : 1][RING ? NT : 1];
     // rows of the W tile: in 1-D and 2-D a tile is one row (row offset RO)
@@ -1033,9 +1043,10 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     double ui[NC];
     int vmi = VM_NONE;
     // the raw halo cell of this thread (HALO_PF: the next plane's, in flight)
-    constexpr bool HALO_PF = StageOccupancy<NDIM, R, MODE>::kHaloPrefetch;
-    constexpr bool PRIO = StageOccupancy<NDIM, R, MODE>::kPrio;
-    constexpr bool BASE_EARLY = StageOccupancy<NDIM, R, MODE>::kBaseEarly;
+    constexpr bool HALO_PF = StageOccupancy<NDIM, R, MODE, FEW>::kHaloPrefetch;
+    constexpr bool PRIO = StageOccupancy<NDIM, R, MODE, FEW>::kPrio;
+    constexpr bool BASE_EARLY = StageOccupancy<NDIM, R, MODE, FEW>::kBaseEarly;
+    constexpr bool BASE_AHEAD = StageOccupancy<NDIM, R, MODE, FEW>::kBaseAhead && NEED_BASE;
     double uhalo[NC];
 
     // interior plane z (any z: outside the mesh it is a ghost plane)
@@ -1129,6 +1140,13 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     }
     if (!CTRL_FIRST && !take_step()) return;
     if (HALO_PF && hact && z0 < z1) load_halo(z0, uhalo);
+    double uahead[NC];  // (BASE_AHEAD) U^n of the next updated plane
+    auto load_ahead = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            uahead[c] = plane_load<double, kNonTemporal>(a.base, c * N + boff + (long long)k * P, ext8, col32 * 8u);
+    };
+    if (BASE_AHEAD && act && z0 < z1) load_ahead(z0);
 
     // One iteration: plane k + HW enters the stencil (its raw data ui, the
     // ghost treatment vmi), the plane after it is loaded into ui in its place,
@@ -1293,7 +1311,10 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
 #pragma unroll
                 for (int c = 0; c < NC; ++c) uin[c] = plane_load(a.in, c * N + kP, ext8, colb);
             }
-            if (NEED_BASE && !BASE_EARLY) {
+            if (BASE_AHEAD) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) ubase[c] = uahead[c];
+            } else if (NEED_BASE && !BASE_EARLY) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c) ubase[c] = plane_load<double, kNonTemporal>(a.base, c * N + kP, ext8, colb);
             }
@@ -1317,8 +1338,15 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
                     r = ubase[c] + acc;
                 else
                     r = 0.5 * ubase[c] + 0.5 * (uin[c] + acc);
-                if (!PRIM_OUT) plane_store<double, EPILOGUE ? kNonTemporal : 0>(a.out, c * N + kP, ext8, colb, r);
+                if (!PRIM_OUT && !BASE_AHEAD)
+                    plane_store<double, EPILOGUE ? kNonTemporal : 0>(a.out, c * N + kP, ext8, colb, r);
                 unew[c] = r;
+            }
+            if (BASE_AHEAD) {
+                if (k + 1 < z1) load_ahead(k + 1);
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    plane_store<double, EPILOGUE ? kNonTemporal : 0>(a.out, c * N + kP, ext8, colb, unew[c]);
             }
             if (PRIM_OUT) {
                 // the predicted state is kept only as primitive variables of type R
@@ -1368,9 +1396,9 @@ __device__ __forceinline__ void stage_body(const StageArgs& a, int b, int blk, b
     }
 }
 
-template <int NDIM, typename R, int MODE, int TX, int TY>
+template <int NDIM, typename R, int MODE, int TX, int TY, bool FEW>
 __global__ __launch_bounds__(TX * TY)
-__attribute__((amdgpu_waves_per_eu(StageOccupancy<NDIM, R, MODE>::kWaves, StageOccupancy<NDIM, R, MODE>::kWavesMax)))
+__attribute__((amdgpu_waves_per_eu(StageOccupancy<NDIM, R, MODE, FEW>::kWaves, StageOccupancy<NDIM, R, MODE, FEW>::kWavesMax)))
 void stage_kernel(StageArgs a) {
     if (!a.chain && a.use_device_dt && a.ctrl->done) return;  // uniform over the grid
     // work-group -> (block, work-group within the block), block after block:
@@ -1384,14 +1412,14 @@ void stage_kernel(StageArgs a) {
         blk += q;
         wg -= q * per;
     }
-    stage_body<NDIM, R, MODE, TX, TY>(a, wg, blk, blockIdx.x == 0);
+    stage_body<NDIM, R, MODE, TX, TY, FEW>(a, wg, blk, blockIdx.x == 0);
 }
 
 // Batched stage: work-group -> (member, work-group of the member) from a
 // table; members that reached their run limit are skipped.
-template <int NDIM, typename R, int MODE, int TX, int TY>
+template <int NDIM, typename R, int MODE, int TX, int TY, bool FEW>
 __global__ __launch_bounds__(TX * TY)
-__attribute__((amdgpu_waves_per_eu(StageOccupancy<NDIM, R, MODE>::kWaves, StageOccupancy<NDIM, R, MODE>::kWavesMax)))
+__attribute__((amdgpu_waves_per_eu(StageOccupancy<NDIM, R, MODE, FEW>::kWaves, StageOccupancy<NDIM, R, MODE, FEW>::kWavesMax)))
 void stage_kernel_batch(
     const MeshDesc* __restrict__ descs, const int2* __restrict__ blk) {
     const int2 e = blk[xcd_remap(blockIdx.x, gridDim.x)];
@@ -1423,7 +1451,7 @@ void stage_kernel_batch(
         a.out = d.U;
         a.want_dt = 1;
     }
-    stage_body<NDIM, R, MODE, TX, TY>(a, e.y, 0, e.y == 0);
+    stage_body<NDIM, R, MODE, TX, TY, FEW>(a, e.y, 0, e.y == 0);
 }
 
 // ------------------------------------------------- 1-D meshes of one work-group
@@ -2360,6 +2388,12 @@ int grid_for(long long work, int block, int cap) {
     return (int)(gb < cap ? gb : cap);
 }
 
+// Work-groups of 512 threads: no more than one fits on a CU in either form.
+template <int NDIM, typename R, int MODE, int TX, int TY>
+constexpr bool always_few() {
+    return has_few(NDIM, sizeof(R) == 8, MODE) && TX * TY > 256;
+}
+
 // What the device holds of this stage kernel at once (zero if the runtime
 // cannot tell).
 template <int NDIM, typename R, int MODE, int TX, int TY>
@@ -2371,7 +2405,8 @@ Slots stage_slots() {
         if (hipDeviceGetAttribute(&o.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return Slots{0, 0, 0};
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &nb, reinterpret_cast<const void*>(&stage_kernel<NDIM, R, MODE, TX, TY>), TX * TY, 0) !=
+                &nb, reinterpret_cast<const void*>(&stage_kernel<NDIM, R, MODE, TX, TY, always_few<NDIM, R, MODE, TX, TY>()>),
+                TX * TY, 0) !=
             hipSuccess)
             return Slots{0, 0, 0};
         o.per_cu = nb;
@@ -2380,28 +2415,58 @@ Slots stage_slots() {
     return slots;
 }
 
+// Whether a launch of the given work-groups takes the FEW form: where they put
+// no more than two waves on a SIMD (eight on a CU).  With twelve the other form
+// is faster (256^3 650 against 689 us for its predecessor in eight waves), but
+// work-groups of 512 threads never get there: 192^3 in 32 x 16 a step 743 ->
+// 708 us, in 64 x 8 771 -> 728 us.
+template <int NDIM, typename R, int MODE, int TX, int TY>
+bool few_waves(long long wgs) {
+    if constexpr (!has_few(NDIM, sizeof(R) == 8, MODE)) return false;
+    if (always_few<NDIM, R, MODE, TX, TY>()) return true;
+    const Slots sl = stage_slots<NDIM, R, MODE, TX, TY>();
+    return wgs * sl.waves <= 8ll * sl.cus;
+}
+
 template <int NDIM, typename R, int MODE, int TX, int TY>
 hipError_t launch_stage_t(const LaunchCtx& L, hipStream_t s) {
+    constexpr bool kRegular = !always_few<NDIM, R, MODE, TX, TY>();
     if (L.slots) {
         *L.slots = stage_slots<NDIM, R, MODE, TX, TY>();
     } else if (L.a) {
         StageArgs a = *L.a;
         const long long nb = (long long)a.tiles_x * a.tiles_y * a.chunks_z * a.nblk;
         if (a.nblk < 1 || nb > 0x7fffffffll) return hipErrorInvalidValue;
-        if (L.rec) {
-            L.rec->func = reinterpret_cast<const void*>(&stage_kernel<NDIM, R, MODE, TX, TY>);
-            L.rec->grid = dim3((unsigned)nb);
-            L.rec->block = dim3(TX * TY);
-            L.rec->args = a;
-            return hipSuccess;
+        auto launch = [&](auto* kernel) {
+            if (L.rec) {
+                L.rec->func = reinterpret_cast<const void*>(kernel);
+                L.rec->grid = dim3((unsigned)nb);
+                L.rec->block = dim3(TX * TY);
+                L.rec->args = a;
+                return hipSuccess;
+            }
+            hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(TX * TY), 0, s, a);
+            return hipGetLastError();
+        };
+        if constexpr (has_few(NDIM, sizeof(R) == 8, MODE)) {
+            // with the work-groups of the launches on the other streams
+            if (few_waves<NDIM, R, MODE, TX, TY>(a.conc > a.nblk ? nb / a.nblk * a.conc : nb))
+                return launch(&stage_kernel<NDIM, R, MODE, TX, TY, true>);
         }
-        hipLaunchKernelGGL((stage_kernel<NDIM, R, MODE, TX, TY>), dim3((unsigned)nb), dim3(TX * TY), 0, s, a);
+        if constexpr (kRegular) return launch(&stage_kernel<NDIM, R, MODE, TX, TY, false>);
     } else if constexpr (MODE == MODE_RHS || MODE == MODE_STAGE2_R || MODE == MODE_VL2_PRED_C || MODE == MODE_VL2_CORR_C) {
         return hipErrorInvalidValue;  // not a batch member's stage
     } else {
         if (L.nblk <= 0) return hipSuccess;
-        hipLaunchKernelGGL((stage_kernel_batch<NDIM, R, MODE, TX, TY>), dim3(L.nblk), dim3(TX * TY), 0, s,
-                           L.d, L.blk);
+        auto launch = [&](auto* kernel) {
+            hipLaunchKernelGGL(kernel, dim3(L.nblk), dim3(TX * TY), 0, s, L.d, L.blk);
+            return hipGetLastError();
+        };
+        if constexpr (has_few(NDIM, sizeof(R) == 8, MODE)) {
+            if (few_waves<NDIM, R, MODE, TX, TY>(L.nblk))
+                return launch(&stage_kernel_batch<NDIM, R, MODE, TX, TY, true>);
+        }
+        if constexpr (kRegular) return launch(&stage_kernel_batch<NDIM, R, MODE, TX, TY, false>);
     }
     return hipGetLastError();
 }
