@@ -788,12 +788,12 @@ __device__ __forceinline__ void load_as_double(const T* __restrict__ F, long lon
 
 // One stage over a TX x TY tile column and a chunk of kz planes.
 //
-// Software pipeline per plane k (kernel z): raw U of the interior plane k+3
-// and of the halo cells of plane k+1 are loaded one iteration before they are
-// converted, and U at plane k for the update is loaded at the top of the
-// iteration and used after the flux phase, so global loads stay in flight
-// across the two LDS barriers.  Each thread owns at most one halo cell of
-// the plane (4 TX + 4 TY <= TX TY).
+// Software pipeline per plane k (kernel z): raw U of the interior plane k+3 is
+// loaded one iteration before it is converted, so global loads stay in flight
+// across the two LDS barriers; where StageOccupancy says so the halo cells of
+// plane k+1 are too, and the input at plane k for the update comes from a ring
+// in LDS.  Each thread owns at most one halo cell of the plane (4 TX + 4 TY <=
+// TX TY).
 // Work-groups per CU the compiler is asked to fit: the FP32 path keeps four
 // 256-thread groups per CU (16 waves); FP64 needs more registers per thread.
 // FEW: the form of the FP64 3-D Heun stage 2 for at most two waves on a SIMD,
@@ -824,7 +824,8 @@ struct StageOccupancy {
     // kWaves (its register budget), at most kWavesMax (8: no bound)
     // The FP64 stage 2 holds three (twelve waves on a CU) without the double
     // buffers of W and the fluxes that one barrier per plane takes: 653 us at
-    // 256^3 against 689 us in eight waves with one barrier.
+    // 256^3 against 689 us in eight waves with one barrier.  (Launches of no
+    // more than eight waves: FEW.)
     // In 2-D the FP64 stages hold four with a few spilled registers (4096 x
     // 1024: a step 200 -> 187 us, 1024^2 72 -> 66 us against three waves).
     static constexpr int kWaves = FEW ? 2 : (sizeof(R) == 4 || NDIM == 2 ? 4 : (NDIM == 3 ? 3 : 2));
@@ -834,8 +835,8 @@ struct StageOccupancy {
     // Measured at 256^3: the mixed Heun stage 2 holds them (462 -> 452 us at
     // four waves per SIMD), the mixed stage 1, the mixed 2-D stages and the
     // mixed van Leer predictor gain about 2 % (192^3 in blocks 128 -> 124 us);
-    // the FP64 stages lose 5-6 % (a wave per SIMD), the mixed van Leer
-    // corrector 17 % in 3-D (383 -> 447 us), and do without.
+    // the FP64 stages lose 5-6 % (a wave per SIMD; FEW has none to lose), the
+    // mixed van Leer corrector 17 % in 3-D (383 -> 447 us), and do without.
     static constexpr bool kHaloPrefetch = FEW || (NDIM >= 2 && sizeof(R) == 4 && (kHeun || kPred));
     // U^n of the next updated plane loaded during this plane's update, before
     // its stores.  With the input ring and the halo prefetch it is what FEW is:

@@ -17,10 +17,12 @@ Tile default_tile(const Geo& g, int precision, int mode) {
     } else if (g.ndim == 3) {
         // From a sweep at 256^3: 32 x 16 halves the share of halo cells and
         // extra faces where the occupancy allows it; 32 x 8 where a larger
-        // work-group would cost occupancy (the FP64 kernels).  16 x 16 is 2-8 % behind those on a
-        // mesh that each fills (even in FP64) and takes over where it pads
-        // less: 48^3 mixed 28 against 31 us a step, 101 x 75 x 50 FP64 57
-        // against 65 us.
+        // work-group would cost occupancy (the FP64 kernels).  16 x 16 is 5-7 %
+        // behind in the mixed kernels on a mesh that each fills (256^3 339 +
+        // 444 against 362 + 476 us a step) and even in FP64 (a step of 128^3,
+        // 192^3, 256^3 and 384^3 within 1 %, both integrators: 256^3 535 + 648
+        // against 541 + 646); it takes over where it pads less: 48^3 mixed 28
+        // against 31 us a step, 101 x 75 x 50 FP64 57 against 65 us.
         const bool narrow = precision == 0;
         auto padded = [&](int tx, int ty) {
             return (double)((g.n[0] + tx - 1) / tx * tx) * ((g.n[1] + ty - 1) / ty * ty);
@@ -94,9 +96,10 @@ int balanced_kz(int n2, int kz) {
 // FP64 89 and 21 us), and a last round of a few work-groups costs as much as a
 // full one (160^3 mixed: 316 us with 800 work-groups on 768 places, 225 us
 // with 700) -- unless each XCD has a block of its own, whose columns' shorter
-// last chunks come last and two deep beside the others (192^3 van Leer in
-// eight blocks: a step 332 us with 432 equal work-groups on 512 places, 310 us
-// with 576 in chunks of 28 and 12).
+// last chunks come last and two deep beside the others (in eight blocks, with
+// the rule and without: 192^3 mixed a step 350 and 362 us, van Leer 292 and
+// 301 us -- 576 work-groups in chunks of 28 and 12 on 512 places, or 432 equal
+// ones; 160^3 FP64 311 and 320 us; 224^3 mixed and 192^3 and 256^3 FP64 even).
 int auto_kz(int ndim, const Slots& sl, const MarchCols* m, int n, double* time) {
     if (time) *time = 0.0;
     if (ndim == 1) return 1;
