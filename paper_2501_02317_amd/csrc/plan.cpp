@@ -20,7 +20,7 @@ Tile default_tile(const Geo& g, int precision, int mode) {
         // work-group would cost occupancy (the FP64 kernels).  16 x 16 is 5-7 %
         // behind in the mixed kernels on a mesh that each fills (256^3 339 +
         // 444 against 362 + 476 us a step) and even in FP64 (a step of 128^3,
-        // 192^3, 256^3 and 384^3 within 1 %, both integrators: 256^3 535 + 648
+        // 192^3, 256^3 and 384^3 within 2 %, both integrators: 256^3 535 + 648
         // against 541 + 646); it takes over where it pads less: 48^3 mixed 28
         // against 31 us a step, 101 x 75 x 50 FP64 57 against 65 us.
         const bool narrow = precision == 0;
