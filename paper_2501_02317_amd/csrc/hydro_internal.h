@@ -21,7 +21,8 @@ constexpr int kMaxComp = 5;
 //
 // The rate of the current state is still in set `par` of the slots while
 // pend is not kPendNone; then dt_raw (and after a step t, steps and done) are
-// those of before it.  Outside such a state both sets are zero.
+// those of before it.  Outside such a state set `par` is zero; a first stage
+// clears the set that its step will use, a control launch both.
 struct Ctrl {
     double dt_raw;                  // cfl / (max CFL rate) of the current state
     double t;                       // simulation time

@@ -48,7 +48,7 @@ struct hydro_ctx {
     int32_t* leaves;               // host: (level, c0, c1, c2) per leaf
     Tile tile[2];  // stage 1 (and the rhs), stage 2
     bool tile_set;  // by the caller or an autotuner (else the defaults)
-    int kz[2][2];   // their automatic chunk lengths, once known (stage_tile)
+    int kz[2][2];   // the chunk lengths of their launches, once known (stage_tile)
     hipStream_t stream;
     int ncomp;
     double dV;
@@ -374,7 +374,8 @@ hipError_t enqueue_step_streams(hydro_t h, bool device_dt, double dt) {
         a.base = h->U;
         a.out = h->U;
         a.want_dt = device_dt ? 1 : 0;
-        if (e == hipSuccess) e = launch_stage(h->cfg.precision, stage2_mode(&h->cfg), stage_tile(h, 1, stage2_mode(&h->cfg), a), a,
+        if (e == hipSuccess)
+            e = launch_stage(h->cfg.precision, stage2_mode(&h->cfg), stage_tile(h, 1, stage2_mode(&h->cfg), a), a,
                              h->bs[g]);
     }
     for (int i = 0; i < h->nbs && e == hipSuccess; ++i) {
