@@ -61,6 +61,15 @@ extern "C" int same_kz(int ndim, int per_cu, int waves, int n, const int* q, int
     const int ka = auto_kz(ndim, sl, m.data(), n, &a), kb = every_kz(ndim, sl, m.data(), n, &b);
     return ka == kb && a == b;
 }
+extern "C" int default_shape(int ndim, int precision, int n0, int n1, int n2) {
+    Geo g{};
+    g.ndim = ndim;
+    g.n[0] = n0;
+    g.n[1] = n1;
+    g.n[2] = n2;
+    const Tile t = default_tile(g, precision, MODE_STAGE1);
+    return 1000 * t.tx + t.ty;
+}
 // members: (ndim, precision, integrator, n0, n1, n2, tx, ty, kz) each, tx 0: the default tile.
 // out: work-groups, groups, then per member (in descriptor order) its index, tiles and chunks.
 extern "C" int plan(int n, const int* q, int rule, int tuned, int* out) {
@@ -155,6 +164,15 @@ def test_tuned_layout_is_the_timed_one_and_fits(lib):
             got = plan(lib, m, r, tuned=True)
             assert got[0] <= most, (m, r, got[0], most)
             assert got == rules[r], (m, r)
+
+
+def test_default_tiles_are_shared(lib):
+    """Ragged 2-D meshes and cubes of both default widths: one launch for each
+    dimensionality, where each member's own tile would make five."""
+    m = [member(n) for n in [(64,) * 2, (96,) * 2, (200, 160), (384, 100), (512,) * 2, (48,) * 3, (64,) * 3]]
+    # rows of 64, 128 and 256; 16 x 16 and 32 x 16
+    assert len({(q[0], lib.default_shape(q[0], q[1], *q[3:6])) for q in m}) == 5
+    assert plan(lib, m, 0)[1] == 2
 
 
 def test_chunk_length_has_the_least_modelled_time(lib):

@@ -35,6 +35,8 @@ def test_autotuned_mix_equals_alone(H, precision, graph):
     say("batch autotune 2-D and 3-D", precision, graph)
     ms = [_mesh(H, i, s, precision) for i in range(len(SIZES))]
     b = H.Batch(ms, use_graph=graph)
+    # members of the default tiles share launches
+    assert b.info()["groups"] < len({(h.ndim, h.get_tile(1)[:2]) for h in ms})
     b.autotune(steps_per_rule=1)
     done, steps, flags = b.status()
     assert steps == [13] * len(ms) and not any(flags)
